@@ -1,7 +1,9 @@
 """Benchmark of the PSDF hot path on one MI355X.
 
 A step is one psdf_batch call (value, winning obstacle and edge, and the pose
-gradient of every stage) on the 'c5' workload: 64 independent instances,
+gradient of every stage) that evaluates every (stage, obstacle) pair
+(PSDF_BATCH_EXHAUSTIVE: psdf_batch by itself would cull this batch; the same
+outputs, reported as `culled`) on the 'c5' workload: 64 independent instances,
 each a hexagonal footprint (circumradius 0.5 m, vertex radii jittered
 +-10 %) at N = 50 stage poses along a random smooth path, against 65536 edges
 from 16384 rectangles (sides U[0.1, 0.8] m) whose centres follow a
@@ -13,6 +15,9 @@ Prints one JSON line:
   value        stage x edge evaluations per second of whole psdf_batch calls
                (K calls, each a replay of the plan's HIP graph, between one
                event pair);
+  culled       the same call as psdf_batch makes it by itself on this batch:
+               bounds on every pair, exact evaluations of the few obstacles
+               per stage that they leave; outputs equal bit for bit;
   screened     the same outputs (bit for bit) from the certified screened
                forms on the same inputs: the bound-threshold form, and the
                top-K forms ranked by the edge distance and by the screener
@@ -298,7 +303,10 @@ def extras(torch, api, flops, inputs):
     log("c4: building 512 instances")
     c4 = inputs.c4(512)
     pairs4 = sum(i.N * i.E for i in c4)
-    b = api.Batch(c4, graph=True, autotune=True)
+    b = api.Batch(c4, graph=True)
+    t_cull = timed_calls(torch, b.run, 50, 10)
+    b.close()
+    b = api.Batch(c4, graph=True, autotune=True, exhaustive=True)
     b.autotune()
     t_batch = timed_calls(torch, b.run, 20, 3)
     views = [b.instance_views(k) for k in range(b.n_inst)]
@@ -308,23 +316,26 @@ def extras(torch, api, flops, inputs):
             api.psdf_grad(fp, ps, e)
     t_loop = timed_calls(torch, loop, 3, 1)
     f4 = sum(flops.flops_instance(len(i.footprint), i.N, i.edges, i.obst_off) for i in c4)
-    out["c4_batch"] = dict(pairs=pairs4, batch_ms=t_batch, loop_ms=t_loop,
+    out["c4_batch"] = dict(pairs=pairs4, batch_ms=t_batch, culled_ms=t_cull, loop_ms=t_loop,
                            batch_evals_per_s=pairs4 / (t_batch * 1e-3),
                            loop_evals_per_s=pairs4 / (t_loop * 1e-3),
                            batch_tflops=f4 / (t_batch * 1e-3) / 1e12, shape=b.info())
-    log(f"c4: batch {t_batch:.3f} ms, loop {t_loop:.3f} ms")
+    log(f"c4: batch {t_batch:.3f} ms, culled {t_cull:.3f} ms, loop {t_loop:.3f} ms")
     b.close()
     del c4, views
 
     c2b = inputs.c2_batch(256)
     pairs2 = sum(i.N * i.E for i in c2b)
-    b = api.Batch(c2b, graph=True, autotune=True)
+    b = api.Batch(c2b, graph=True)
+    t_cull = timed_calls(torch, b.run, 50, 10)
+    b.close()
+    b = api.Batch(c2b, graph=True, autotune=True, exhaustive=True)
     b.autotune()
     t = timed_calls(torch, b.run, 20, 3)
     f2 = sum(flops.flops_instance(len(i.footprint), i.N, i.edges, i.obst_off) for i in c2b)
-    out["c2x256_batch"] = dict(pairs=pairs2, ms=t, evals_per_s=pairs2 / (t * 1e-3),
+    out["c2x256_batch"] = dict(pairs=pairs2, ms=t, culled_ms=t_cull, evals_per_s=pairs2 / (t * 1e-3),
                                tflops=f2 / (t * 1e-3) / 1e12, shape=b.info())
-    log(f"c2x256: {t:.3f} ms")
+    log(f"c2x256: {t:.3f} ms, culled {t_cull:.3f} ms")
     b.close()
     del c2b
 
@@ -531,7 +542,7 @@ def main():
     pairs = sum(i.N * i.E for i in c5)
     if args.counters:
         if args.counters == "c5":
-            b = api.Batch(c5, graph=False)
+            b = api.Batch(c5, graph=False, exhaustive=True)
             for _ in range(args.steps):
                 b.run()
             b.close()
@@ -552,8 +563,8 @@ def main():
                               copy_bytes=src.numel() * 4)))
         return
 
-    bg = api.Batch(c5, graph=True)       # replays the plan's own HIP graph
-    be = api.Batch(c5, graph=False)      # eager launches (kernel timing, screened forms)
+    bg = api.Batch(c5, graph=True, exhaustive=True)    # replays the plan's own HIP graph
+    be = api.Batch(c5, graph=False, exhaustive=True)   # eager (kernel timing, screened forms)
     if bg.info() != be.info():
         raise RuntimeError("the two plans of the same batch chose different launch shapes")
     be.run()
@@ -625,6 +636,16 @@ def main():
                       source_sha256=source_hash("batch_kernel", info)),
         wall_s=wall,
     )
+    bc = api.Batch(c5, graph=True)       # psdf_batch by itself: culled
+    t_c = timed_calls(torch, bc.run, args.steps, args.warmup)
+    same = all(torch.equal(x.view(torch.uint8), y.view(torch.uint8))
+               for x, y in zip((bc.d, bc.edge, bc.obst, bc.grad, bc.keys), ref))
+    if not same:
+        raise RuntimeError("the culled psdf_batch differs from the full evaluation")
+    res["culled"] = dict(ms_per_call=t_c, pairs_per_s=pairs / (t_c * 1e-3), speedup=ms_step / t_c,
+                         bitwise_equal=same)
+    log(f"c5 culled psdf_batch: {t_c:.4f} ms per call")
+    bc.close()
     if args.screened:
         res["screened"] = screened_forms(torch, api, inputs, c5, be, ref, args.steps)
     bg.close()

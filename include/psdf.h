@@ -324,7 +324,8 @@ typedef struct psdf_batch_plan psdf_batch_plan;
 
 enum {
   PSDF_BATCH_GRAPH = 1,    /* replay a captured hipGraph (captured on first run) */
-  PSDF_BATCH_AUTOTUNE = 2  /* psdf_batch_autotune may pick the launch shape */
+  PSDF_BATCH_AUTOTUNE = 2, /* psdf_batch_autotune may pick the launch shape */
+  PSDF_BATCH_EXHAUSTIVE = 4 /* psdf_batch evaluates every (stage, obstacle) pair */
 };
 
 /* Build a plan.  desc: host array of n_inst descriptors; footprints: host
@@ -342,13 +343,19 @@ int psdf_batch_plan_create(psdf_batch_plan** plan, const psdf_batch_desc* desc, 
 void psdf_batch_plan_destroy(psdf_batch_plan* plan);
 
 /* Evaluate every instance: d, edge, obst, grad and keys as described above.
- * The launches of the different footprint sizes run concurrently: they fork
+ * A batch of enough (stage, obstacle) pairs, with enough obstacles per stage,
+ * is evaluated culled: a bound on every pair (from the obstacle's bounding
+ * box) leaves a few obstacles per stage, which alone are evaluated, in two
+ * or three launches on `stream`; the outputs are those of the full
+ * evaluation bit for bit, for every input.  With PSDF_BATCH_EXHAUSTIVE, or
+ * after psdf_batch_set_shape, every pair is evaluated.  In the full
+ * evaluation the launches of the different footprint sizes run concurrently: they fork
  * from `stream` onto up to three plan-owned side streams with events and
  * join back before the final kernel, so the call still completes in
  * `stream` order.  With PSDF_BATCH_GRAPH the first call (and any call whose
  * pointers differ from the captured ones) captures the launch into a
  * hipGraph on a plan-owned stream; later calls replay it on `stream`.  Input
- * contents may change between replays.  The final kernel also clears the
+ * contents may change between replays.  Its final kernel also clears the
  * plan's work counters for the next call: if a call returns an error after
  * it has enqueued work, destroy the plan rather than call it again. */
 int psdf_batch(psdf_batch_plan* plan, const float* poses, const float* ax, const float* ay,
@@ -360,7 +367,8 @@ int psdf_batch(psdf_batch_plan* plan, const float* poses, const float* ax, const
  * obstacles per tile 64 or 256 x persistent grid or one work-group per
  * item) on `stream` as a burst of back-to-back calls, in two rounds over
  * all candidates after ten warm-up calls (the better burst counts),
- * synchronising it, keeps the fastest in the plan and in a
+ * synchronising it (and, where psdf_batch would be culled, that form),
+ * keeps the fastest in the plan and in a
  * process-wide cache keyed by the batch's size signature (later plans of the
  * same signature start from it; with PSDF_TUNE_CACHE set to a file path the
  * cache is also read from and appended to that file).  Outputs are left
@@ -370,8 +378,9 @@ int psdf_batch_autotune(psdf_batch_plan* plan, const float* poses, const float* 
                         const int32_t* obst_off, float* d, int32_t* edge, int32_t* obst,
                         float* grad, uint64_t* keys, hipStream_t stream, float* best_ms);
 
-/* Set the plan's launch shape explicitly (for sweeps and for reproducing a
- * tuned shape): stages_per_item 1..64 (each instance's horizon is cut into
+/* Set the launch shape of the plan's full evaluation explicitly (for sweeps
+ * and for reproducing a tuned shape), which psdf_batch then takes:
+ * stages_per_item 1..64 (each instance's horizon is cut into
  * ceil(N / stages_per_item) blocks of equal length), obstacles_per_tile 64
  * or 256, direct 0 (persistent grid) or 1 (one work-group per item).  A
  * captured graph is dropped and captured again on the next call.  Results
@@ -506,7 +515,8 @@ int psdf_set_launch_shape(int32_t blk, int32_t sb);
  * pair of HIP events recorded on its launch stream, for up to `capacity`
  * launches: the per-stage minimum kernel of psdf_eval / psdf_grad and the
  * persistent batch kernel of each footprint-size group of an eager
- * psdf_batch call (events recorded by the dispatch itself), the graph
+ * psdf_batch call (events recorded by the dispatch itself; the launches of a
+ * culled call between one pair), the graph
  * replay of a graph psdf_batch call, the screening kernels of
  * psdf_batch_screened / psdf_batch_screened_bound.
  * psdf_timer_read waits for those events, returns their summed duration in

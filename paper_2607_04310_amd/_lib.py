@@ -52,6 +52,7 @@ class PsdfBatchDesc(ctypes.Structure):
 
 PSDF_BATCH_GRAPH = 1
 PSDF_BATCH_AUTOTUNE = 2
+PSDF_BATCH_EXHAUSTIVE = 4
 
 
 class PsdfError(RuntimeError):

@@ -310,10 +310,12 @@ class Batch:
     """Uneven batch of independent instances evaluated by one persistent
     launch (psdf_batch).  ``instances`` is a sequence of objects with
     ``footprint`` (m, 2), ``poses`` (N, 3), ``edges`` (E, 4) and ``obst_off``
-    (M + 1,); they are packed host-side once and uploaded."""
+    (M + 1,); they are packed host-side once and uploaded.  ``exhaustive``
+    evaluates every (stage, obstacle) pair where psdf_batch would cull (same
+    outputs)."""
 
     def __init__(self, instances, mbar=None, params: Params | None = None, graph=True,
-                 autotune=False, device="cuda"):
+                 autotune=False, device="cuda", exhaustive=False):
         self.params = params or Params()
         fps, poses, edges, offs, desc = [], [], [], [], []
         nfp = npose = nedge = noff = 0
@@ -346,6 +348,7 @@ class Batch:
         self.keys = torch.empty(S, dtype=torch.int64, device=dev)
         arr = (_lib.PsdfBatchDesc * max(1, self.n_inst))(*[_lib.PsdfBatchDesc(*d) for d in desc])
         flags = (_lib.PSDF_BATCH_GRAPH if graph else 0) | (_lib.PSDF_BATCH_AUTOTUNE if autotune else 0)
+        flags |= _lib.PSDF_BATCH_EXHAUSTIVE if exhaustive else 0
         plan = ctypes.c_void_p(0)
         pc = self.params.c()
         _lib.check(_lib.lib().psdf_batch_plan_create(

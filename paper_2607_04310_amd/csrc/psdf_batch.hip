@@ -13,6 +13,7 @@
 
 #include "psdf.h"
 #include "psdf_batch.hpp"
+#include "psdf_cull.hpp"
 #include "psdf_host.hpp"
 #include "psdf_screen.hpp"
 #include "psdf_horizon.hpp"
@@ -23,6 +24,10 @@ struct Shape {
   int sb;       // stages per work item
   int nw;       // waves per work-group (obstacles per tile = 64 nw)
   int direct;   // 1: one work-group per item instead of a persistent grid
+  // what the autotuner chose: -1 not tuned (the size rule decides), 0 this
+  // shape, 1 the culled evaluation; in the cache file 2 * (cull + 1) is added
+  // to direct, so that a line without it leaves the choice to the size rule
+  int cull = -1;
 };
 
 }  // namespace psdf
@@ -76,6 +81,18 @@ struct psdf_batch_plan {
   unsigned char* d_rows = nullptr;   // staged obstacle rows (psdf_staged.hpp)
   bool circ_staged = false;
   const void* circ_src[5] = {};
+  // culled evaluation (psdf_cull.hpp): whether psdf_batch takes it, its
+  // segments and stage records, and its lists (rewritten by every call)
+  bool cull_ready = false;   // the tables below exist
+  bool culled = false;
+  int n_segs = 0;
+  CullSeg* d_segs = nullptr;
+  CullStage* d_cstages = nullptr;
+  float4* d_cbox = nullptr;
+  int4* d_cmeta = nullptr;
+  int* d_ccnt = nullptr;
+  struct CGroup { int mf, start, count; };
+  std::vector<CGroup> cgroups;
   // graph
   hipStream_t cap_stream = nullptr;
   // footprint-size groups run concurrently on up to kLanes streams: the
@@ -117,8 +134,8 @@ void cache_load_locked() {
   char key[128];
   int sb, nw, direct;
   while (std::fscanf(f, "%127s %d %d %d", key, &sb, &nw, &direct) == 4)
-    if (sb >= 1 && sb <= kMaxStageBlock && (nw == 1 || nw == 4) && (direct == 0 || direct == 1))
-      g_cache[key] = Shape{sb, nw, direct};
+    if (sb >= 1 && sb <= kMaxStageBlock && (nw == 1 || nw == 4) && direct >= 0 && direct <= 5)
+      g_cache[key] = Shape{sb, nw, direct & 1, direct / 2 - 1};
   std::fclose(f);
 }
 
@@ -128,7 +145,7 @@ void cache_store(const std::string& key, Shape s) {
   g_cache[key] = s;
   if (const char* path = std::getenv("PSDF_TUNE_CACHE")) {
     if (FILE* f = std::fopen(path, "a")) {
-      std::fprintf(f, "%s %d %d %d\n", key.c_str(), s.sb, s.nw, s.direct);
+      std::fprintf(f, "%s %d %d %d\n", key.c_str(), s.sb, s.nw, s.direct + 2 * (s.cull + 1));
       std::fclose(f);
     }
   }
@@ -390,6 +407,112 @@ __global__ __launch_bounds__(64) void batch_finish_kernel(
   }
 }
 
+// When the culled evaluation is the faster one: it spends a fixed part per
+// stage (a seed, a few candidates and their reductions, about the issue time
+// of two 64-obstacle tiles of the full evaluation) and two launches, and
+// reads every edge once, where the full evaluation spends its time per
+// (stage, obstacle) pair.
+constexpr double kCullPairs = 4e6;
+constexpr double kCullObstacles = 512;   // per stage, mean
+
+bool cull_pays(const psdf_batch_plan& p) {
+  double pairs = 0.0;
+  for (const auto& d : p.desc) pairs += (double)d.N * d.M;
+  return pairs >= kCullPairs && pairs >= kCullObstacles * p.total_stages;
+}
+
+// Segments, stage records and lists of the culled evaluation.
+hipError_t cull_create(psdf_batch_plan* p) {
+  std::vector<CullSeg> segs;
+  std::vector<CullStage> stages;
+  // the stages of one instance read the same list: deal the instances (most
+  // obstacles first) to the chip's XCDs, whose L2 caches are separate, and
+  // interleave the stages as consecutive work-groups are dealt to them
+  constexpr int kXcd = 8;
+  std::vector<int> seg0(p->n_inst), slot0(p->n_inst), order(p->n_inst);
+  long slot = 0;
+  for (int k = 0; k < p->n_inst; ++k) {
+    order[k] = k;
+    seg0[k] = (int)segs.size();
+    slot0[k] = (int)slot;
+    for (int o0 = 0; o0 < p->desc[k].M; o0 += kSegObst)
+      segs.push_back(CullSeg{k, o0, std::min(kSegObst, p->desc[k].M - o0), (int)(slot + o0)});
+    slot += p->desc[k].M;
+  }
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int a, int b) { return p->desc[a].M > p->desc[b].M; });
+  // one launch per footprint class: up to eight vertices (evaluated with as
+  // many slots as the largest has: further slots repeat the last one and
+  // change no result), and more
+  for (int wide = 0; wide < 2; ++wide) {
+    std::vector<std::vector<CullStage>> q(kXcd);
+    int mf = 0;
+    for (int k : order) {
+      const psdf_batch_desc& d = p->desc[k];
+      if ((p->fp[k].m > 8 ? 1 : 0) != wide) continue;
+      mf = std::max(mf, kGroupMF[group_of(p->fp[k].m)]);
+      auto& to = *std::min_element(q.begin(), q.end(), [](const std::vector<CullStage>& a,
+                                                          const std::vector<CullStage>& b) {
+        return a.size() < b.size();
+      });
+      for (int t = 0; t < d.N; ++t)
+        to.push_back(CullStage{d.pose_off + t, k, slot0[k], seg0[k],
+                               (d.M + kSegObst - 1) / kSegObst, d.M, d.obst_off, d.edge_off});
+    }
+    size_t longest = 0;
+    for (const auto& v : q) longest = std::max(longest, v.size());
+    const int start = (int)stages.size();
+    for (size_t i = 0; i < longest; ++i)
+      for (const auto& v : q)
+        if (i < v.size()) stages.push_back(v[i]);
+    if ((int)stages.size() > start)
+      p->cgroups.push_back({mf, start, (int)stages.size() - start});
+  }
+  p->n_segs = (int)segs.size();
+  const size_t slots = (size_t)slot + kCullPad;
+  hipError_t err = hipMalloc(&p->d_segs, std::max<size_t>(1, segs.size()) * sizeof(CullSeg));
+  if (err == hipSuccess) err = hipMalloc(&p->d_cstages, std::max<size_t>(1, stages.size()) * sizeof(CullStage));
+  if (err == hipSuccess) err = hipMalloc(&p->d_cbox, slots * sizeof(float4));
+  if (err == hipSuccess) err = hipMalloc(&p->d_cmeta, slots * sizeof(int4));
+  if (err == hipSuccess) err = hipMalloc(&p->d_ccnt, std::max<size_t>(1, segs.size()) * sizeof(int));
+  if (err == hipSuccess && !segs.empty())
+    err = hipMemcpy(p->d_segs, segs.data(), segs.size() * sizeof(CullSeg), hipMemcpyHostToDevice);
+  if (err == hipSuccess && !stages.empty())
+    err = hipMemcpy(p->d_cstages, stages.data(), stages.size() * sizeof(CullStage),
+                    hipMemcpyHostToDevice);
+  p->cull_ready = err == hipSuccess;
+  return err;
+}
+
+hipError_t launch_cull(int mf, int mi_class, int n, const CullArgs& a, hipStream_t st) {
+  switch (mf) {
+    case 3: return launch_cull_mf<3>(mi_class, n, a, st);
+    case 4: return launch_cull_mf<4>(mi_class, n, a, st);
+    case 5: return launch_cull_mf<5>(mi_class, n, a, st);
+    case 6: return launch_cull_mf<6>(mi_class, n, a, st);
+    case 7: return launch_cull_mf<7>(mi_class, n, a, st);
+    case 8: return launch_cull_mf<8>(mi_class, n, a, st);
+    default: return launch_cull_mf<16>(mi_class, n, a, st);
+  }
+}
+
+hipError_t cull_enqueue(psdf_batch_plan* p, const BatchArgs& b, hipStream_t st) {
+  CullArgs a{p->d_fp, p->d_inst, p->d_segs, p->d_cstages, b.poses, b.ax,   b.ay,   b.bx, b.by,
+             b.off,   p->d_cbox, p->d_cmeta, p->d_ccnt,   b.d,     b.edge, b.obst, b.grad, b.keys};
+  if (p->n_segs > 0) {
+    if (p->mi_class == 4) cull_list_kernel<4><<<p->n_segs, kCullThreads, 0, st>>>(a);
+    else if (p->mi_class == 8) cull_list_kernel<8><<<p->n_segs, kCullThreads, 0, st>>>(a);
+    else cull_list_kernel<16><<<p->n_segs, kCullThreads, 0, st>>>(a);
+  }
+  hipError_t err = hipGetLastError();
+  for (const auto& g : p->cgroups) {
+    if (err != hipSuccess) break;
+    a.stages = p->d_cstages + g.start;
+    err = launch_cull(g.mf, p->mi_class, g.count, a, st);
+  }
+  return err;
+}
+
 int run(psdf_batch_plan* p, const float* poses, const float* ax, const float* ay,
         const float* bx, const float* by, const int32_t* off, float* d, int32_t* edge,
         int32_t* obst, float* grad, uint64_t* keys, hipStream_t stream, bool use_graph) {
@@ -398,6 +521,12 @@ int run(psdf_batch_plan* p, const float* poses, const float* ax, const float* ay
   // timed: events recorded by each batch-kernel dispatch itself (eager
   // calls only; a captured graph is timed as a whole)
   auto enqueue = [&](hipStream_t st, bool timed) -> hipError_t {
+    if (p->culled) {
+      if (timed) timer_begin(st);
+      const hipError_t e = cull_enqueue(p, a, st);
+      if (timed) timer_end(st);
+      return e;
+    }
     // the groups write disjoint partial rows and count their items on
     // counters of their own, so they run concurrently (their tails overlap)
     const int ng = (int)p->groups.size(), nl = p->n_lanes;
@@ -699,6 +828,11 @@ void psdf_batch_plan_destroy(psdf_batch_plan* p) {
   (void)hipFree(p->d_frag);
   (void)hipFree(p->d_hcount);
   (void)hipFree(p->d_hrest);
+  (void)hipFree(p->d_segs);
+  (void)hipFree(p->d_cstages);
+  (void)hipFree(p->d_cbox);
+  (void)hipFree(p->d_cmeta);
+  (void)hipFree(p->d_ccnt);
   (void)hipSetDevice(cur);
   delete p;
 }
@@ -867,6 +1001,12 @@ int psdf_batch_plan_create(psdf_batch_plan** out, const psdf_batch_desc* desc, i
   }
   int rc = build_items(p, sh);
   if (rc) { psdf_batch_plan_destroy(p); return rc; }
+  if (!(flags & PSDF_BATCH_EXHAUSTIVE) && p->sum_M + kCullPad < 0x7fffffffu &&
+      (sh.cull == 1 || cull_pays(*p))) {
+    rc = hip_status(cull_create(p));
+    if (rc) { psdf_batch_plan_destroy(p); return rc; }
+    p->culled = sh.cull != 0;
+  }
   *out = p;
   return PSDF_OK;
 }
@@ -912,33 +1052,48 @@ int psdf_batch_autotune(psdf_batch_plan* p, const float* poses, const float* ax,
   float t_best[kCand];
   for (float& t : t_best) t = INFINITY;
   int rc = PSDF_OK;
+  const bool was_culled = p->culled;
+  p->culled = false;
   for (int w = 0; w < 10 && rc == PSDF_OK; ++w)
     rc = run(p, poses, ax, ay, bx, by, off, d, edge, obst, grad, keys, stream, false);
-  for (int round = 0; round < kRounds && rc == PSDF_OK; ++round)
+  // one burst of the plan's current form, after one untimed call
+  auto burst = [&](float& best) {
+    rc = run(p, poses, ax, ay, bx, by, off, d, edge, obst, grad, keys, stream, false);
+    if (rc) return;
+    err = hipEventRecord(e0, stream);
+    for (int k = 0; k < kBurst && err == hipSuccess && rc == PSDF_OK; ++k)
+      rc = run(p, poses, ax, ay, bx, by, off, d, edge, obst, grad, keys, stream, false);
+    if (rc) return;
+    if (err == hipSuccess) err = hipEventRecord(e1, stream);
+    if (err == hipSuccess) err = hipEventSynchronize(e1);
+    float ms = 0.f;
+    if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
+    if (err != hipSuccess) { rc = hip_status(err); return; }
+    best = std::min(best, ms / kBurst);
+  };
+  float t_cull = INFINITY;
+  for (int round = 0; round < kRounds && rc == PSDF_OK; ++round) {
     for (int cand = 0; cand < kCand && rc == PSDF_OK; ++cand) {
       rc = build_items(p, shape_of(cand));
-      if (rc) break;
-      rc = run(p, poses, ax, ay, bx, by, off, d, edge, obst, grad, keys, stream, false);
-      if (rc) break;
-      err = hipEventRecord(e0, stream);
-      for (int k = 0; k < kBurst && err == hipSuccess && rc == PSDF_OK; ++k)
-        rc = run(p, poses, ax, ay, bx, by, off, d, edge, obst, grad, keys, stream, false);
-      if (rc) break;
-      if (err == hipSuccess) err = hipEventRecord(e1, stream);
-      if (err == hipSuccess) err = hipEventSynchronize(e1);
-      float ms = 0.f;
-      if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
-      if (err != hipSuccess) { rc = hip_status(err); break; }
-      t_best[cand] = std::min(t_best[cand], ms / kBurst);
+      if (!rc) burst(t_best[cand]);
     }
+    if (p->cull_ready && rc == PSDF_OK) {
+      p->culled = true;
+      burst(t_cull);
+      p->culled = false;
+    }
+  }
   float best = INFINITY;
   Shape best_sh = p->shape;
   for (int cand = 0; cand < kCand; ++cand)
     if (t_best[cand] < best) { best = t_best[cand]; best_sh = shape_of(cand); }
+  best_sh.cull = p->cull_ready ? (t_cull < best ? 1 : 0) : -1;
+  p->culled = rc ? was_culled : best_sh.cull == 1;
+  best = std::min(best, t_cull);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc) return rc;
-  rc = build_items(p, best_sh);
+  rc = build_items(p, best_sh);   // drops the captured graph
   if (rc) return rc;
   cache_store(signature(*p), best_sh);
   rc = run(p, poses, ax, ay, bx, by, off, d, edge, obst, grad, keys, stream, false);
@@ -954,6 +1109,7 @@ int psdf_batch_set_shape(psdf_batch_plan* p, int32_t stages_per_item, int32_t ob
       (obstacles_per_tile != 64 && obstacles_per_tile != 256) || (direct != 0 && direct != 1))
     return set_error(PSDF_EINVAL, "shape sb=%d tile=%d direct=%d (sb 1..%d, tile 64 or 256, direct 0 or 1)",
                      stages_per_item, obstacles_per_tile, direct, kMaxStageBlock);
+  p->culled = false;   // the shape is the full evaluation's
   return build_items(p, Shape{stages_per_item, obstacles_per_tile / 64, direct});
 }
 

@@ -66,6 +66,11 @@ struct FpConst {
   // the rounding (eps_sat / kappa + margin, kappa = cos of half the largest
   // exterior angle of the footprint).
   float rmax, tau_sep;
+  // Culling constants (psdf_cull.hpp): the smallest |v_l|; the distance above
+  // which the axis test separates, with the rounding of its projections
+  // divided by kappa; that or the largest sd of sets that are not separated;
+  // the relative rounding allowance of a bound.
+  float rmin, cull_tau, sd_floor, cull_rel;
 };
 
 // One obstacle in registers, with its pose-independent constants.  Slots

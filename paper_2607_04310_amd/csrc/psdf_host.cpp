@@ -121,9 +121,11 @@ int prepare_footprint(const float* xy, int m, const psdf_params* params, FpConst
     f.ob[l] = (float)(hi - (vx[l] * nx + vy[l] * ny));
   }
   // certificate constants (see FpConst)
-  double rmax = 0.0, max_ext = 0.0;
+  double rmax = 0.0, rmin = INFINITY, max_ext = 0.0;
   for (int l = 0; l < m; ++l) {
-    rmax = std::fmax(rmax, std::sqrt(vx[l] * vx[l] + vy[l] * vy[l]));
+    const double r = std::sqrt(vx[l] * vx[l] + vy[l] * vy[l]);
+    rmax = std::fmax(rmax, r);
+    rmin = std::fmin(rmin, r);
     const int a = l, b = (l + 1) % m, c = (l + 2) % m;
     const double e1x = vx[b] - vx[a], e1y = vy[b] - vy[a], e2x = vx[c] - vx[b], e2y = vy[c] - vy[b];
     const double ext = std::atan2(e1x * e2y - e1y * e2x, e1x * e2x + e1y * e2y);  // exterior angle
@@ -132,6 +134,13 @@ int prepare_footprint(const float* xy, int m, const psdf_params* params, FpConst
   const double kappa = std::cos(0.5 * max_ext);
   f.rmax = (float)(rmax * (1.0 + 1e-6) + 1e-6);
   f.tau_sep = kappa > 1e-3 ? (float)((double)p.eps_sat / kappa + 1e-3) : INFINITY;
+  f.rmin = (float)(rmin * (1.0 + 1e-6) + 1e-6);
+  f.cull_tau = kappa > 1e-3
+                   ? (float)(((double)p.eps_sat + 4e-6 * (rmax + 1.0)) / kappa + 1e-3)
+                   : INFINITY;
+  f.cull_rel = kappa > 1e-3 ? (float)(1e-5 + 2e-6 / kappa) : 1.0f;
+  f.sd_floor = f.hard ? f.cull_tau
+                      : std::fmax(f.cull_tau, (float)(1.001 * std::log((double)(m + kMaxObst)) / p.eta));
   for (int l = m; l < kMaxFp; ++l) {  // padded slots repeat slot m - 1
     f.vx[l] = f.vx[m - 1]; f.vy[l] = f.vy[m - 1];
     f.ex[l] = f.ex[m - 1]; f.ey[l] = f.ey[m - 1];

@@ -1,0 +1,156 @@
+"""The culled evaluation of a batch gives the full evaluation's outputs bit
+for bit: instances at the edges of the segments and list rounds, obstacles
+that no bound covers (open chains, stars, degenerate edges, non-finite and
+huge coordinates, invalid ranges), footprints and constants at the ends of
+their ranges, non-finite poses, graph replays with changed inputs."""
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+
+from paper_2607_04310_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _closed(P):
+    """Edges of a polygon with corners P (k, 2)."""
+    return np.concatenate([P, np.roll(P, -1, axis=0)], 1).astype(np.float32)
+
+
+def _inst(rng, fp, N, M, half, spread=None, mbar=4, odd=()):
+    """M obstacles in [-half, half]^2: rectangles, free segments and, for
+    larger bounds, polygons of up to mbar edges; `odd` obstacles are mixed in."""
+    rows = []
+    k = rng.integers(0, 3, M)
+    rect = inputs.random_rects(rng, M, 0.1, 0.8, -half, half).reshape(M, 4, 4)
+    seg = inputs.segment_edges(rng.uniform(-half, half, (M, 2)), rng.uniform(0.1, 2.0, M),
+                               rng.uniform(-np.pi, np.pi, M))
+    for i in range(M):
+        if k[i] == 2 and mbar > 4:
+            n = int(rng.integers(3, mbar + 1))
+            a = np.sort(rng.uniform(0, 2 * np.pi, n))
+            rows.append(_closed(rng.uniform(-half, half, 2) + 0.4 * np.stack([np.cos(a), np.sin(a)], 1)))
+        else:
+            rows.append(rect[i] if k[i] else seg[i:i + 1])
+    for e in odd:
+        rows.insert(int(rng.integers(0, len(rows) + 1)), np.asarray(e, np.float32).reshape(-1, 4))
+    sizes = [len(r) for r in rows]
+    edges = np.concatenate(rows) if rows else np.zeros((0, 4), np.float32)
+    if spread is None:
+        poses = inputs.path_poses(rng, N, -half / 2, half / 2)
+    else:
+        poses = inputs.uniform_poses(rng, N, -spread, spread)
+    return SimpleNamespace(footprint=fp, poses=poses, edges=edges.astype(np.float32),
+                           obst_off=inputs.csr_offsets(sizes))
+
+
+def _big(rng, fp, half=20.0):
+    """Enough pairs for the culled form: 300 stages x 16384 rectangles."""
+    return SimpleNamespace(footprint=fp, poses=inputs.path_poses(rng, 300, -half, half),
+                           edges=inputs.random_rects(rng, 16384, 0.1, 0.8, -half, half),
+                           obst_off=inputs.csr_offsets([4] * 16384))
+
+
+def _check(insts, mbar=None, params=None, change=None):
+    import torch
+    from paper_2607_04310_amd import api
+    a = api.Batch(insts, mbar=mbar, params=params)
+    b = api.Batch(insts, mbar=mbar, params=params, graph=False, exhaustive=True)
+    for round_ in range(3):
+        if change is not None and round_:
+            for x in (a, b):
+                change(x, round_)
+        got = [t.clone() for t in a.run()]
+        want = [t.clone() for t in b.run()]
+        torch.cuda.synchronize()
+        for name, g, w in zip(("d", "edge", "obst", "grad", "keys"), got, want):
+            g, w = g.cpu().numpy(), w.cpu().numpy()
+            bad = np.flatnonzero((g.view(np.uint8) != w.view(np.uint8)).reshape(len(g), -1).any(1))
+            assert len(bad) == 0, (round_, name, bad[:5], g[bad[:5]], w[bad[:5]])
+    a.close()
+    b.close()
+    return want
+
+
+def test_sizes_at_the_edges():
+    rng = np.random.default_rng(11)
+    fps = [inputs.random_convex_footprint(rng, m) for m in (3, 4, 5, 7, 8)] + [inputs.rect_footprint()]
+    insts = [_big(rng, inputs.hexagon_footprint(rng))]
+    for k, (M, N) in enumerate([(0, 3), (1, 1), (63, 2), (64, 7), (65, 1), (1023, 5), (1024, 5),
+                                (1025, 5), (3000, 64), (5000, 65), (20000, 9)]):
+        insts.append(_inst(rng, fps[k % len(fps)], N, M, max(2.0, 0.5 * np.sqrt(M))))
+    # poses all over the map: every obstacle is listed, more than the rounds in registers
+    insts.append(_inst(rng, fps[0], 40, 18000, 40.0, spread=40.0))
+    # a heap: every obstacle overlaps the robot
+    insts.append(_inst(rng, fps[5], 6, 2500, 0.3))
+    _check(insts)
+
+
+@pytest.mark.parametrize("mbar,m", [(8, 6), (16, 4), (4, 12), (16, 16)])
+def test_edge_classes_and_wide_footprints(mbar, m):
+    rng = np.random.default_rng(100 * mbar + m)
+    ang = 2 * np.pi * np.arange(m) / m
+    fp = np.stack([0.5 * np.cos(ang), 0.35 * np.sin(ang)], 1).astype(np.float32)
+    insts = [_big(rng, fp)] + [_inst(rng, fp, N, M, 0.5 * np.sqrt(M), mbar=mbar)
+                               for M, N in ((777, 33), (1500, 8))]
+    insts.append(_inst(rng, inputs.rect_footprint(), 5, 300, 8.0, mbar=mbar))
+    _check(insts, mbar=mbar)
+
+
+ODD = [
+    [[0, 0, 1, 0], [1, 0, 1, 1]],                               # open chain
+    [[-9, 0, 9, 0], [9, 0, 9, 0.5], [9, 0.5, -9, 0.5]],          # open chain, long
+    [[2, 2, 2, 2]],                                             # degenerate segment
+    [[1, 1, 2, 1], [2, 1, 2, 1], [2, 1, 1.5, 2], [1.5, 2, 1, 1]],   # a zero-length edge
+    _closed(np.array([[0, 0], [4, 0], [1, 0.5], [0, 4]])),       # not convex
+    _closed(np.array([[0, 0], [1, 1], [1, 0], [0, 1]]) + 3.0),   # crosses itself
+    _closed(np.array([[0, 0], [2, 0], [4, 0], [4, 3]])),         # a straight corner
+    _closed(np.array([[-8, -8], [-8, 8], [8, 8], [8, -8]])),     # clockwise, around everything
+    [[-30, -30.001, 30, 30]],                                   # a long diagonal wall
+    [[1e16, 0, 1e16, 1]], [[3e30, 1, 1, 1]], [[1e-30, 0, 2e-30, 0]],
+    [],                                                         # empty
+]
+
+
+@pytest.mark.parametrize("case", ["default", "hard", "soft", "eps", "eps_sat"])
+def test_obstacles_without_a_bound(case):
+    from paper_2607_04310_amd import api
+    rng = np.random.default_rng(5)
+    params = {"default": None, "hard": api.hard_min(), "soft": api.Params(eta=2.0),
+              "eps": api.Params(eps=1e-2), "eps_sat": api.Params(eps_sat=0.05)}[case]
+    sliver = np.array([[-0.5, 0.0], [0.5, -0.004], [0.5, 0.004]], np.float32)
+    away = inputs.rect_footprint() + np.array([3.0, -2.0], np.float32)   # origin far outside
+    insts = [_big(rng, inputs.hexagon_footprint(rng))]
+    for k, fp in enumerate((inputs.rect_footprint(), sliver, away, sliver[::-1].copy())):
+        insts.append(_inst(rng, fp, 20, 1500, 15.0, odd=ODD[k::2] if k < 2 else ODD))
+        insts.append(_inst(rng, fp, 9, 40, 3.0, odd=ODD[:4] if k else ()))
+    _check(insts, params=params)
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_non_finite_inputs_and_ranges(bad):
+    rng = np.random.default_rng(8)
+    fp = inputs.hexagon_footprint(rng)
+    insts = [_big(rng, fp)] + [_inst(rng, fp, 12, 1400, 18.0, odd=[[]]) for _ in range(6)]
+    insts[1].edges[37, 1] = bad                       # one obstacle
+    insts[2].poses[3, 0] = bad                        # one stage: position
+    insts[2].poses[5, 2] = bad                        # and heading
+    insts[3].poses[:] = bad                           # every stage
+    insts[4].poses[2, 1] = 3e15                       # beyond the bound's range
+    insts[5].obst_off[200:] += 3                      # a range past the edges at the end
+    insts[6].obst_off[100] = insts[6].obst_off[99] - 2    # a negative count, then too many edges
+    _check(insts)
+
+
+def test_replays_see_changed_inputs():
+    import torch
+    rng = np.random.default_rng(21)
+    fp = inputs.hexagon_footprint(rng)
+    insts = [_big(rng, fp), _inst(rng, inputs.rect_footprint(), 30, 2000, 20.0)]
+
+    def change(b, k):
+        b.poses[:, 0] += 0.37 * k
+        b.poses[:, 2] -= 0.2
+        b.ax[::2] = torch.roll(b.ax, 8)[::2]          # breaks closed boundaries, moves corners
+    _check(insts, change=change)
