@@ -346,7 +346,7 @@ void psdf_batch_plan_destroy(psdf_batch_plan* plan);
  * A batch of enough (stage, obstacle) pairs, with enough obstacles per stage,
  * is evaluated culled: a bound on every pair (from the obstacle's bounding
  * box) leaves a few obstacles per stage, which alone are evaluated, in two
- * or three launches on `stream`; the outputs are those of the full
+ * launches on `stream`; the outputs are those of the full
  * evaluation bit for bit, for every input.  With PSDF_BATCH_EXHAUSTIVE, or
  * after psdf_batch_set_shape, every pair is evaluated.  In the full
  * evaluation the launches of the different footprint sizes run concurrently: they fork

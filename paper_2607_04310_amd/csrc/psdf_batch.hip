@@ -86,13 +86,11 @@ struct psdf_batch_plan {
   bool cull_ready = false;   // the tables below exist
   bool culled = false;
   int n_segs = 0;
+  FpRow* d_frows = nullptr;
   CullSeg* d_segs = nullptr;
   CullStage* d_cstages = nullptr;
-  float4* d_cbox = nullptr;
-  int4* d_cmeta = nullptr;
+  CullRec* d_crec = nullptr;
   int* d_ccnt = nullptr;
-  struct CGroup { int mf, start, count; };
-  std::vector<CGroup> cgroups;
   // graph
   hipStream_t cap_stream = nullptr;
   // footprint-size groups run concurrently on up to kLanes streams: the
@@ -395,7 +393,8 @@ __global__ __launch_bounds__(64) void batch_finish_kernel(
     sincosf(th, &sn, &cs);
     wave_sync();
     // last round: the winner's edges
-    write_stage(F, fl, wl, ax, ay, bx, by, key, valid, e0, mi, R.edge_off, cs, sn, px, py, g, keys,
+    write_stage(F, fl, wl, EdgeArrays{ax, ay, bx, by, e0}, key, valid, e0, mi, R.edge_off, cs, sn,
+                px, py, g, keys,
                 d, edge, obst, grad);
   }
   if (blockIdx.x == 0) {
@@ -441,39 +440,31 @@ hipError_t cull_create(psdf_batch_plan* p) {
   }
   std::stable_sort(order.begin(), order.end(),
                    [&](int a, int b) { return p->desc[a].M > p->desc[b].M; });
-  // one launch per footprint class: up to eight vertices (evaluated with as
-  // many slots as the largest has: further slots repeat the last one and
-  // change no result), and more
-  for (int wide = 0; wide < 2; ++wide) {
-    std::vector<std::vector<CullStage>> q(kXcd);
-    int mf = 0;
-    for (int k : order) {
-      const psdf_batch_desc& d = p->desc[k];
-      if ((p->fp[k].m > 8 ? 1 : 0) != wide) continue;
-      mf = std::max(mf, kGroupMF[group_of(p->fp[k].m)]);
-      auto& to = *std::min_element(q.begin(), q.end(), [](const std::vector<CullStage>& a,
-                                                          const std::vector<CullStage>& b) {
-        return a.size() < b.size();
-      });
-      for (int t = 0; t < d.N; ++t)
-        to.push_back(CullStage{d.pose_off + t, k, slot0[k], seg0[k],
-                               (d.M + kSegObst - 1) / kSegObst, d.M, d.obst_off, d.edge_off});
-    }
-    size_t longest = 0;
-    for (const auto& v : q) longest = std::max(longest, v.size());
-    const int start = (int)stages.size();
-    for (size_t i = 0; i < longest; ++i)
-      for (const auto& v : q)
-        if (i < v.size()) stages.push_back(v[i]);
-    if ((int)stages.size() > start)
-      p->cgroups.push_back({mf, start, (int)stages.size() - start});
+  std::vector<std::vector<CullStage>> q(kXcd);
+  for (int k : order) {
+    const psdf_batch_desc& d = p->desc[k];
+    auto& to = *std::min_element(q.begin(), q.end(), [](const std::vector<CullStage>& a,
+                                                        const std::vector<CullStage>& b) {
+      return a.size() < b.size();
+    });
+    for (int t = 0; t < d.N; ++t)
+      to.push_back(CullStage{d.pose_off + t, k, slot0[k], seg0[k],
+                             (d.M + kSegObst - 1) / kSegObst, d.M, d.obst_off, d.edge_off});
   }
+  for (size_t i = 0; (int)stages.size() < p->total_stages; ++i)
+    for (const auto& v : q)
+      if (i < v.size()) stages.push_back(v[i]);
   p->n_segs = (int)segs.size();
   const size_t slots = (size_t)slot + kCullPad;
-  hipError_t err = hipMalloc(&p->d_segs, std::max<size_t>(1, segs.size()) * sizeof(CullSeg));
+  std::vector<FpRow> rows;
+  for (const FpConst& f : p->fp)
+    for (int l = 0; l < kMaxFp; ++l) rows.push_back(fp_row(f, l));
+  hipError_t err = hipMalloc(&p->d_frows, std::max<size_t>(1, rows.size()) * sizeof(FpRow));
+  if (err == hipSuccess && !rows.empty())
+    err = hipMemcpy(p->d_frows, rows.data(), rows.size() * sizeof(FpRow), hipMemcpyHostToDevice);
+  if (err == hipSuccess) err = hipMalloc(&p->d_segs, std::max<size_t>(1, segs.size()) * sizeof(CullSeg));
   if (err == hipSuccess) err = hipMalloc(&p->d_cstages, std::max<size_t>(1, stages.size()) * sizeof(CullStage));
-  if (err == hipSuccess) err = hipMalloc(&p->d_cbox, slots * sizeof(float4));
-  if (err == hipSuccess) err = hipMalloc(&p->d_cmeta, slots * sizeof(int4));
+  if (err == hipSuccess) err = hipMalloc(&p->d_crec, slots * sizeof(CullRec));
   if (err == hipSuccess) err = hipMalloc(&p->d_ccnt, std::max<size_t>(1, segs.size()) * sizeof(int));
   if (err == hipSuccess && !segs.empty())
     err = hipMemcpy(p->d_segs, segs.data(), segs.size() * sizeof(CullSeg), hipMemcpyHostToDevice);
@@ -484,33 +475,19 @@ hipError_t cull_create(psdf_batch_plan* p) {
   return err;
 }
 
-hipError_t launch_cull(int mf, int mi_class, int n, const CullArgs& a, hipStream_t st) {
-  switch (mf) {
-    case 3: return launch_cull_mf<3>(mi_class, n, a, st);
-    case 4: return launch_cull_mf<4>(mi_class, n, a, st);
-    case 5: return launch_cull_mf<5>(mi_class, n, a, st);
-    case 6: return launch_cull_mf<6>(mi_class, n, a, st);
-    case 7: return launch_cull_mf<7>(mi_class, n, a, st);
-    case 8: return launch_cull_mf<8>(mi_class, n, a, st);
-    default: return launch_cull_mf<16>(mi_class, n, a, st);
-  }
-}
-
 hipError_t cull_enqueue(psdf_batch_plan* p, const BatchArgs& b, hipStream_t st) {
-  CullArgs a{p->d_fp, p->d_inst, p->d_segs, p->d_cstages, b.poses, b.ax,   b.ay,   b.bx, b.by,
-             b.off,   p->d_cbox, p->d_cmeta, p->d_ccnt,   b.d,     b.edge, b.obst, b.grad, b.keys};
+  CullArgs a{p->d_fp, p->d_frows, p->d_inst, p->d_segs, p->d_cstages, b.poses, b.ax,   b.ay,   b.bx, b.by,
+             b.off,   p->d_crec, p->d_ccnt,  b.d,     b.edge, b.obst, b.grad, b.keys};
   if (p->n_segs > 0) {
     if (p->mi_class == 4) cull_list_kernel<4><<<p->n_segs, kCullThreads, 0, st>>>(a);
     else if (p->mi_class == 8) cull_list_kernel<8><<<p->n_segs, kCullThreads, 0, st>>>(a);
     else cull_list_kernel<16><<<p->n_segs, kCullThreads, 0, st>>>(a);
   }
-  hipError_t err = hipGetLastError();
-  for (const auto& g : p->cgroups) {
-    if (err != hipSuccess) break;
-    a.stages = p->d_cstages + g.start;
-    err = launch_cull(g.mf, p->mi_class, g.count, a, st);
-  }
-  return err;
+  const int S = p->total_stages;
+  if (p->mi_class == 4) cull_stage_kernel<4><<<S, 64, 0, st>>>(a);
+  else if (p->mi_class == 8) cull_stage_kernel<8><<<S, 64, 0, st>>>(a);
+  else cull_stage_kernel<16><<<S, 64, 0, st>>>(a);
+  return hipGetLastError();
 }
 
 int run(psdf_batch_plan* p, const float* poses, const float* ax, const float* ay,
@@ -828,10 +805,10 @@ void psdf_batch_plan_destroy(psdf_batch_plan* p) {
   (void)hipFree(p->d_frag);
   (void)hipFree(p->d_hcount);
   (void)hipFree(p->d_hrest);
+  (void)hipFree(p->d_frows);
   (void)hipFree(p->d_segs);
   (void)hipFree(p->d_cstages);
-  (void)hipFree(p->d_cbox);
-  (void)hipFree(p->d_cmeta);
+  (void)hipFree(p->d_crec);
   (void)hipFree(p->d_ccnt);
   (void)hipSetDevice(cur);
   delete p;

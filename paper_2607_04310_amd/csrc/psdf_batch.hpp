@@ -93,18 +93,15 @@ __device__ __forceinline__ bool key_range(uint64_t key, const int* __restrict__ 
 }
 
 // Stage g's outputs from its final key (Sec. IV-D: the winner adjoint of
-// the winning obstacle, edges [e0, e0 + mi) global): an empty key gives the
+// the winning obstacle, edges [e0, e0 + mi) global, read through src): an empty key gives the
 // empty-set result (d = +inf, no winner, zero gradient); a key that names
 // no usable obstacle (valid false) gives NaN.  One whole wave with uniform
 // arguments; fl must hold F (stage_footprint) and be visible to the wave.
 // Every kernel that ends a stage goes through here, so a stage's outputs do
 // not depend on which kernel finished it.
+template <class Edge>
 __device__ __forceinline__ void write_stage(const FpConst& F, const FpLds& fl, WinnerLds& wl,
-                                            const float* __restrict__ ax,
-                                            const float* __restrict__ ay,
-                                            const float* __restrict__ bx,
-                                            const float* __restrict__ by, uint64_t key,
-                                            bool valid, int e0, int mi, int edge_off, float cs,
+                                            Edge src, uint64_t key, bool valid, int e0, int mi, int edge_off, float cs,
                                             float sn, float px, float py, int g,
                                             uint64_t* __restrict__ keys, float* __restrict__ d,
                                             int* __restrict__ edge, int* __restrict__ obst,
@@ -116,7 +113,7 @@ __device__ __forceinline__ void write_stage(const FpConst& F, const FpLds& fl, W
     gv[0] = gv[1] = gv[2] = dv;
   } else if (valid) {
     int jstar = 0;
-    winner_adjoint(F, fl, wl, ax, ay, bx, by, e0, mi, cs, sn, px, py, true, jstar, gv);
+    winner_adjoint(F, fl, wl, src, mi, cs, sn, px, py, true, jstar, gv);
     dv = from_orderable((uint32_t)(key >> 32));
     ov = (int)(key & 0xffffffffu);
     ev = e0 - edge_off + jstar;

@@ -26,16 +26,16 @@
 //    vertex of each, and an obstacle that is not separated has
 //    sd <= log(axes) / eta), so an obstacle whose bound from B exceeds H is
 //    beyond phi and tau at every stage.
-//  * cull_stage_kernel, one wave per stage: the listed obstacle with the
-//    smallest D (the seed) is evaluated exactly; its sd, or tau if that
-//    is larger, is a bar T >= phi, and every listed obstacle with LB <= T is
-//    evaluated exactly.  The minimum key over these is the stage's key: every
-//    other obstacle has sd >= LB > T >= phi.  The wave then ends the stage
+//  * cull_stage_kernel, one wave per stage: the listed obstacles nearest by
+//    D are evaluated exactly; their least sd, or tau if that is larger, is a
+//    bar T >= phi, and every listed obstacle with LB <= T is evaluated
+//    exactly.  The minimum key over these is the stage's key: every other
+//    obstacle has sd >= LB > T >= phi.  The wave then ends the stage
 //    (write_stage).
-// What it measured (graph replay per call, one card, full evaluation before):
-// 64 instances x 50 stages x 16384 rectangles 557 -> 47 us (list 17 us for
-// 67 MB of edges, stage 23 us), 512 uneven instances (23 800 stages, 2.7 M
-// edges) 581 -> 208 us (list 18, stage 177 us).
+// What it measured (graph replay per call, one card; full evaluation before):
+// 64 instances x 50 stages x 16384 rectangles 544 -> 43 us (list 17 us for
+// 67 MB of edges, stage 20 us), 512 uneven instances (23 800 stages, 2.7 M
+// edges) 581 -> 76 us (list 18, stage 58 us).
 // Lists have a fixed place per segment and are rewritten by every call:
 // no counter to reset, nothing kept between calls, no capacity to exceed.
 #pragma once
@@ -66,19 +66,44 @@ struct CullStage {
   int row, inst, slot0, seg0, nseg, M, obst_off, edge_off;
 };
 
+// A listed obstacle, one 64-byte record, so that the scan of the boxes brings
+// in what the evaluation reads next: the box (lo.x NaN: irregular), the
+// obstacle's index, first edge (global) and edge count, flags, and the points
+// of a closed polygon of at most four edges (A_j) or of one edge (A_0, B_0).
+constexpr int kRecClosed = 1, kRecBad = 2, kRecPoints = 4;
+struct CullRec {
+  float4 box;
+  int4 meta;
+  float4 pts[2];
+};
+static_assert(sizeof(CullRec) == 64, "one record, one line");
+
+// Slot l of an instance's footprint, 64 bytes, so that one wave reads a
+// footprint with four vector loads:
+//   v_l, u_l | e_l, 1 / (|e|^2 + eps), |e_l| | n_l, own interval | cu, cn, oa, ob
+struct FpRow {
+  float4 q[4];
+};
+inline FpRow fp_row(const FpConst& F, int l) {
+  return FpRow{{make_float4(F.vx[l], F.vy[l], F.ux[l], F.uy[l]),
+                make_float4(F.ex[l], F.ey[l], F.einv[l], F.len[l]),
+                make_float4(F.nx[l], F.ny[l], F.pa[l], F.pb[l]),
+                make_float4(F.cu[l], F.cn[l], F.oa[l], F.ob[l])}};
+}
+
 struct CullArgs {
   const FpConst* fps;
+  const FpRow* rows;         // kMaxFp per instance
   const BatchInst* insts;
   const CullSeg* segs;
-  const CullStage* stages;   // this launch's
+  const CullStage* stages;
   const float* poses;
   const float* ax;
   const float* ay;
   const float* bx;
   const float* by;
   const int* off;
-  float4* box;    // per list slot: lo.x (NaN: irregular), lo.y, hi.x, hi.y
-  int4* meta;     // per list slot: obstacle, first edge (global), edge count, closed | bad << 1
+  CullRec* rec;   // list slots
   int* cnt;       // per segment: list length
   float* d;
   int* edge;
@@ -127,11 +152,12 @@ __device__ __forceinline__ bool same_bits(float a, float b) {
   return __float_as_uint(a) == __float_as_uint(b);
 }
 
-// Box, flags (closed | bad << 1) and regularity of the obstacle with edges
-// [e0, e0 + mi), 1 <= mi <= MI and in range; the first edge (mi != 4) or all
-// four (mi == 4) are in v (ax, ay, bx, by).
+// Box, flags and regularity of the obstacle with edges [e0, e0 + mi),
+// 1 <= mi <= MI and in range; the first edge (mi != 4) or all four (mi == 4)
+// are in v (ax, ay, bx, by), and with kRecPoints in the flags its points are
+// afterwards (v[0], v[1]: A_j).
 template <int MI>
-__device__ __forceinline__ bool cull_obstacle(const float (&v)[4][4], const float* __restrict__ gax,
+__device__ __forceinline__ bool cull_obstacle(float (&v)[4][4], const float* __restrict__ gax,
                                               const float* __restrict__ gay,
                                               const float* __restrict__ gbx,
                                               const float* __restrict__ gby, int e0, int mi,
@@ -168,7 +194,9 @@ __device__ __forceinline__ bool cull_obstacle(const float (&v)[4][4], const floa
     cull_point(c, ax0, ay0);
     cull_point(c, bx, by);
     c.longe = fmaf(ex, ex, ey * ey) >= minl2;
-    for (int j = 1; j < mi; ++j) {
+#pragma unroll
+    for (int j = 1; j < (MI == 4 ? 4 : mi); ++j) {
+      if (MI == 4 && j >= mi) break;
       const float a0 = gax[e0 + j], a1 = gay[e0 + j], b0 = gbx[e0 + j], b1 = gby[e0 + j];
       c.closed = c.closed && same_bits(bx, a0) && same_bits(by, a1);
       cull_point(c, a0, a1);
@@ -177,12 +205,15 @@ __device__ __forceinline__ bool cull_obstacle(const float (&v)[4][4], const floa
       c.longe = c.longe && fmaf(fx, fx, fy * fy) >= minl2;
       cull_turn(c, ex, ey, fx, fy);
       ex = fx; ey = fy; bx = b0; by = b1;
+      if (MI == 4) { v[0][j & 3] = a0; v[1][j & 3] = a1; }
     }
+    if (mi == 1) { v[0][1] = bx; v[1][1] = by; }
     c.closed = c.closed && mi >= 3 && same_bits(bx, ax0) && same_bits(by, ay0);
     cull_turn(c, ex, ey, ex0, ey0);
   }
   const bool bad = c.bad != c.bad;
-  flags = (c.closed ? 1 : 0) | (bad ? 2 : 0);
+  flags = (c.closed ? kRecClosed : 0) | (bad ? kRecBad : 0) |
+          (MI == 4 && (c.closed || mi == 1) ? kRecPoints : 0);
   // a strictly convex polygon turns one way and its direction changes half
   // twice in one round (a star turns one way too, in more rounds)
   const bool convex = mi == 1 || (c.closed && (c.left || c.right) && c.flips <= 2);
@@ -281,7 +312,7 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
 #pragma unroll
   for (int q = 0; q < kCullPer; ++q) {
     box[q] = make_float4(__builtin_nanf(""), 0.f, 0.f, 0.f);
-    flags[q] = 2;
+    flags[q] = kRecBad;
     if (ok[q] && cull_obstacle<MI>(v[q], A.ax, A.ay, A.bx, A.by, e0[q], mi[q], minl2,
                                    F.cull_rel, box[q], flags[q])) {
       const float fx = fmaxf(fabsf(v[q][0][0] - plx), fabsf(v[q][0][0] - phx));
@@ -325,39 +356,71 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
 #pragma unroll
   for (int q = 0; q < kCullPer; ++q)
     if (take[q]) {
-      A.box[base + at[q]] = box[q];
-      A.meta[base + at[q]] = make_int4(S.o0 + tid + kCullThreads * q, e0[q], mi[q], flags[q]);
+      CullRec* r = A.rec + base + at[q];
+      r->box = box[q];
+      r->meta = make_int4(S.o0 + tid + kCullThreads * q, e0[q], mi[q], flags[q]);
+      r->pts[0] = make_float4(v[q][0][0], v[q][1][0], v[q][0][1], v[q][1][1]);
+      r->pts[1] = make_float4(v[q][0][2], v[q][1][2], v[q][0][3], v[q][1][3]);
     }
   if (tid == 0) A.cnt[blockIdx.x] = total;
 }
 
-constexpr int kCullRounds = 16;   // first list rounds kept in registers
-constexpr int kCullCand = 64 * kCullRounds;   // candidates held between evaluations
+constexpr int kCullRounds = 4;    // list entries kept in registers: 64 x this
+constexpr int kCullFlat = 4096;   // list entries found through the start bits
+constexpr int kCullCand = 192;    // candidates held between evaluations (three per lane)
 
-// Waves per SIMD the compiler must fit: a wave is a chain of dependent loads
-// and reductions, so four of them share a SIMD where the registers allow.
-template <int MF, int MI>
-constexpr int kCullWavesPerEU = (MI == 4 && MF <= 8) ? 4 : 1;
+// Edge j (at most its last one) of the listed obstacle of record r, meta m:
+// from its points, else from the edge arrays (act; without it, nothing).
+template <int MI>
+__device__ __forceinline__ void cull_edge(const CullArgs& A, const CullRec& r, const int4& m, int j,
+                                          bool act, float& ax, float& ay, float& bx, float& by) {
+  if (!act) return;
+  const int e = min(j, m.z - 1);
+  if (MI == 4 && (m.w & kRecPoints)) {
+    const float2* p = reinterpret_cast<const float2*>(r.pts);
+    const int n = m.z == 1 ? 1 : (e + 1 < m.z ? e + 1 : 0);
+    const float2 a = p[e], b = p[n];
+    ax = a.x; ay = a.y; bx = b.x; by = b.y;
+  } else {
+    ax = A.ax[m.y + e]; ay = A.ay[m.y + e]; bx = A.bx[m.y + e]; by = A.by[m.y + e];
+  }
+}
 
-template <int MF, int MI>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kCullWavesPerEU<MF, MI>)))
-void cull_stage_kernel(CullArgs A) {
+// One wave per stage, MI lanes per evaluated obstacle.  Bound by its chain
+// (list, footprint, candidates, the adjoint: 7 to 12 us) where the batch has
+// few stages, by VALU issue where it has many.  The footprint's slots in a
+// loop (group_sd) instead of an instance per footprint size: 79 VGPRs and six
+// waves per SIMD instead of 113 and four, and one launch for all sizes (512
+// uneven instances: stage 177 -> 55 us).  A second bound on the candidates,
+// and lists longer than the registers walked with four loads in flight, keep
+// the crowded stages short (64 x 50 x 16384: 36 -> 20 us).  The segments'
+// lists are read as one: lane s holds the
+// length of segment s, their prefix sums place each segment's start as a bit
+// in LDS, and entry f's segment is the number of bits up to f.
+template <int MI>
+__global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
   __shared__ int cand[kCullCand];
-  __shared__ float4 rf[MF];
+  __shared__ uint8_t pick[kCullCand];
+  __shared__ int segbase[64];
+  __shared__ uint32_t starts[kCullFlat / 32];
+  __shared__ FpSlot fs[kMaxFp];
+  __shared__ float dls[64 / MI * kMaxFp];
   __shared__ FpLds fl;
   __shared__ WinnerLds wl;
   const int lane = threadIdx.x;
+  const uint64_t below = (1ull << lane) - 1ull;
   typedef const __attribute__((address_space(4))) CullStage StC;
   const CullStage& R = *(const CullStage*)((StC*)A.stages + blockIdx.x);
   const int g = R.row, nseg = R.nseg;
   const float* p = A.poses + 3 * g;
   const float px = p[0], py = p[1], th = p[2];
-  const float4* box = A.box + R.slot0;
+  const CullRec* rec = A.rec + R.slot0;
   const int* cnt = A.cnt + R.seg0;
-  // lane s: the length of segment s
   const int cv = lane < nseg ? cnt[lane] : 0;
-  auto seg_n = [&](int r) { return (int)lane_u32((uint32_t)cv, r); };
   const FpConst& F = fp_const(A.fps, R.inst);
+  FpRow fr;
+  if (lane < kMaxFp) fr = A.rows[R.inst * kMaxFp + lane];
+  starts[lane] = starts[64 + lane] = 0u;
 
   // squared distance from the stage position to a box; -1 for an irregular
   // obstacle (last in the seed's order, within every bar)
@@ -368,57 +431,121 @@ void cull_stage_kernel(CullArgs A) {
     return (b.x == b.x && within) ? fmaf(gx, gx, gy * gy) : -1.f;
   };
 
-  // ---- the seed.  Round r < kCullRounds: the first 64 entries of segment r,
-  // kept in registers; the rest of the list is read again in the second pass.
-  float d2[kCullRounds];
-  uint32_t kb = 0xffffffffu;
-  int sl = 0;
-#pragma unroll
-  for (int r0 = 0; r0 < kCullRounds; r0 += 8) {
-    float4 b[8];
-#pragma unroll
-    for (int r = 0; r < 8; ++r)
-      b[r] = r0 + r < nseg ? box[(r0 + r) * kSegObst + lane] : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      d2[r0 + r] = __builtin_huge_valf();
-      const bool in = lane < seg_n(r0 + r);   // 0 past the last segment
-      const float x = dist2(b[r]);
-      if (in) {
-        d2[r0 + r] = x;
-        if (__float_as_uint(x) < kb) { kb = __float_as_uint(x); sl = (r0 + r) * kSegObst + lane; }
-      }
-    }
+  // ---- the list as one
+  static_assert(kCullFlat == 64 * 64, "two words of starts per lane");
+  int total;
+  const int start = fw_scan_i32(cv, &total) - cv;
+  wave_sync();
+  const uint64_t full = __ballot(cv > 0);
+  if (cv > 0) {
+    segbase[__popcll(full & below)] = lane * kSegObst - start;
+    if (start < kCullFlat) atomicOr(&starts[start >> 5], 1u << (start & 31));
   }
-  if (lane < MF) {
-    float sn0, cs0;
-    sincosf(th, &sn0, &cs0);
-    rf[lane] = rotated_slot(F, lane, cs0, sn0);
-  }
-  stage_footprint(fl, F);
-  float sn, cs;
-  sincosf(th, &sn, &cs);
-  // entries past the registers: f(slot, live) for 64 entries at a time
-  const bool more = nseg > kCullRounds || __ballot(cv > 64) != 0;
-  auto others = [&](auto f) {
-    if (!more) return;
-    for (int s = 0; s < nseg; ++s) {
-      const int n = cnt[s];
-      for (int i = s < kCullRounds ? 64 : 0; i < n; i += 64)
-        f(s * kSegObst + i + lane, i + lane < n);
+  wave_sync();
+  const int nflat = min(total, 64 * kCullRounds);
+  // the slots of entries 64 r + lane, r = r0 .. r0 + 3; ord: segments with
+  // entries that start before, less one
+  auto slots = [&](int r0, int& ord, int n, int (&sl)[4]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int r = r0 + u;
+      const uint64_t m = ((uint64_t)starts[2 * r + 1] << 32) | starts[2 * r];
+      sl[u] = 0;
+      if (r * 64 + lane < n)
+        sl[u] = segbase[ord + (int)__popcll(m & (below | (1ull << lane)))] + r * 64 + lane;
+      ord += (int)__popcll(m);
     }
   };
-  others([&](int slot, bool live) {
-    if (live) {
-      const uint32_t u = __float_as_uint(dist2(box[slot]));
-      if (u < kb) { kb = u; sl = slot; }
+  int slot[kCullRounds];
+  float d2[kCullRounds];
+  uint32_t kb = 0xffffffffu;
+  int ord0 = -1;
+  static_assert(kCullRounds == 4, "one group of rounds");
+  float4 b0[kCullRounds];
+  slots(0, ord0, nflat, slot);
+#pragma unroll
+  for (int r = 0; r < kCullRounds; ++r) b0[r] = rec[slot[r]].box;
+  // while these are in flight: the footprint at this stage
+  float sn, cs;
+  sincosf(th, &sn, &cs);
+  if (lane < kMaxFp) {
+    const float4 a = fr.q[0], e = fr.q[1], n = fr.q[2], c = fr.q[3];
+    fl.vx[lane] = a.x; fl.vy[lane] = a.y;
+    fl.ex[lane] = e.x; fl.ey[lane] = e.y; fl.einv[lane] = e.z;
+    fl.nx[lane] = n.x; fl.ny[lane] = n.y; fl.pa[lane] = n.z; fl.pb[lane] = n.w;
+    fs[lane] = FpSlot{rotated(a.x, a.y, a.z, a.w, cs, sn), c.x, c.y, e.w, c.z, c.w};
+  }
+#pragma unroll
+  for (int r = 0; r < kCullRounds; ++r) {
+    d2[r] = dist2(b0[r]);
+    if (r * 64 + lane < nflat) kb = min(kb, __float_as_uint(d2[r]));
+  }
+  // The entries past the registers, four rounds of loads in flight:
+  // f(slot, D^2, live) per round until it returns false (that round counts).  (r, ord) or, for a
+  // list longer than kCullFlat or of more than 64 segments, (seg, at) is
+  // where the walk stands.
+  struct Walk { int r, ord, seg, at; };
+  const bool flat = total <= kCullFlat && nseg <= 64;
+  auto walk = [&](Walk& k, auto f) {
+    bool go = true;
+    if (flat) {
+      while (go && k.r * 64 < total) {
+        int sl[4], ord = k.ord;
+        float4 b[4];
+        const int r0 = k.r & ~3;
+        slots(r0, ord, total, sl);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) b[u] = rec[sl[u]].box;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (!go || r0 + u < k.r || (r0 + u) * 64 >= total) continue;
+          go = f(sl[u], dist2(b[u]), (r0 + u) * 64 + lane < total);
+          k.r = r0 + u + 1;
+        }
+        if (k.r == r0 + 4) k.ord = ord;
+      }
+      return k.r * 64 < total;
     }
-  });
+    while (go && k.seg < nseg) {
+      const int c = k.seg < 64 ? (int)lane_u32((uint32_t)cv, k.seg) : cnt[k.seg];
+      float4 b[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = k.at + 64 * u + lane;
+        b[u] = rec[i < c ? k.seg * kSegObst + i : 0].box;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (!go || k.at >= c) continue;
+        const int i = k.at + lane;
+        go = f(k.seg * kSegObst + i, dist2(b[u]), i < c);
+        k.at += 64;
+      }
+      if (k.at >= c) {
+        ++k.seg;
+        k.at = 0;
+      }
+    }
+    return k.seg < nseg;
+  };
+  const bool in_regs = total <= 64 * kCullRounds && nseg <= 64;
+  // past the registers, or (all = true) from the start
+  auto walk_from = [&](bool all) {
+    return flat && !all ? Walk{kCullRounds, ord0, 0, 0} : Walk{0, -1, 0, 0};
+  };
+  if (!in_regs) {
+    Walk k = walk_from(false);
+    walk(k, [&](int, float x, bool live) {
+      if (live) kb = min(kb, __float_as_uint(x));
+      return true;
+    });
+  }
   const uint32_t kmin = fw_min_u32(kb);
-  wave_sync();   // rf and fl are written
+  wave_sync();   // fs and fl are written
 
   uint64_t key = kEmptyKey;
-  int we0 = 0, wmi = 0;   // the winner's edge range
+  int wsl = 0;                          // the winner's list slot and
+  int4 wm = make_int4(0, 0, 0, 0);      // edge range (y, z) and flags (w)
   const bool pose_ok = isfinite(px) && isfinite(py) && isfinite(cs) && isfinite(sn);
   if (!pose_ok) {
     // every obstacle's sd is NaN: the first one that has an edge entry wins
@@ -432,107 +559,135 @@ void cull_stage_kernel(CullArgs A) {
       }
     }
   } else if (kmin != 0xffffffffu) {
-    const int first = __ffsll((unsigned long long)__ballot(kb == kmin)) - 1;
-    const int seed = (int)lane_u32((uint32_t)sl, first);
-    const int4* meta = A.meta + R.slot0;
-
-    // evaluates list slots, a quad of lanes per slot (four-edge class) or a
-    // lane per slot, and folds them into (key, we0, wmi)
-    auto fold = [&](uint64_t k, int e0, int mi) {
-      const uint64_t kw = fw_min_u64(k);
-      if (kw < key) {
-        key = kw;
-        const int f = __ffsll((unsigned long long)__ballot(k == kw)) - 1;
-        we0 = (int)lane_u32((uint32_t)e0, f);
-        wmi = (int)lane_u32((uint32_t)mi, f);
-      }
+    auto least_sd = [&]() {   // a NaN once an invalid obstacle is in
+      return key == kEmptyKey ? __builtin_huge_valf() : from_orderable((uint32_t)(key >> 32));
     };
-    auto quads = [&](int slot, bool act) {
-      int4 m = make_int4(0, 0, 1, 2);
-      if (act) m = meta[slot];
-      const bool bad = (m.w & 2) != 0;
-      QuadEdge q;
-      float ax, ay, bx, by;
-      quad_load(q, A.ax, A.ay, A.bx, A.by, m.y, m.z, (m.w & 1) != 0, act && !bad, F.eps, px, py,
-                ax, ay, bx, by);
-      const float sd = quad_eval<MF>(F, q, rf, [&](float& lo, float& hi) {
-        quad_own(q, ax, ay, bx, by, lo, hi);
-      });
-      const uint32_t k = bad ? 0u : orderable(sd);
-      fold(act ? ((uint64_t)k << 32) | (uint32_t)m.x : kEmptyKey, m.y, m.z);
+    auto bar2 = [&](float t) {
+      const float b = (t + F.rmax + kCullGamma) * (1.0f + 2.0f * F.cull_rel);
+      return b * b;
     };
-    auto lanes = [&](int slot, bool act) {
-      int4 m = make_int4(0, 0, 0, 2);
-      if (act) m = meta[slot];
-      const bool bad = (m.w & 2) != 0;
-      uint32_t k = 0u;
-      if (!bad) {
-        Obst<MI> ob;
-        load_obstacle<MI>(ob, A.ax, A.ay, A.bx, A.by, m.y, m.z, 0x7fffffff, F.eps);
-        k = orderable(obstacle_sd<MF, MI, true>(F, ob, rf, px, py));
-      }
-      fold(act ? ((uint64_t)k << 32) | (uint32_t)m.x : kEmptyKey, m.y, m.z);
-    };
-    if constexpr (MI == 4) quads(seed, true);
-    else lanes(seed, lane == 0);
-
-    // ---- the bar, and every listed obstacle within it
-    const float phi = from_orderable((uint32_t)(key >> 32));   // NaN: the bar is tau
-    const float bar = (fmaxf(phi, F.cull_tau) + F.rmax + kCullGamma) * (1.0f + 2.0f * F.cull_rel);
-    const float bar2 = bar * bar;
-    int n = 0;
-    auto flush = [&]() {
-      wave_sync();
-      if (MI == 4 && n <= 32) {
-        for (int c0 = 0; c0 < n; c0 += 16) {
-          const int c = c0 + (lane >> 2);
-          quads(c < n ? cand[c] : 0, c < n);
-        }
-      } else {
-        for (int c0 = 0; c0 < n; c0 += 64) lanes(c0 + lane < n ? cand[c0 + lane] : 0, c0 + lane < n);
-      }
-      n = 0;
-      wave_sync();
-    };
-    auto collect = [&](int slot, bool t) {
-      const uint64_t m = __ballot(t);
-      if (t) cand[n + (int)__popcll(m & ((1ull << lane) - 1ull))] = slot;
-      n += (int)__popcll(m);
-    };
-#pragma unroll
-    for (int r = 0; r < kCullRounds; ++r) {
-      if (r >= nseg) break;
-      const int slot = r * kSegObst + lane;
-      collect(slot, lane < seg_n(r) && !(d2[r] > bar2) && slot != seed);
+    // First what every bar includes (T >= tau) or, where nothing is that
+    // near, the nearest and those not much further (irregular ones in either
+    // case); their least sd sets the bar, which seldom leaves more.
+    const float least = __uint_as_float(kmin);
+    float first = bar2(F.cull_tau);
+    if (least > first) {
+      const float b = fmaf(0.25f, F.rmax, sqrtf(least) * (1.0f + 1e-5f));
+      first = b * b;
     }
-    others([&](int slot, bool live) {
-      if (n > kCullCand - 64) flush();
-      collect(slot, live && slot != seed && !(dist2(box[slot]) > bar2));
-    });
-    flush();
+    float lo = -2.f, hi = first;   // lo < D^2 <= hi
+    for (int pass = 0; pass < 2; ++pass) {
+      int n = 0;
+      auto take = [&](int sl, float x, bool live) {
+        const bool t = live && x > lo && !(x > hi);
+        const uint64_t m = __ballot(t);
+        const int at = n + (int)__popcll(m & below);
+        if (t && at < kCullCand) cand[at] = sl;
+        n += (int)__popcll(m);
+      };
+#pragma unroll
+      for (int r = 0; r < kCullRounds; ++r) {
+        if (r * 64 >= nflat) break;
+        take(slot[r], d2[r], r * 64 + lane < nflat);
+      }
+      // more of the list: what the registers do not hold or, with more
+      // candidates in them than the buffer holds (or a list too long for the
+      // start bits), all of it again, a buffer at a time
+      const bool again = n > kCullCand || !flat;
+      bool rest = again || !in_regs;
+      if (again) n = 0;
+      Walk k = walk_from(again);
+      do {
+        if (rest && n <= kCullCand - 64)
+          rest = walk(k, [&](int sl, float x, bool live) {
+            take(sl, x, live);
+            return n <= kCullCand - 64;
+          });
+        wave_sync();
+        // More than one round of candidates is cut down by a second bound:
+        // the depth of an overlap is at most the overlap on any axis (the
+        // soft minimum is below the minimum), and on robot axis l that is at
+        // most cn_l - min over the box of (W - p) . n_l; so
+        // sd >= min(0, -that) =: lb.  The lowest go first, then those whose
+        // lb does not exceed the least sd so far (a crowd of 50 to 130
+        // overlapping boxes leaves one or two rounds).
+        float lb[kCullCand / 64];
+        const bool cut = n > 64 / MI;
+        float from = __builtin_nanf(""), to = __builtin_huge_valf();
+#pragma unroll
+        for (int h = 0; h < kCullCand / 64; ++h) {
+          lb[h] = 0.f;
+          if (cut && lane + 64 * h < n) {
+            const float4 b = rec[cand[lane + 64 * h]].box;
+            const float cx = 0.5f * (b.x + b.z) - px, cy = 0.5f * (b.y + b.w) - py;
+            const float hx = 0.5f * (b.z - b.x), hy = 0.5f * (b.w - b.y);
+            float depth = __builtin_huge_valf();
+            for (int l = 0; l < F.m; ++l) {
+              const float nx = fs[l].r.w, ny = -fs[l].r.z;
+              const float w = fmaf(cx, nx, fmaf(cy, ny, -fmaf(hx, fabsf(nx), hy * fabsf(ny))));
+              depth = fminf(depth, fs[l].cn - w);
+            }
+            const float low = -fmaxf(depth, 0.f) - fmaf(F.cull_rel, F.rmax, 1e-4f);
+            lb[h] = b.x == b.x ? low : -__builtin_huge_valf();   // irregular: always
+          }
+        }
+        if (cut) {
+          float x = lb[0];
+#pragma unroll
+          for (int h = 1; h < kCullCand / 64; ++h) x = fminf(x, lb[h]);
+          to = fminf(fw_min_f32(x) + 0.1f, least_sd());
+        }
+        for (int step = 0; step < 2; ++step) {
+          int np = 0;
+#pragma unroll
+          for (int h = 0; h < kCullCand / 64; ++h) {
+            const bool t = lane + 64 * h < n && !(lb[h] > to) && !(lb[h] <= from);
+            const uint64_t m = __ballot(t);
+            if (t) pick[np + (int)__popcll(m & below)] = (uint8_t)(lane + 64 * h);
+            np += (int)__popcll(m);
+          }
+          wave_sync();
+          for (int c0 = 0; c0 < np; c0 += 64 / MI) {
+            const int c = c0 + lane / MI;
+            const bool act = c < np;
+            const int sl = act ? cand[pick[c]] : 0;
+            const int4 m = act ? rec[sl].meta : make_int4(0, 0, 1, kRecBad);
+            const bool bad = (m.w & kRecBad) != 0;
+            float ax = 0.f, ay = 0.f, bx = 0.f, by = 0.f;
+            cull_edge<MI>(A, rec[sl], m, lane & (MI - 1), !bad, ax, ay, bx, by);
+            const float sd = group_sd<MI>(F, fs, dls, ax, ay, bx, by, m.z,
+                                          (m.w & kRecClosed) != 0, !bad, px, py);
+            const uint64_t k =
+                act ? ((uint64_t)(bad ? 0u : orderable(sd)) << 32) | (uint32_t)m.x : kEmptyKey;
+            const uint64_t kw = fw_min_u64(k);
+            if (kw < key) {
+              key = kw;
+              const int f = __ffsll((unsigned long long)__ballot(k == kw)) - 1;
+              wsl = (int)lane_u32((uint32_t)sl, f);
+              wm = make_int4(m.x, (int)lane_u32((uint32_t)m.y, f), (int)lane_u32((uint32_t)m.z, f),
+                             (int)lane_u32((uint32_t)m.w, f));
+            }
+          }
+          wave_sync();
+          if (!cut || least_sd() <= to) break;
+          from = to;
+          to = least_sd();
+        }
+        n = 0;
+      } while (rest);
+      const float bar = bar2(fmaxf(least_sd(), F.cull_tau));   // a NaN: the bar of tau
+      if (bar <= first) break;
+      lo = first;
+      hi = bar;
+    }
   }
-  const bool valid = key != kEmptyKey && (key >> 32) != 0 && wmi >= 1 && wmi <= kMaxObst;
-  write_stage(F, fl, wl, A.ax, A.ay, A.bx, A.by, key, valid, we0, wmi, R.edge_off, cs, sn, px, py,
-              g, A.keys, A.d, A.edge, A.obst, A.grad);
+  const bool valid = key != kEmptyKey && (key >> 32) != 0 && wm.z >= 1 && wm.z <= kMaxObst;
+  write_stage(F, fl, wl,
+              [&](int j, float& ax, float& ay, float& bx, float& by) {
+                cull_edge<MI>(A, rec[wsl], wm, j, true, ax, ay, bx, by);
+              },
+              key, valid, wm.y, wm.z, R.edge_off, cs, sn, px, py, g, A.keys, A.d, A.edge, A.obst,
+              A.grad);
 }
-
-// Per footprint-size entry points (instantiated in psdf_batch_mf*.hip).
-template <int MF>
-hipError_t launch_cull_mf(int mi_class, int n_stages, const CullArgs& a, hipStream_t st) {
-  if (mi_class == 4) cull_stage_kernel<MF, 4><<<n_stages, 64, 0, st>>>(a);
-  else if (mi_class == 8) cull_stage_kernel<MF, 8><<<n_stages, 64, 0, st>>>(a);
-  else cull_stage_kernel<MF, 16><<<n_stages, 64, 0, st>>>(a);
-  return hipGetLastError();
-}
-
-#define PSDF_EXTERN_CULL(MF) \
-  extern template hipError_t launch_cull_mf<MF>(int, int, const CullArgs&, hipStream_t);
-PSDF_EXTERN_CULL(3)
-PSDF_EXTERN_CULL(4)
-PSDF_EXTERN_CULL(5)
-PSDF_EXTERN_CULL(6)
-PSDF_EXTERN_CULL(7)
-PSDF_EXTERN_CULL(8)
-PSDF_EXTERN_CULL(16)
 
 }  // namespace psdf

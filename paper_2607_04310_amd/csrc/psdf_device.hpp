@@ -233,10 +233,12 @@ __device__ __forceinline__ void own_intervals(Obst<MI>& o) {
 
 // The footprint rotated by a stage heading (c, s) = (cos, sin): slot l of rf
 // holds (R v_l, R u_l), u_l the unit direction of robot edge l.
-__device__ __forceinline__ float4 rotated_slot(const FpConst& F, int l, float c, float s) {
-  const float vx = F.vx[l], vy = F.vy[l], ux = F.ux[l], uy = F.uy[l];
+__device__ __forceinline__ float4 rotated(float vx, float vy, float ux, float uy, float c, float s) {
   return make_float4(fmaf(c, vx, -(s * vy)), fmaf(s, vx, c * vy), fmaf(c, ux, -(s * uy)),
                      fmaf(s, ux, c * uy));
+}
+__device__ __forceinline__ float4 rotated_slot(const FpConst& F, int l, float c, float s) {
+  return rotated(F.vx[l], F.vy[l], F.ux[l], F.uy[l], c, s);
 }
 
 // Squared distance from point (px, py) to the segment [a, a + v], with

@@ -70,7 +70,7 @@ __device__ __forceinline__ void epilogue_finish(const FpConst& F, FpLds& FL, Win
     g[0] = g[1] = g[2] = nan;
   } else {
     int jstar = 0;
-    winner_adjoint(F, FL, WL, ax, ay, bx, by, e0, mi, cs, sn, px, py, O.mode != 0, jstar, g);
+    winner_adjoint(F, FL, WL, EdgeArrays{ax, ay, bx, by, e0}, mi, cs, sn, px, py, O.mode != 0, jstar, g);
     dv = from_orderable((uint32_t)(key >> 32));
     ov = i;
     ev = e0 + jstar;

@@ -124,54 +124,150 @@ __device__ __forceinline__ float quad_eval(const FpConst& F, const QuadEdge& q, 
   return sd;
 }
 
-// Lane j's edge of an obstacle with edges [e0, e0 + mi), 1 <= mi <= 4, read
-// from the edge arrays, with the constants load_obstacle derives (act false:
-// no load, the zero edge).  (ax, ay) and (bx, by) get A_j and B_j.
-__device__ __forceinline__ void quad_load(QuadEdge& q, const float* __restrict__ gax,
-                                          const float* __restrict__ gay,
-                                          const float* __restrict__ gbx,
-                                          const float* __restrict__ gby, int e0, int mi,
-                                          bool closed, bool act, float eps, float px, float py,
-                                          float& ax, float& ay, float& bx, float& by) {
-  const int j = threadIdx.x & 3;
-  ax = ay = bx = by = 0.f;
-  if (act) {
-    const int e = e0 + min(j, mi - 1);
-    ax = gax[e]; ay = gay[e]; bx = gbx[e]; by = gby[e];
+// ---- an obstacle of at most G = 4, 8 or 16 edges per group of G lanes, the
+// footprint's slots in a loop over a table in LDS: the same value again, bit
+// for bit, with no footprint size in the code and few registers (which is
+// what a chain of dependent loads needs: waves to hide it behind).
+
+// Slot l of the footprint at a stage: the rotated vertex and direction
+// (rotated_slot), and the constants of robot edge l.
+struct FpSlot {
+  float4 r;                     // R v_l, R u_l
+  float cu, cn, len, oa, ob;
+};
+
+template <int G>
+__device__ __forceinline__ float group_min(float x) {
+  x = fminf(x, quad_dpp<kDppXor1>(x));
+  x = fminf(x, quad_dpp<kDppXor2>(x));
+  if (G > 4) x = fminf(x, quad_dpp<kDppHalfMirror>(x));
+  if (G > 8) x = fminf(x, quad_dpp<kDppMirror>(x));
+  return x;
+}
+template <int G>
+__device__ __forceinline__ float group_max(float x) {
+  x = fmaxf(x, quad_dpp<kDppXor1>(x));
+  x = fmaxf(x, quad_dpp<kDppXor2>(x));
+  if (G > 4) x = fmaxf(x, quad_dpp<kDppHalfMirror>(x));
+  if (G > 8) x = fmaxf(x, quad_dpp<kDppMirror>(x));
+  return x;
+}
+// Lane k of the group's value (k a constant after unrolling).
+template <int G>
+__device__ __forceinline__ float group_lane(float x, int k) {
+  if constexpr (G == 4) {
+    switch (k) {
+      case 0: return quad_dpp<0x00>(x);
+      case 1: return quad_dpp<0x55>(x);
+      case 2: return quad_dpp<0xAA>(x);
+      default: return quad_dpp<0xFF>(x);
+    }
   }
-  const float dx = bx - ax, dy = by - ay;
-  float iv2, il;
-  edge_consts(dx, dy, eps, iv2, il);
-  q.ux = dx * il;
-  q.uy = dy * il;
-  q.len = __builtin_amdgcn_sqrtf(fmaf(dx, dx, dy * dy));
-  q.tax = ax - px; q.tay = ay - py;
-  q.tbx = bx - px; q.tby = by - py;
-  q.mi = mi;
-  q.closed = closed;
-  q.bad = false;
+  return __shfl(x, ((threadIdx.x & 63) & ~(G - 1)) + k);
 }
 
-// Lane j's own-axis interval from the quad's edges (own_intervals).
-__device__ __forceinline__ void quad_own(const QuadEdge& q, float ax, float ay, float bx, float by,
-                                         float& lo, float& hi) {
-  lo = __builtin_huge_valf();
-  hi = -__builtin_huge_valf();
-  auto point = [&](float wx, float wy) {
-    const float p = fmaf(wy - ay, q.ux, -((wx - ax) * q.uy));
-    lo = fminf(lo, p);
-    hi = fmaxf(hi, p);
-  };
-  point(quad_dpp<0x00>(ax), quad_dpp<0x00>(ay));
-  point(quad_dpp<0x55>(ax), quad_dpp<0x55>(ay));
-  point(quad_dpp<0xAA>(ax), quad_dpp<0xAA>(ay));
-  point(quad_dpp<0xFF>(ax), quad_dpp<0xFF>(ay));
-  if (!q.closed) {
-    point(quad_dpp<0x00>(bx), quad_dpp<0x00>(by));
-    point(quad_dpp<0x55>(bx), quad_dpp<0x55>(by));
-    point(quad_dpp<0xAA>(bx), quad_dpp<0xAA>(by));
-    point(quad_dpp<0xFF>(bx), quad_dpp<0xFF>(by));
+// sd of an obstacle of mi edges, 1 <= mi <= G, at a stage at (px, py); lane j
+// of the group has its edge min(j, mi - 1), A = (ax, ay), B = (bx, by)
+// (act; without it the value is meaningless).  dls holds 64 / G x kMaxFp
+// floats of the wave.  Every lane of the wave is active.
+template <int G>
+__device__ __forceinline__ float group_sd(const FpConst& F, const FpSlot* fs, float* dls,
+                                          float ax, float ay, float bx, float by, int mi,
+                                          bool closed, bool act, float px, float py) {
+  const int lane = threadIdx.x & 63, j = lane & (G - 1), m = F.m;
+  float* dl = dls + (lane / G) * kMaxFp;
+  const float dx = bx - ax, dy = by - ay;
+  float iv2, il;
+  edge_consts(dx, dy, F.eps, iv2, il);
+  const float ux = dx * il, uy = dy * il;
+  const float len = __builtin_amdgcn_sqrtf(fmaf(dx, dx, dy * dy));
+  const float tax = ax - px, tay = ay - py, tbx = bx - px, tby = by - py;
+  const float ca = fmaf(tax, ux, tay * uy);
+  const float cb = fmaf(tay, ux, -(tax * uy));
+  const bool open = act && !closed;
+  const bool any_open = __ballot(open) != 0;
+
+  float dv2 = __builtin_huge_valf(), rlo = __builtin_huge_valf(), rhi = -__builtin_huge_valf();
+  float de2 = __builtin_huge_valf(), mu = __builtin_huge_valf();
+  bool sep = false;
+#pragma unroll 2
+  for (int l = 0; l < m; ++l) {
+    const FpSlot f = fs[l];
+    // robot vertex l against edge j; the robot's interval on n'_j
+    const float a = fmaf(f.r.x, ux, fmaf(f.r.y, uy, -ca));
+    const float b = fmaf(f.r.y, ux, fmaf(-f.r.x, uy, -cb));
+    rlo = fminf(rlo, b);
+    rhi = fmaxf(rhi, b);
+    dv2 = fminf(dv2, frame_d2(a, b, len));
+    // the point(s) of slot j against robot edge l, and the overlap on its
+    // normal across the group
+    const float a2 = fmaf(tax, f.r.z, fmaf(tay, f.r.w, -f.cu));
+    const float b2 = fmaf(tax, f.r.w, fmaf(-tay, f.r.z, -f.cn));
+    de2 = fminf(de2, frame_d2(a2, b2, f.len));
+    float lo = b2, hi = b2;
+    if (any_open) {
+      const float a3 = fmaf(tbx, f.r.z, fmaf(tby, f.r.w, -f.cu));
+      const float b3 = fmaf(tbx, f.r.w, fmaf(-tby, f.r.z, -f.cn));
+      if (open) {
+        de2 = fminf(de2, frame_d2(a3, b3, f.len));
+        lo = fminf(lo, b3);
+        hi = fmaxf(hi, b3);
+      }
+    }
+    lo = group_min<G>(lo);
+    hi = group_max<G>(hi);
+    const float d = fminf(hi - f.oa, f.ob - lo);
+    sep = sep || (d < -F.eps_sat);
+    mu = fminf(mu, fmaxf(d, 0.0f));
+    if (j == 0) dl[l] = d;
   }
+  dv2 = group_min<G>(dv2);
+  de2 = group_min<G>(de2);
+  float dlo = 0.f;   // obstacle axis j
+  if (__ballot(act && !sep)) {
+    // the obstacle's interval on its own axis j (own_intervals)
+    float lo = __builtin_huge_valf(), hi = -__builtin_huge_valf();
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      const float wx = group_lane<G>(ax, k), wy = group_lane<G>(ay, k);
+      const float q = fmaf(wy - ay, ux, -((wx - ax) * uy));
+      lo = fminf(lo, q);
+      hi = fmaxf(hi, q);
+    }
+    if (any_open) {
+#pragma unroll
+      for (int k = 0; k < G; ++k) {
+        const float wx = group_lane<G>(bx, k), wy = group_lane<G>(by, k);
+        const float q = fmaf(wy - ay, ux, -((wx - ax) * uy));
+        if (open) {
+          lo = fminf(lo, q);
+          hi = fmaxf(hi, q);
+        }
+      }
+    }
+    dlo = fminf(hi - rlo, rhi - lo);
+    sep = sep || group_max<G>((dlo < -F.eps_sat) ? 1.f : 0.f) > 0.f;
+  }
+  float sd = sqrtf(fminf(dv2, de2));
+  if (__ballot(act && !sep)) {
+    mu = fminf(mu, group_min<G>(fmaxf(dlo, 0.0f)));
+    float depth = mu;
+    if (!F.hard) {
+      wave_sync();   // dl is written
+      float acc = 0.0f;
+      for (int l = 0; l < m; ++l) acc += expf(-F.eta * (fmaxf(dl[l], 0.0f) - mu));
+      const float ej = expf(-F.eta * (fmaxf(dlo, 0.0f) - mu));
+#pragma unroll
+      for (int k = 0; k < G; ++k) {
+        const float e = group_lane<G>(ej, k);
+        if (k < mi) acc += e;
+      }
+      depth = mu - logf(acc) / F.eta;
+    }
+    if (!sep) sd = -depth;
+  }
+  wave_sync();   // dl is free again
+  return sd;
 }
 
 }  // namespace psdf

@@ -800,8 +800,8 @@ __global__ __launch_bounds__(64) void screen_bound_kernel(ScreenArgs A) {
     int e0, mi;
     const bool valid = key_range(keyK, A.off, in.obst_off, in.M, in.edge_off, in.E, e0, mi);
     wave_sync();   // fl is written
-    write_stage(F, fl, wl, A.ax, A.ay, A.bx, A.by, keyK, valid, e0, mi, in.edge_off, cs, sn, px,
-                py, s, A.keys, A.d, A.edge, A.obst, A.grad);
+    write_stage(F, fl, wl, EdgeArrays{A.ax, A.ay, A.bx, A.by, e0}, keyK, valid, e0, mi,
+                in.edge_off, cs, sn, px, py, s, A.keys, A.d, A.edge, A.obst, A.grad);
   }
   if (lane == 0) {
     if (!(A.finish && cert)) A.keys[s] = keyK;
@@ -888,8 +888,8 @@ __global__ __launch_bounds__(256) void screen_fallback_kernel(ScreenArgs A, int 
           int e0, mi2;
           const bool valid = key_range(kf, A.off, in.obst_off, in.M, in.edge_off, in.E, e0, mi2);
           wave_sync();   // fl is written
-          write_stage(F, fl, wl, A.ax, A.ay, A.bx, A.by, kf, valid, e0, mi2, in.edge_off, cs, sn,
-                      px, py, s, A.keys, A.d, A.edge, A.obst, A.grad);
+          write_stage(F, fl, wl, EdgeArrays{A.ax, A.ay, A.bx, A.by, e0}, kf, valid, e0, mi2,
+                      in.edge_off, cs, sn, px, py, s, A.keys, A.d, A.edge, A.obst, A.grad);
         }
       }
     }

@@ -236,23 +236,22 @@ __device__ __forceinline__ void wave_stages(const FpConst& F, const float* __res
                                       rft, emit);
 }
 
-// Whole-wave call with uniform arguments; the obstacle owns edges
-// [e0, e0 + mi), 1 <= mi <= kMaxObst.  Results are uniform across the wave.
+// Whole-wave call with uniform arguments; the obstacle has mi edges,
+// 1 <= mi <= kMaxObst, and edge(j, ax, ay, bx, by) gives A_j and B_j.
+// Results are uniform across the wave.
+template <class Edge>
 __device__ __forceinline__ void winner_adjoint(const FpConst& F, const FpLds& FL, WinnerLds& W,
-                               const float* __restrict__ ax, const float* __restrict__ ay,
-                               const float* __restrict__ bx, const float* __restrict__ by, int e0,
-                               int mi, float c, float s, float px, float py, bool want_grad,
-                               int& jstar, float g[3]) {
+                               Edge edge, int mi, float c, float s, float px, float py,
+                               bool want_grad, int& jstar, float g[3]) {
   const int lane = threadIdx.x & 63;
   const int m = F.m;
 
   // ---- stage the obstacle (lane j <-> edge j)
   bool open_edge = false;
   if (lane < mi) {
-    const float a0 = ax[e0 + lane], a1 = ay[e0 + lane];
-    const float b0 = bx[e0 + lane], b1 = by[e0 + lane];
-    const int nxt = lane + 1 < mi ? lane + 1 : 0;
-    const float n0 = ax[e0 + nxt], n1 = ay[e0 + nxt];
+    float a0, a1, b0, b1, n0, n1, x0, x1;
+    edge(lane, a0, a1, b0, b1);
+    edge(lane + 1 < mi ? lane + 1 : 0, n0, n1, x0, x1);   // x0, x1: unused
     open_edge = __float_as_uint(b0) != __float_as_uint(n0) || __float_as_uint(b1) != __float_as_uint(n1);
     float iv2, il, tx, ty, vx, vy;
     edge_consts(b0 - a0, b1 - a1, F.eps, iv2, il);
@@ -409,5 +408,19 @@ __device__ __forceinline__ void winner_adjoint(const FpConst& F, const FpLds& FL
   g[1] = -(s * sx + c * sy);
   g[2] = gth;
 }
+
+// The edges [e0, ...) of the edge arrays as winner_adjoint reads them.
+struct EdgeArrays {
+  const float* __restrict__ ax;
+  const float* __restrict__ ay;
+  const float* __restrict__ bx;
+  const float* __restrict__ by;
+  int e0;
+  __device__ __forceinline__ void operator()(int j, float& a0, float& a1, float& b0,
+                                             float& b1) const {
+    a0 = ax[e0 + j]; a1 = ay[e0 + j];
+    b0 = bx[e0 + j]; b1 = by[e0 + j];
+  }
+};
 
 }  // namespace psdf
