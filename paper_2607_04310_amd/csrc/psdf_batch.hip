@@ -393,7 +393,7 @@ __global__ __launch_bounds__(64) void batch_finish_kernel(
     sincosf(th, &sn, &cs);
     wave_sync();
     // last round: the winner's edges
-    write_stage(F, fl, wl, EdgeArrays{ax, ay, bx, by, e0}, key, valid, e0, mi, R.edge_off, cs, sn,
+    write_stage<kMaxObst>(F, fl, wl, EdgeArrays{ax, ay, bx, by, e0}, key, valid, e0, mi, R.edge_off, cs, sn,
                 px, py, g, keys,
                 d, edge, obst, grad);
   }

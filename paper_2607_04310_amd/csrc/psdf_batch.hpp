@@ -93,13 +93,14 @@ __device__ __forceinline__ bool key_range(uint64_t key, const int* __restrict__ 
 }
 
 // Stage g's outputs from its final key (Sec. IV-D: the winner adjoint of
-// the winning obstacle, edges [e0, e0 + mi) global, read through src): an empty key gives the
-// empty-set result (d = +inf, no winner, zero gradient); a key that names
-// no usable obstacle (valid false) gives NaN.  One whole wave with uniform
+// the winning obstacle, edges [e0, e0 + mi) global, at most MAXE of them,
+// read through src): an empty key gives the empty-set result (d = +inf, no
+// winner, zero gradient); a key that names no usable obstacle (valid false)
+// gives NaN.  One whole wave with uniform
 // arguments; fl must hold F (stage_footprint) and be visible to the wave.
 // Every kernel that ends a stage goes through here, so a stage's outputs do
 // not depend on which kernel finished it.
-template <class Edge>
+template <int MAXE, class Edge>
 __device__ __forceinline__ void write_stage(const FpConst& F, const FpLds& fl, WinnerLds& wl,
                                             Edge src, uint64_t key, bool valid, int e0, int mi, int edge_off, float cs,
                                             float sn, float px, float py, int g,
@@ -113,8 +114,8 @@ __device__ __forceinline__ void write_stage(const FpConst& F, const FpLds& fl, W
     gv[0] = gv[1] = gv[2] = dv;
   } else if (valid) {
     int jstar = 0;
-    winner_adjoint(F, fl, wl, src, mi, cs, sn, px, py, true, jstar, gv);
     dv = from_orderable((uint32_t)(key >> 32));
+    winner_adjoint<MAXE>(F, fl, wl, src, mi, cs, sn, px, py, true, dv, jstar, gv);
     ov = (int)(key & 0xffffffffu);
     ev = e0 - edge_off + jstar;
   }

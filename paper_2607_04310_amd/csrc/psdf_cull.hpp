@@ -682,7 +682,7 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
     }
   }
   const bool valid = key != kEmptyKey && (key >> 32) != 0 && wm.z >= 1 && wm.z <= kMaxObst;
-  write_stage(F, fl, wl,
+  write_stage<MI>(F, fl, wl,
               [&](int j, float& ax, float& ay, float& bx, float& by) {
                 cull_edge<MI>(A, rec[wsl], wm, j, true, ax, ay, bx, by);
               },

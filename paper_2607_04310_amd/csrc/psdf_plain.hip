@@ -41,7 +41,9 @@ struct EpiOut {
 
 // One wave finishes stage s from its winning key: the winner's edge range
 // (e0, mi) comes from the aux word (have_aux) or from the offsets; the wave
-// recomputes the winner (winner_adjoint) and lane 0 writes the outputs.
+// recomputes the winner (winner_adjoint; at most MAXE edges) and lane 0 writes
+// the outputs.
+template <int MAXE>
 __device__ __forceinline__ void epilogue_finish(const FpConst& F, FpLds& FL, WinnerLds& WL,
                                                 const float* __restrict__ ax,
                                                 const float* __restrict__ ay,
@@ -70,8 +72,9 @@ __device__ __forceinline__ void epilogue_finish(const FpConst& F, FpLds& FL, Win
     g[0] = g[1] = g[2] = nan;
   } else {
     int jstar = 0;
-    winner_adjoint(F, FL, WL, EdgeArrays{ax, ay, bx, by, e0}, mi, cs, sn, px, py, O.mode != 0, jstar, g);
     dv = from_orderable((uint32_t)(key >> 32));
+    winner_adjoint<MAXE>(F, FL, WL, EdgeArrays{ax, ay, bx, by, e0}, mi, cs, sn, px, py,
+                         O.mode != 0, dv, jstar, g);
     ov = i;
     ev = e0 + jstar;
   }
@@ -164,7 +167,7 @@ __global__ __launch_bounds__(64 * kEpiWaves) void epilogue_kernel(
     have_aux = true;
   }
   wave_sync();
-  epilogue_finish(F, fl[w], wl[w], ax, ay, bx, by, off, E, M, s, px, py, cs, sn, key, e0, mi,
+  epilogue_finish<kMaxObst>(F, fl[w], wl[w], ax, ay, bx, by, off, E, M, s, px, py, cs, sn, key, e0, mi,
                   have_aux, scale, O);
 }
 
@@ -216,7 +219,7 @@ __global__ __launch_bounds__(kWideThreads) void epilogue_wide_kernel(
   sincosf(p[2], &sn, &cs);
   const uint64_t a = kmin != kEmptyKey ? s_aux : 0;
   if (lane == 0) O.keys[s] = kmin;
-  epilogue_finish(F, fl, wl, ax, ay, bx, by, off, E, M, s, px, py, cs, sn, kmin,
+  epilogue_finish<kMaxObst>(F, fl, wl, ax, ay, bx, by, off, E, M, s, px, py, cs, sn, kmin,
                   (int)(uint32_t)(a >> 32), (int)(uint32_t)(a & 0xffffffffu), true, 1.0f, O);
 }
 
@@ -304,7 +307,7 @@ __global__ __launch_bounds__(64 * NW) void small_kernel(
       }
   }
   if (lane == 0) O.keys[s] = key;
-  epilogue_finish(F, fl[0], wl[0], ax, ay, bx, by, off, E, M, s, px, py, cs, sn, key,
+  epilogue_finish<4>(F, fl[0], wl[0], ax, ay, bx, by, off, E, M, s, px, py, cs, sn, key,
                   (int)(uint32_t)(a >> 32), (int)(uint32_t)(a & 0xffffffffu), true, 1.0f, O);
 }
 

@@ -800,7 +800,7 @@ __global__ __launch_bounds__(64) void screen_bound_kernel(ScreenArgs A) {
     int e0, mi;
     const bool valid = key_range(keyK, A.off, in.obst_off, in.M, in.edge_off, in.E, e0, mi);
     wave_sync();   // fl is written
-    write_stage(F, fl, wl, EdgeArrays{A.ax, A.ay, A.bx, A.by, e0}, keyK, valid, e0, mi,
+    write_stage<MI>(F, fl, wl, EdgeArrays{A.ax, A.ay, A.bx, A.by, e0}, keyK, valid, e0, mi,
                 in.edge_off, cs, sn, px, py, s, A.keys, A.d, A.edge, A.obst, A.grad);
   }
   if (lane == 0) {
@@ -888,7 +888,7 @@ __global__ __launch_bounds__(256) void screen_fallback_kernel(ScreenArgs A, int 
           int e0, mi2;
           const bool valid = key_range(kf, A.off, in.obst_off, in.M, in.edge_off, in.E, e0, mi2);
           wave_sync();   // fl is written
-          write_stage(F, fl, wl, EdgeArrays{A.ax, A.ay, A.bx, A.by, e0}, kf, valid, e0, mi2,
+          write_stage<MI>(F, fl, wl, EdgeArrays{A.ax, A.ay, A.bx, A.by, e0}, kf, valid, e0, mi2,
                       in.edge_off, cs, sn, px, py, s, A.keys, A.d, A.edge, A.obst, A.grad);
         }
       }

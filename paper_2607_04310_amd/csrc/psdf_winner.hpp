@@ -11,8 +11,8 @@
 //     separated branch through the winning point-segment pair (first entry on
 //     ties), otherwise through the soft-min weights of the axis overlaps and,
 //     for each axis, the first extreme vertices of both intervals.
-// Lanes share the work: one pool entry per lane (strided), one SAT axis per
-// lane; the winner's local geometry is staged in LDS.
+// Lanes share the work: one pool pair per lane (winner_pools4, or strided over
+// more edges), one SAT axis per lane.
 //
 // The adjoint is contracted on the fly: a local point P~ with adjoint gP
 // contributes -R gP to d/dp and gP . (P~_y, -P~_x) to d/dtheta (P~ moves by
@@ -236,16 +236,112 @@ __device__ __forceinline__ void wave_stages(const FpConst& F, const float* __res
                                       rft, emit);
 }
 
-// Whole-wave call with uniform arguments; the obstacle has mi edges,
-// 1 <= mi <= kMaxObst, and edge(j, ax, ay, bx, by) gives A_j and B_j.
-// Results are uniform across the wave.
+// The point-segment pools of the winner (Sec. IV-B) as the adjoint uses them:
+// the active pair (the smallest squared distance, first entry on ties; entry
+// l * mi + j is robot vertex l against obstacle edge j, entry m * mi + k * m + l
+// V_obs point k against robot edge l), Q against the segment S + t V with
+// iv = 1 / (|V|^2 + eps), and the reported edge.
+struct WinnerPools {
+  float d2, qx, qy, sx, sy, vx, vy, iv;
+  bool vtype;    // Q is a robot vertex
+  bool closed;
+  int jstar;
+};
+
+// Minimum over the 16 lanes l = 0 .. 15 at 4 l + j, for each j (all lanes).
+__device__ __forceinline__ uint32_t stride4_min(uint32_t x) {
+  x = min(x, dpp_u32<0x124>(x));   // row rotate by 4, 8
+  x = min(x, dpp_u32<0x128>(x));
+  const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = min(r[0], r[1]);
+  const auto q = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return min(q[0], q[1]);
+}
+
+// At most four edges: lane 4 l + j holds robot slot l and edge j, so every
+// pair is one lane's (no index division, no LDS pass over the pairs).
+// stage: also writes the obstacle's geometry to W.
 template <class Edge>
-__device__ __forceinline__ void winner_adjoint(const FpConst& F, const FpLds& FL, WinnerLds& W,
-                               Edge edge, int mi, float c, float s, float px, float py,
-                               bool want_grad, int& jstar, float g[3]) {
+__device__ __forceinline__ WinnerPools winner_pools4(const FpConst& F, const FpLds& FL,
+                                                     WinnerLds& W, Edge edge, int mi, float c,
+                                                     float s, float px, float py, bool stage) {
+  const int lane = threadIdx.x & 63, j = lane & 3, l = lane >> 2, m = F.m;
+  float a0, a1, b0, b1;
+  edge(min(j, mi - 1), a0, a1, b0, b1);
+  const float rvx = FL.vx[l], rvy = FL.vy[l], rex = FL.ex[l], rey = FL.ey[l], rin = FL.einv[l];
+  // the value that lane j + 1 of the quad has, or lane 0 for the last edge's
+  // lane (both moves by all lanes, then the choice)
+  const bool last = j + 1 >= mi;
+  auto next = [&](uint32_t x) {
+    const uint32_t first = dpp_u32<0x00>(x), right = dpp_u32<0x39>(x);
+    return last ? first : right;
+  };
+  const uint32_t n0 = next(__float_as_uint(a0)), n1 = next(__float_as_uint(a1));
+  const bool open_edge = j < mi && (__float_as_uint(b0) != n0 || __float_as_uint(b1) != n1);
+  float iv2, il, tx, ty, vx, vy;
+  edge_consts(b0 - a0, b1 - a1, F.eps, iv2, il);
+  local_point(a0, a1, c, s, px, py, tx, ty);
+  local_vector(b0 - a0, b1 - a1, c, s, vx, vy);
+  if (stage && lane < mi) {
+    W.tax[lane] = tx; W.tay[lane] = ty; W.vx[lane] = vx; W.vy[lane] = vy;
+    W.nx[lane] = -vy * il; W.ny[lane] = vx * il;
+    W.iv2[lane] = iv2; W.il[lane] = il;
+    W.px[lane] = tx; W.py[lane] = ty;
+    W.px[mi + lane] = tx + vx; W.py[mi + lane] = ty + vy;
+  }
+  WinnerPools r;
+  r.closed = mi >= 3 && __ballot(open_edge) == 0;
+  const bool act = l < m && j < mi;
+  const int PV = m * mi;
+  const uint32_t none = 0xffffffffu;
+  const uint32_t dv = act ? __float_as_uint(seg_d2(rvx, rvy, tx, ty, vx, vy, iv2)) : none;
+  const uint32_t da = act ? __float_as_uint(seg_d2(tx, ty, rvx, rvy, rex, rey, rin)) : none;
+  uint32_t d = dv, e = (uint32_t)(l * mi + j);
+  if (da < d) { d = da; e = (uint32_t)(PV + j * m + l); }
+  uint32_t ep = min(dv, da);
+  const float wx = tx + vx, wy = ty + vy;
+  if (!r.closed) {
+    const uint32_t db = act ? __float_as_uint(seg_d2(wx, wy, rvx, rvy, rex, rey, rin)) : none;
+    if (db < d) { d = db; e = (uint32_t)(PV + (mi + j) * m + l); }
+    ep = min(ep, db);
+  }
+  // the active pair
+  const uint32_t dmin = fw_min_u32(d);
+  const uint32_t emin = fw_min_u32(d == dmin ? e : none);
+  const int w = __ffsll((unsigned long long)__ballot(d == dmin && e == emin)) - 1;
+  r.d2 = __uint_as_float(dmin);
+  r.vtype = (int)emin < PV;
+  const bool btype = (int)emin >= PV + mi * m;
+  auto from = [&](float x) { return __uint_as_float(lane_u32(__float_as_uint(x), w)); };
+  r.qx = from(r.vtype ? rvx : (btype ? wx : tx));
+  r.qy = from(r.vtype ? rvy : (btype ? wy : ty));
+  r.sx = from(r.vtype ? tx : rvx);
+  r.sy = from(r.vtype ? ty : rvy);
+  r.vx = from(r.vtype ? vx : rex);
+  r.vy = from(r.vtype ? vy : rey);
+  r.iv = from(r.vtype ? iv2 : rin);
+  // the reported edge: a closed polygon's point belongs to two edges
+  ep = stride4_min(ep);
+  if (r.closed) {
+    const uint32_t p = stride4_min(da);
+    ep = min(ep, next(p));
+  }
+  ep = j < mi ? min(ep, 0x7f800000u) : none;
+  uint32_t q = min(ep, dpp_u32<kDppXor1>(ep));
+  q = min(q, dpp_u32<kDppXor2>(q));
+  r.jstar = __ffs((int)(__ballot(ep == q) & 15ull)) - 1;
+  wave_sync();   // W is written
+  return r;
+}
+
+// Any edge count up to kMaxObst: the pairs strided over the lanes, the
+// obstacle's geometry (always written) and the per-edge minima in LDS.
+template <class Edge>
+__device__ __forceinline__ WinnerPools winner_pools(const FpConst& F, const FpLds& FL,
+                                                    WinnerLds& W, Edge edge, int mi, float c,
+                                                    float s, float px, float py) {
   const int lane = threadIdx.x & 63;
   const int m = F.m;
-
   // ---- stage the obstacle (lane j <-> edge j)
   bool open_edge = false;
   if (lane < mi) {
@@ -264,30 +360,34 @@ __device__ __forceinline__ void winner_adjoint(const FpConst& F, const FpLds& FL
     W.px[mi + lane] = tx + vx; W.py[mi + lane] = ty + vy;
   }
   if (lane < kMaxObst) W.epool[lane] = 0x7f800000u;   // +inf
-  const bool closed = mi >= 3 && __ballot(open_edge) == 0;
-  const int nv = closed ? mi : 2 * mi;
+  WinnerPools r;
+  r.closed = mi >= 3 && __ballot(open_edge) == 0;
+  const int nv = r.closed ? mi : 2 * mi;
   wave_sync();
 
-  // ---- pools (Sec. IV-B): entry e < m*mi is robot vertex l = e / mi against
-  // obstacle edge j = e % mi; the rest is V_obs point k against robot edge l.
   const int PV = m * mi, P = PV + nv * m;
-  uint64_t best = ~0ull;
-  for (int e = lane; e < P; e += 64) {
-    float qx, qy, sax, say, svx, svy, siv;
-    int ej, ej2 = -1;
-    if (e < PV) {
+  // operands of entry e; ej and ej2 (or -1): the edges it belongs to
+  auto entry = [&](int e, int& ej, int& ej2) {
+    ej2 = -1;
+    r.vtype = e < PV;
+    if (r.vtype) {
       const int l = e / mi, j = e - l * mi;
-      qx = FL.vx[l]; qy = FL.vy[l];
-      sax = W.tax[j]; say = W.tay[j]; svx = W.vx[j]; svy = W.vy[j]; siv = W.iv2[j];
+      r.qx = FL.vx[l]; r.qy = FL.vy[l];
+      r.sx = W.tax[j]; r.sy = W.tay[j]; r.vx = W.vx[j]; r.vy = W.vy[j]; r.iv = W.iv2[j];
       ej = j;
     } else {
       const int e2 = e - PV, k = e2 / m, l = e2 - k * m;
-      qx = W.px[k]; qy = W.py[k];
-      sax = FL.vx[l]; say = FL.vy[l]; svx = FL.ex[l]; svy = FL.ey[l]; siv = FL.einv[l];
+      r.qx = W.px[k]; r.qy = W.py[k];
+      r.sx = FL.vx[l]; r.sy = FL.vy[l]; r.vx = FL.ex[l]; r.vy = FL.ey[l]; r.iv = FL.einv[l];
       ej = k < mi ? k : k - mi;
-      if (closed) ej2 = k > 0 ? k - 1 : mi - 1;
+      if (r.closed) ej2 = k > 0 ? k - 1 : mi - 1;
     }
-    const float d2 = seg_d2(qx, qy, sax, say, svx, svy, siv);
+  };
+  uint64_t best = ~0ull;
+  int ej, ej2;
+  for (int e = lane; e < P; e += 64) {
+    entry(e, ej, ej2);
+    const float d2 = seg_d2(r.qx, r.qy, r.sx, r.sy, r.vx, r.vy, r.iv);
     atomicMin(&W.epool[ej], __float_as_uint(d2));
     if (ej2 >= 0) atomicMin(&W.epool[ej2], __float_as_uint(d2));
     const uint64_t key = ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)e;
@@ -296,12 +396,32 @@ __device__ __forceinline__ void winner_adjoint(const FpConst& F, const FpLds& FL
   best = wave_min_u64(best);
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
   wave_sync();
-  {
-    const uint64_t ek = lane < mi ? (((uint64_t)W.epool[lane] << 32) | (uint32_t)lane) : ~0ull;
-    jstar = (int)(wave_min_u64(ek) & 0xffffffffu);
-  }
+  const uint64_t ek = lane < mi ? (((uint64_t)W.epool[lane] << 32) | (uint32_t)lane) : ~0ull;
+  r.jstar = (int)(wave_min_u64(ek) & 0xffffffffu);
+  entry((int)(best & 0xffffffffu), ej, ej2);
+  r.d2 = __uint_as_float((uint32_t)(best >> 32));
+  return r;
+}
+
+// Whole-wave call with uniform arguments; the obstacle has mi edges,
+// 1 <= mi <= MAXE, edge(j, ax, ay, bx, by) gives A_j and B_j, and sd is its
+// signed distance (the stage's minimum).  Results are uniform across the wave.
+template <int MAXE, class Edge>
+__device__ __forceinline__ void winner_adjoint(const FpConst& F, const FpLds& FL, WinnerLds& W,
+                               Edge edge, int mi, float c, float s, float px, float py,
+                               bool want_grad, float sd, int& jstar, float g[3]) {
+  const int lane = threadIdx.x & 63;
+  const int m = F.m;
+  // sets that the axis test does not separate have sd <= log(axes) / eta
+  // <= sd_floor, so a larger sd needs no axis test here
+  const bool far = sd > F.sd_floor;
+  const WinnerPools wp = MAXE <= 4 || mi <= 4
+                             ? winner_pools4(F, FL, W, edge, mi, c, s, px, py, want_grad && !far)
+                             : winner_pools(F, FL, W, edge, mi, c, s, px, py);
+  jstar = wp.jstar;
   g[0] = g[1] = g[2] = 0.f;
   if (!want_grad) return;
+  const int nv = wp.closed ? mi : 2 * mi;
 
   // ---- SAT (Sec. IV-C): lane q < m + mi owns axis q.
   const int K = m + mi;
@@ -309,7 +429,7 @@ __device__ __forceinline__ void winner_adjoint(const FpConst& F, const FpLds& FL
   float lox = 0.f, loy = 0.f, hix = 0.f, hiy = 0.f;      // obstacle extremes
   float rlx = 0.f, rly = 0.f, rhx = 0.f, rhy = 0.f;      // robot extremes (obstacle axes)
   int br = 0;
-  if (lane < K) {
+  if (!far && lane < K) {
     float alo, ahi;
     if (lane < m) {
       nxq = FL.nx[lane]; nyq = FL.ny[lane];
@@ -335,24 +455,14 @@ __device__ __forceinline__ void winner_adjoint(const FpConst& F, const FpLds& FL
     dl = fminf(d1, d2);
     br = d1 <= d2 ? 0 : 1;
   }
-  const bool sep = __ballot(lane < K && dl < -F.eps_sat) != 0;
+  const bool sep = far || __ballot(lane < K && dl < -F.eps_sat) != 0;
 
   float sx = 0.f, sy = 0.f, gth = 0.f;
   if (sep) {
     // d sd / d(d^2) through the winning pair: d^2 = |w - t V|^2, w = Q - A
-    const int e = (int)(best & 0xffffffffu);
-    const float d2b = __uint_as_float((uint32_t)(best >> 32));
-    float qx, qy, sax, say, svx, svy, siv;
-    const bool vtype = e < PV;
-    if (vtype) {
-      const int l = e / mi, j = e - l * mi;
-      qx = FL.vx[l]; qy = FL.vy[l];
-      sax = W.tax[j]; say = W.tay[j]; svx = W.vx[j]; svy = W.vy[j]; siv = W.iv2[j];
-    } else {
-      const int e2 = e - PV, k = e2 / m, l = e2 - k * m;
-      qx = W.px[k]; qy = W.py[k];
-      sax = FL.vx[l]; say = FL.vy[l]; svx = FL.ex[l]; svy = FL.ey[l]; siv = FL.einv[l];
-    }
+    const float qx = wp.qx, qy = wp.qy, sax = wp.sx, say = wp.sy, svx = wp.vx, svy = wp.vy;
+    const float siv = wp.iv, d2b = wp.d2;
+    const bool vtype = wp.vtype;
     const float coef = 1.0f / (2.0f * sqrtf(d2b));
     const float wx = qx - sax, wy = qy - say;
     const float u = fmaf(wx, svx, wy * svy) * siv;
