@@ -90,6 +90,8 @@ struct psdf_batch_plan {
   CullSeg* d_segs = nullptr;
   CullStage* d_cstages = nullptr;
   CullRec* d_crec = nullptr;
+  float4* d_sbox = nullptr;     // taken once per edge set (psdf_batch_stage)
+  CullRec* d_srec = nullptr;
   int* d_ccnt = nullptr;
   // graph
   hipStream_t cap_stream = nullptr;
@@ -475,19 +477,32 @@ hipError_t cull_create(psdf_batch_plan* p) {
   return err;
 }
 
-hipError_t cull_enqueue(psdf_batch_plan* p, const BatchArgs& b, hipStream_t st) {
-  CullArgs a{p->d_fp, p->d_frows, p->d_inst, p->d_segs, p->d_cstages, b.poses, b.ax,   b.ay,   b.bx, b.by,
-             b.off,   p->d_crec, p->d_ccnt,  b.d,     b.edge, b.obst, b.grad, b.keys};
+// staged: from the boxes and records taken by psdf_batch_stage.
+hipError_t cull_enqueue(psdf_batch_plan* p, const CullArgs& a, bool staged, hipStream_t st) {
   if (p->n_segs > 0) {
-    if (p->mi_class == 4) cull_list_kernel<4><<<p->n_segs, kCullThreads, 0, st>>>(a);
-    else if (p->mi_class == 8) cull_list_kernel<8><<<p->n_segs, kCullThreads, 0, st>>>(a);
-    else cull_list_kernel<16><<<p->n_segs, kCullThreads, 0, st>>>(a);
+    const int n = p->n_segs;
+    if (staged) cull_list_kernel<4, true><<<n, kCullThreads, 0, st>>>(a);
+    else if (p->mi_class == 4) cull_list_kernel<4, false><<<n, kCullThreads, 0, st>>>(a);
+    else if (p->mi_class == 8) cull_list_kernel<8, false><<<n, kCullThreads, 0, st>>>(a);
+    else cull_list_kernel<16, false><<<n, kCullThreads, 0, st>>>(a);
   }
   const int S = p->total_stages;
   if (p->mi_class == 4) cull_stage_kernel<4><<<S, 64, 0, st>>>(a);
   else if (p->mi_class == 8) cull_stage_kernel<8><<<S, 64, 0, st>>>(a);
   else cull_stage_kernel<16><<<S, 64, 0, st>>>(a);
   return hipGetLastError();
+}
+
+CullArgs cull_args(psdf_batch_plan* p, const float* poses, const float* ax, const float* ay,
+                   const float* bx, const float* by, const int32_t* off, float* d, int32_t* edge,
+                   int32_t* obst, float* grad, uint64_t* keys) {
+  CullArgs a;
+  a.fps = p->d_fp; a.rows = p->d_frows; a.insts = p->d_inst; a.segs = p->d_segs;
+  a.stages = p->d_cstages;
+  a.poses = poses; a.ax = ax; a.ay = ay; a.bx = bx; a.by = by; a.off = off;
+  a.sbox = p->d_sbox; a.srec = p->d_srec; a.rec = p->d_crec; a.cnt = p->d_ccnt;
+  a.d = d; a.edge = edge; a.obst = obst; a.grad = grad; a.keys = keys;
+  return a;
 }
 
 int run(psdf_batch_plan* p, const float* poses, const float* ax, const float* ay,
@@ -500,7 +515,8 @@ int run(psdf_batch_plan* p, const float* poses, const float* ax, const float* ay
   auto enqueue = [&](hipStream_t st, bool timed) -> hipError_t {
     if (p->culled) {
       if (timed) timer_begin(st);
-      const hipError_t e = cull_enqueue(p, a, st);
+      const hipError_t e = cull_enqueue(
+          p, cull_args(p, poses, ax, ay, bx, by, off, d, edge, obst, grad, keys), false, st);
       if (timed) timer_end(st);
       return e;
     }
@@ -643,6 +659,18 @@ static int screened_run(psdf_batch_plan* p, bool bound, const float* theta, int3
                          "from (stage again, or psdf_batch_unstage)");
     circ = p->d_circ;
   }
+  if (bound && p->cull_ready && !stage_cand && !stage_cert && !cand_keys) {
+    // the same scheme with boxes for circles and lists that leave no stage
+    // uncertified: nothing to fall back from, two launches.  (On 64 x 50 x
+    // 16384 the circles' 512-entry lists leave some stages of most draws to
+    // the full evaluation, 77 us of fallback in a call of 85 to 132 us.)
+    timer_begin(stream);
+    const hipError_t e = cull_enqueue(
+        p, cull_args(p, poses, ax, ay, bx, by, off, d, edge, obst, grad, keys),
+        p->circ_staged, stream);
+    timer_end(stream);
+    return hip_status(e);
+  }
   ScreenArgs a;
   a.rows = circ ? p->d_rows : nullptr;
   a.fps = p->d_fp; a.insts = p->d_inst; a.stage_inst = p->d_stage_inst;
@@ -738,6 +766,14 @@ int psdf_batch_stage(psdf_batch_plan* p, const float* ax, const float* ay, const
       err = hipMalloc(&p->d_rows, p->sum_M * (size_t)(40 * p->mi_class + 16));
       if (err != hipSuccess) p->d_rows = nullptr;
     }
+    if (err == hipSuccess && p->cull_ready && !p->d_sbox) {
+      err = hipMalloc(&p->d_sbox, p->sum_M * sizeof(float4));
+      if (err != hipSuccess) p->d_sbox = nullptr;
+    }
+    if (err == hipSuccess && p->cull_ready && !p->d_srec) {
+      err = hipMalloc(&p->d_srec, p->sum_M * sizeof(CullRec));
+      if (err != hipSuccess) p->d_srec = nullptr;
+    }
     if (err != hipSuccess) return hip_status(err);
     const dim3 grid((p->max_M + 255) / 256, p->n_inst);
 #define PSDF_STAGE_BATCH(MI)                                                               \
@@ -747,6 +783,19 @@ int psdf_batch_stage(psdf_batch_plan* p, const float* ax, const float* ay, const
     else if (p->mi_class == 8) PSDF_STAGE_BATCH(8);
     else PSDF_STAGE_BATCH(16);
 #undef PSDF_STAGE_BATCH
+    if (p->cull_ready) {
+      const CullArgs ca = cull_args(p, nullptr, ax, ay, bx, by, off, nullptr, nullptr, nullptr,
+                                    nullptr, nullptr);
+      // a grid's second dimension holds 65535 segments
+      for (int s0 = 0; s0 < p->n_segs; s0 += 65535) {
+        CullArgs c = ca;
+        c.segs = ca.segs + s0;
+        const dim3 g(kSegObst / 256, std::min(65535, p->n_segs - s0));
+        if (p->mi_class == 4) cull_stage_edges_kernel<4><<<g, 256, 0, stream>>>(c, p->d_sbox, p->d_srec);
+        else if (p->mi_class == 8) cull_stage_edges_kernel<8><<<g, 256, 0, stream>>>(c, p->d_sbox, p->d_srec);
+        else cull_stage_edges_kernel<16><<<g, 256, 0, stream>>>(c, p->d_sbox, p->d_srec);
+      }
+    }
     err = hipGetLastError();
     if (err != hipSuccess) return hip_status(err);
   }
@@ -809,6 +858,8 @@ void psdf_batch_plan_destroy(psdf_batch_plan* p) {
   (void)hipFree(p->d_segs);
   (void)hipFree(p->d_cstages);
   (void)hipFree(p->d_crec);
+  (void)hipFree(p->d_sbox);
+  (void)hipFree(p->d_srec);
   (void)hipFree(p->d_ccnt);
   (void)hipSetDevice(cur);
   delete p;

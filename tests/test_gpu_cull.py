@@ -1,5 +1,6 @@
-"""The culled evaluation of a batch gives the full evaluation's outputs bit
-for bit: instances at the edges of the segments and list rounds, obstacles
+"""The culled evaluation of a batch, and the bound-threshold screened call
+that takes it (with and without staged boxes), give the full evaluation's
+outputs bit for bit: instances at the edges of the segments and list rounds, obstacles
 that no bound covers (open chains, stars, degenerate edges, non-finite and
 huge coordinates, invalid ranges), footprints and constants at the ends of
 their ranges, non-finite poses, graph replays with changed inputs."""
@@ -61,13 +62,18 @@ def _check(insts, mbar=None, params=None, change=None):
         if change is not None and round_:
             for x in (a, b):
                 change(x, round_)
-        got = [t.clone() for t in a.run()]
         want = [t.clone() for t in b.run()]
-        torch.cuda.synchronize()
-        for name, g, w in zip(("d", "edge", "obst", "grad", "keys"), got, want):
-            g, w = g.cpu().numpy(), w.cpu().numpy()
-            bad = np.flatnonzero((g.view(np.uint8) != w.view(np.uint8)).reshape(len(g), -1).any(1))
-            assert len(bad) == 0, (round_, name, bad[:5], g[bad[:5]], w[bad[:5]])
+        calls = [("culled", a.run)]
+        if max(len(i.obst_off) - 1 for i in insts) <= 16384:   # what screening takes
+            calls += [("bound", a.unstage().screened_bound),
+                      ("bound, staged", lambda: a.stage().screened_bound())]
+        for form, call in calls:
+            got = [t.clone() for t in call()]
+            torch.cuda.synchronize()
+            for name, g, w in zip(("d", "edge", "obst", "grad", "keys"), got, want):
+                g, w = g.cpu().numpy(), w.cpu().numpy()
+                bad = np.flatnonzero((g.view(np.uint8) != w.view(np.uint8)).reshape(len(g), -1).any(1))
+                assert len(bad) == 0, (round_, form, name, bad[:5], g[bad[:5]], w[bad[:5]])
     a.close()
     b.close()
     return want
