@@ -114,12 +114,6 @@ struct CullArgs {
   uint64_t* keys;
 };
 
-// Four consecutive floats at any float address: global loads of several
-// dwords need dword alignment only.
-struct __attribute__((packed, aligned(4))) Float4u {
-  float v[4];
-};
-
 // Running facts of an obstacle, edge by edge.
 struct CullAcc {
   float lox, loy, hix, hiy;

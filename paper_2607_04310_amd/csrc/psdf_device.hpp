@@ -73,6 +73,12 @@ struct FpConst {
   float rmin, cull_tau, sd_floor, cull_rel;
 };
 
+// Four consecutive floats at any float address (global loads of several
+// dwords need dword alignment only).
+struct __attribute__((packed, aligned(4))) Float4u {
+  float v[4];
+};
+
 // One obstacle in registers, with its pose-independent constants.  Slots
 // j >= mi repeat edge mi - 1, which leaves every min / max / any-reduction
 // unchanged; only the soft-min sum masks them.
