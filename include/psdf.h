@@ -50,6 +50,9 @@
  *    point-segment pool distance (lowest index on ties), grad[3s..3s+2] =
  *    dphi/d(x, y, theta).  An empty edge set gives d = +inf, obst = edge = -1,
  *    grad = 0; a non-finite pose gives d = NaN, obst = edge = -1, grad = NaN.
+ *  - Problems of many (stage, obstacle) pairs are evaluated culled: a bound on
+ *    every pair leaves a few obstacles per stage that are evaluated.  The
+ *    outputs are those of the full evaluation bit for bit, for every input.
  *  - keys (device uint64[N]) receives the winner of each stage:
  *    (orderable(sd) << 32) | obstacle, where orderable maps floats to
  *    unsigned integers in the same order (NaN lowest).  psdf_bwd consumes it.
@@ -509,8 +512,8 @@ int psdf_screen_labels(const psdf_batch_plan* plan, const float* poses, const fl
 
 /* Launch shape of the per-stage minimum kernel: blk obstacles per work-group
  * (64 or 256) and sb stages per work-group (1..64).  A non-zero blk overrides
- * every later call in the process (for sweeps); blk = 0 restores the
- * automatic choice (a heuristic on N and M).  Results do not depend on the
+ * every later call in the process (for sweeps), which then evaluates every
+ * pair; blk = 0 restores the automatic choice (a heuristic on the sizes).  Results do not depend on the
  * shape (the minimum and its tie rule are exact). */
 int psdf_set_launch_shape(int32_t blk, int32_t sb);
 

@@ -428,22 +428,153 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
 
 constexpr int kCullRounds = 4;    // list entries kept in registers: 64 x this
 constexpr int kCullFlat = 4096;   // list entries found through the start bits
+
+// Listed obstacles as the evaluation reads them: the box, the meta word and
+// edge j (at most the obstacle's last; act: without it, nothing) of a slot,
+// from its record's points or else from the edge arrays.
+template <int MI>
+struct RecSource {
+  const CullArgs& A;
+  const CullRec* rec;
+  __device__ __forceinline__ float4 box(int sl) const { return rec[sl].box; }
+  __device__ __forceinline__ int4 meta(int sl) const { return rec[sl].meta; }
+  __device__ __forceinline__ void edge(int sl, const int4& m, int j, bool act, float& ax,
+                                       float& ay, float& bx, float& by) const {
+    if (!act) return;
+    const int e = min(j, m.z - 1);
+    if (MI == 4 && (m.w & kRecPoints)) {
+      const float2* p = reinterpret_cast<const float2*>(rec[sl].pts);
+      const int n = m.z == 1 ? 1 : (e + 1 < m.z ? e + 1 : 0);
+      const float2 a = p[e], b = p[n];
+      ax = a.x; ay = a.y; bx = b.x; by = b.y;
+    } else {
+      ax = A.ax[m.y + e]; ay = A.ay[m.y + e]; bx = A.bx[m.y + e]; by = A.by[m.y + e];
+    }
+  }
+};
+
+// The least key so far, and its slot and meta word.
+struct CullBest {
+  uint64_t key;
+  int slot;
+  int4 meta;
+  // the least sd: NaN once an invalid obstacle is in
+  __device__ __forceinline__ float least() const {
+    return key == kEmptyKey ? __builtin_huge_valf() : from_orderable((uint32_t)(key >> 32));
+  }
+};
+
+// Squared distance from (px, py) to a box; -1 for an irregular obstacle, or
+// with ok false (last as unsigned bits, within every bar).
+__device__ __forceinline__ float cull_dist2(const float4& b, float px, float py, bool ok) {
+  const float gx = fmaxf(fmaxf(b.x - px, px - b.z), 0.f);
+  const float gy = fmaxf(fmaxf(b.y - py, py - b.w), 0.f);
+  return (b.x == b.x && ok) ? fmaf(gx, gx, gy * gy) : -1.f;
+}
+
+// The bar of a least sd (a NaN: of tau) as a squared distance to a box.
+__device__ __forceinline__ float cull_bar2(const FpConst& F, float sd) {
+  const float b = (fmaxf(sd, F.cull_tau) + F.rmax + kCullGamma) * (1.0f + 2.0f * F.cull_rel);
+  return b * b;
+}
+
+// Past the nearest box, what is evaluated with it, in footprint radii: far
+// enough that the bar seldom asks for a second round, near enough that one
+// round of groups holds it.
+constexpr float kCullReach = 0.5f;
+
+// What to evaluate first, least being the smallest squared distance: what
+// every bar includes (T >= tau) or, where nothing is that near, the nearest
+// and those not much further (irregular ones in either case); their least sd
+// sets the bar, which seldom leaves more.
+__device__ __forceinline__ float cull_first(const FpConst& F, float least) {
+  const float first = cull_bar2(F, F.cull_tau);
+  if (!(least > first)) return first;
+  const float b = fmaf(kCullReach, F.rmax, sqrtf(least) * (1.0f + 1e-5f));
+  return b * b;
+}
+
 constexpr int kCullCand = 192;    // candidates held between evaluations (three per lane)
 
-// Edge j (at most its last one) of the listed obstacle of record r, meta m:
-// from its points, else from the edge arrays (act; without it, nothing).
-template <int MI>
-__device__ __forceinline__ void cull_edge(const CullArgs& A, const CullRec& r, const int4& m, int j,
-                                          bool act, float& ax, float& ay, float& bx, float& by) {
-  if (!act) return;
-  const int e = min(j, m.z - 1);
-  if (MI == 4 && (m.w & kRecPoints)) {
-    const float2* p = reinterpret_cast<const float2*>(r.pts);
-    const int n = m.z == 1 ? 1 : (e + 1 < m.z ? e + 1 : 0);
-    const float2 a = p[e], b = p[n];
-    ax = a.x; ay = a.y; bx = b.x; by = b.y;
-  } else {
-    ax = A.ax[m.y + e]; ay = A.ay[m.y + e]; bx = A.bx[m.y + e]; by = A.by[m.y + e];
+// Evaluates the n candidates cand[0 .. n) (slots of src), a group of MI lanes
+// each, and folds them into best.  More than one round of them is cut down by
+// a second bound, the robot's axes against the box: on axis l the overlap is
+// at most o_l = cn_l - min over the box of (W - p) . n_l.  Sets that overlap
+// are no deeper than their overlap on any axis (and the soft minimum is below
+// the minimum); separated ones are at least -o_l apart; ones within eps_sat
+// have sd >= 0.  So sd >= -min_l o_l - eps_sat =: lb.  The lowest go first,
+// then those whose lb does not exceed the least sd so far (a crowd of 50 to
+// 130 overlapping boxes, or the map around a long footprint, leaves one or two
+// rounds).  One whole wave; cand may be written just before by the wave.
+template <int MI, class Src>
+__device__ __forceinline__ void cull_evaluate(const FpConst& F, const FpSlot* fs, float* dls,
+                                              const int* cand, uint8_t* pick, int n,
+                                              const Src& src, float px, float py,
+                                              CullBest& best) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t below = (1ull << lane) - 1ull;
+  wave_sync();
+  float lb[kCullCand / 64];
+  const bool cut = n > 64 / MI;
+  float from = __builtin_nanf(""), to = __builtin_huge_valf();
+#pragma unroll
+  for (int h = 0; h < kCullCand / 64; ++h) {
+    lb[h] = 0.f;
+    if (cut && lane + 64 * h < n) {
+      const float4 b = src.box(cand[lane + 64 * h]);
+      const float cx = 0.5f * (b.x + b.z) - px, cy = 0.5f * (b.y + b.w) - py;
+      const float hx = 0.5f * (b.z - b.x), hy = 0.5f * (b.w - b.y);
+      float depth = __builtin_huge_valf();
+      for (int l = 0; l < F.m; ++l) {
+        const float nx = fs[l].r.w, ny = -fs[l].r.z;
+        const float w = fmaf(cx, nx, fmaf(cy, ny, -fmaf(hx, fabsf(nx), hy * fabsf(ny))));
+        depth = fminf(depth, fs[l].cn - w);
+      }
+      const float low = -depth - fmaf(F.cull_rel, F.rmax + 2.0f * fabsf(depth), F.eps_sat + 1e-4f);
+      lb[h] = b.x == b.x ? low : -__builtin_huge_valf();   // irregular: always
+    }
+  }
+  if (cut) {
+    float x = lb[0];
+#pragma unroll
+    for (int h = 1; h < kCullCand / 64; ++h) x = fminf(x, lb[h]);
+    to = fminf(fw_min_f32(x) + 0.1f, best.least());
+  }
+  for (int step = 0; step < 2; ++step) {
+    int np = 0;
+#pragma unroll
+    for (int h = 0; h < kCullCand / 64; ++h) {
+      const bool t = lane + 64 * h < n && !(lb[h] > to) && !(lb[h] <= from);
+      const uint64_t m = __ballot(t);
+      if (t) pick[np + (int)__popcll(m & below)] = (uint8_t)(lane + 64 * h);
+      np += (int)__popcll(m);
+    }
+    wave_sync();
+    for (int c0 = 0; c0 < np; c0 += 64 / MI) {
+      const int c = c0 + lane / MI;
+      const bool act = c < np;
+      const int sl = act ? cand[pick[c]] : 0;
+      const int4 m = act ? src.meta(sl) : make_int4(0, 0, 1, kRecBad);
+      const bool bad = (m.w & kRecBad) != 0;
+      float ax = 0.f, ay = 0.f, bx = 0.f, by = 0.f;
+      src.edge(sl, m, lane & (MI - 1), !bad, ax, ay, bx, by);
+      const float sd = group_sd<MI>(F, fs, dls, ax, ay, bx, by, m.z, (m.w & kRecClosed) != 0, !bad,
+                                    px, py);
+      const uint64_t k =
+          act ? ((uint64_t)(bad ? 0u : orderable(sd)) << 32) | (uint32_t)m.x : kEmptyKey;
+      const uint64_t kw = fw_min_u64(k);
+      if (kw < best.key) {
+        best.key = kw;
+        const int f = __ffsll((unsigned long long)__ballot(k == kw)) - 1;
+        best.slot = (int)lane_u32((uint32_t)sl, f);
+        best.meta = make_int4((int)(uint32_t)kw, (int)lane_u32((uint32_t)m.y, f),
+                              (int)lane_u32((uint32_t)m.z, f), (int)lane_u32((uint32_t)m.w, f));
+      }
+    }
+    wave_sync();
+    if (!cut || best.least() <= to) break;
+    from = to;
+    to = best.least();
   }
 }
 
@@ -483,14 +614,8 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
   if (lane < kMaxFp) fr = A.rows[R.inst * kMaxFp + lane];
   starts[lane] = starts[64 + lane] = 0u;
 
-  // squared distance from the stage position to a box; -1 for an irregular
-  // obstacle (last in the seed's order, within every bar)
   const bool within = fmaxf(fabsf(px), fabsf(py)) < kCullMax;
-  auto dist2 = [&](const float4& b) {
-    const float gx = fmaxf(fmaxf(b.x - px, px - b.z), 0.f);
-    const float gy = fmaxf(fmaxf(b.y - py, py - b.w), 0.f);
-    return (b.x == b.x && within) ? fmaf(gx, gx, gy * gy) : -1.f;
-  };
+  auto dist2 = [&](const float4& b) { return cull_dist2(b, px, py, within); };
 
   // ---- the list as one
   static_assert(kCullFlat == 64 * 64, "two words of starts per lane");
@@ -604,9 +729,7 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
   const uint32_t kmin = fw_min_u32(kb);
   wave_sync();   // fs and fl are written
 
-  uint64_t key = kEmptyKey;
-  int wsl = 0;                          // the winner's list slot and
-  int4 wm = make_int4(0, 0, 0, 0);      // edge range (y, z) and flags (w)
+  CullBest best{kEmptyKey, 0, make_int4(0, 0, 0, 0)};
   const bool pose_ok = isfinite(px) && isfinite(py) && isfinite(cs) && isfinite(sn);
   if (!pose_ok) {
     // every obstacle's sd is NaN: the first one that has an edge entry wins
@@ -615,27 +738,12 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
       const int o = o0 + lane;
       const uint64_t m = __ballot(o < R.M && off[o + 1] != off[o]);
       if (m) {
-        key = (uint64_t)(uint32_t)(o0 + __ffsll((unsigned long long)m) - 1);
+        best.key = (uint64_t)(uint32_t)(o0 + __ffsll((unsigned long long)m) - 1);
         break;
       }
     }
   } else if (kmin != 0xffffffffu) {
-    auto least_sd = [&]() {   // a NaN once an invalid obstacle is in
-      return key == kEmptyKey ? __builtin_huge_valf() : from_orderable((uint32_t)(key >> 32));
-    };
-    auto bar2 = [&](float t) {
-      const float b = (t + F.rmax + kCullGamma) * (1.0f + 2.0f * F.cull_rel);
-      return b * b;
-    };
-    // First what every bar includes (T >= tau) or, where nothing is that
-    // near, the nearest and those not much further (irregular ones in either
-    // case); their least sd sets the bar, which seldom leaves more.
-    const float least = __uint_as_float(kmin);
-    float first = bar2(F.cull_tau);
-    if (least > first) {
-      const float b = fmaf(0.25f, F.rmax, sqrtf(least) * (1.0f + 1e-5f));
-      first = b * b;
-    }
+    const float first = cull_first(F, __uint_as_float(kmin));
     float lo = -2.f, hi = first;   // lo < D^2 <= hi
     for (int pass = 0; pass < 2; ++pass) {
       int n = 0;
@@ -664,91 +772,182 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
             take(sl, x, live);
             return n <= kCullCand - 64;
           });
-        wave_sync();
-        // More than one round of candidates is cut down by a second bound:
-        // the depth of an overlap is at most the overlap on any axis (the
-        // soft minimum is below the minimum), and on robot axis l that is at
-        // most cn_l - min over the box of (W - p) . n_l; so
-        // sd >= min(0, -that) =: lb.  The lowest go first, then those whose
-        // lb does not exceed the least sd so far (a crowd of 50 to 130
-        // overlapping boxes leaves one or two rounds).
-        float lb[kCullCand / 64];
-        const bool cut = n > 64 / MI;
-        float from = __builtin_nanf(""), to = __builtin_huge_valf();
-#pragma unroll
-        for (int h = 0; h < kCullCand / 64; ++h) {
-          lb[h] = 0.f;
-          if (cut && lane + 64 * h < n) {
-            const float4 b = rec[cand[lane + 64 * h]].box;
-            const float cx = 0.5f * (b.x + b.z) - px, cy = 0.5f * (b.y + b.w) - py;
-            const float hx = 0.5f * (b.z - b.x), hy = 0.5f * (b.w - b.y);
-            float depth = __builtin_huge_valf();
-            for (int l = 0; l < F.m; ++l) {
-              const float nx = fs[l].r.w, ny = -fs[l].r.z;
-              const float w = fmaf(cx, nx, fmaf(cy, ny, -fmaf(hx, fabsf(nx), hy * fabsf(ny))));
-              depth = fminf(depth, fs[l].cn - w);
-            }
-            const float low = -fmaxf(depth, 0.f) - fmaf(F.cull_rel, F.rmax, 1e-4f);
-            lb[h] = b.x == b.x ? low : -__builtin_huge_valf();   // irregular: always
-          }
-        }
-        if (cut) {
-          float x = lb[0];
-#pragma unroll
-          for (int h = 1; h < kCullCand / 64; ++h) x = fminf(x, lb[h]);
-          to = fminf(fw_min_f32(x) + 0.1f, least_sd());
-        }
-        for (int step = 0; step < 2; ++step) {
-          int np = 0;
-#pragma unroll
-          for (int h = 0; h < kCullCand / 64; ++h) {
-            const bool t = lane + 64 * h < n && !(lb[h] > to) && !(lb[h] <= from);
-            const uint64_t m = __ballot(t);
-            if (t) pick[np + (int)__popcll(m & below)] = (uint8_t)(lane + 64 * h);
-            np += (int)__popcll(m);
-          }
-          wave_sync();
-          for (int c0 = 0; c0 < np; c0 += 64 / MI) {
-            const int c = c0 + lane / MI;
-            const bool act = c < np;
-            const int sl = act ? cand[pick[c]] : 0;
-            const int4 m = act ? rec[sl].meta : make_int4(0, 0, 1, kRecBad);
-            const bool bad = (m.w & kRecBad) != 0;
-            float ax = 0.f, ay = 0.f, bx = 0.f, by = 0.f;
-            cull_edge<MI>(A, rec[sl], m, lane & (MI - 1), !bad, ax, ay, bx, by);
-            const float sd = group_sd<MI>(F, fs, dls, ax, ay, bx, by, m.z,
-                                          (m.w & kRecClosed) != 0, !bad, px, py);
-            const uint64_t k =
-                act ? ((uint64_t)(bad ? 0u : orderable(sd)) << 32) | (uint32_t)m.x : kEmptyKey;
-            const uint64_t kw = fw_min_u64(k);
-            if (kw < key) {
-              key = kw;
-              const int f = __ffsll((unsigned long long)__ballot(k == kw)) - 1;
-              wsl = (int)lane_u32((uint32_t)sl, f);
-              wm = make_int4(m.x, (int)lane_u32((uint32_t)m.y, f), (int)lane_u32((uint32_t)m.z, f),
-                             (int)lane_u32((uint32_t)m.w, f));
-            }
-          }
-          wave_sync();
-          if (!cut || least_sd() <= to) break;
-          from = to;
-          to = least_sd();
-        }
+        cull_evaluate<MI>(F, fs, dls, cand, pick, n, RecSource<MI>{A, rec}, px, py, best);
         n = 0;
       } while (rest);
-      const float bar = bar2(fmaxf(least_sd(), F.cull_tau));   // a NaN: the bar of tau
+      const float bar = cull_bar2(F, best.least());
       if (bar <= first) break;
       lo = first;
       hi = bar;
     }
   }
-  const bool valid = key != kEmptyKey && (key >> 32) != 0 && wm.z >= 1 && wm.z <= kMaxObst;
+  const int4 wm = best.meta;
+  const bool valid =
+      best.key != kEmptyKey && (best.key >> 32) != 0 && wm.z >= 1 && wm.z <= kMaxObst;
   write_stage<MI>(F, fl, wl,
-              [&](int j, float& ax, float& ay, float& bx, float& by) {
-                cull_edge<MI>(A, rec[wsl], wm, j, true, ax, ay, bx, by);
-              },
-              key, valid, wm.y, wm.z, R.edge_off, cs, sn, px, py, g, A.keys, A.d, A.edge, A.obst,
-              A.grad);
+                  [&](int j, float& ax, float& ay, float& bx, float& by) {
+                    RecSource<MI>{A, rec}.edge(best.slot, wm, j, true, ax, ay, bx, by);
+                  },
+                  best.key, valid, wm.y, wm.z, R.edge_off, cs, sn, px, py, g, A.keys, A.d, A.edge,
+                  A.obst, A.grad);
+}
+
+// ------------------------------------------------------------------ plain calls
+
+// Culled form of the plain path's per-stage minimum (psdf_kernels.hpp): the
+// same partials for segments of kSegObst obstacles, one work-group per
+// (segment, block of SB stages).  The work-group derives the segment's boxes
+// once, in LDS; then each wave takes every fourth stage: the distances to
+// the boxes, and exact evaluations of the segment's few obstacles within the
+// bar that the nearest sets.  The segment's minimum is exact, so the
+// epilogue reduces these partials as it does the full kernel's.  Bound by
+// latency (12 to 14 us) up to about a million pairs; one pose against 1 M
+// rectangles reads 68 MB in 20 us (full form 24 us, its evaluations of every
+// obstacle), 50 x 65536 takes 17 us (54 us).
+struct SegSource {
+  const float* ax;
+  const float* ay;
+  const float* bx;
+  const float* by;
+  const float4* lbox;
+  const int* le0;
+  const uint16_t* lmeta;   // edge count << 4 | flags
+  int o0;
+  __device__ __forceinline__ float4 box(int sl) const { return lbox[sl]; }
+  __device__ __forceinline__ int4 meta(int sl) const {
+    const int m = lmeta[sl];
+    return make_int4(o0 + sl, le0[sl], m >> 4, m & 15);
+  }
+  __device__ __forceinline__ void edge(int, const int4& m, int j, bool act, float& a0, float& a1,
+                                       float& b0, float& b1) const {
+    if (!act) return;
+    const int e = m.y + min(j, m.z - 1);
+    a0 = ax[e]; a1 = ay[e]; b0 = bx[e]; b1 = by[e];
+  }
+};
+
+__device__ __forceinline__ FpSlot cull_slot(const FpConst& F, int l, float c, float s) {
+  return FpSlot{rotated_slot(F, l, c, s), F.cu[l], F.cn[l], F.len[l], F.oa[l], F.ob[l]};
+}
+
+template <int MI>
+__global__ __launch_bounds__(kCullThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void cull_main_kernel(
+    FpConst F, const float* __restrict__ poses, int N, int SB, const float* __restrict__ ax,
+    const float* __restrict__ ay, const float* __restrict__ bx, const float* __restrict__ by,
+    const int* __restrict__ off, int E, int M, ulonglong2* __restrict__ partial) {
+  constexpr int kWaves4 = kCullThreads / 64, kBoxRounds = kSegObst / 64;
+  __shared__ float4 lbox[kSegObst];
+  __shared__ int le0[kSegObst];
+  __shared__ uint16_t lmeta[kSegObst];
+  __shared__ FpSlot fss[kWaves4][kMaxFp];
+  __shared__ float dlss[kWaves4][64 / MI * kMaxFp];
+  __shared__ int cands[kWaves4][kCullCand];
+  __shared__ uint8_t picks[kWaves4][kCullCand];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int o0 = blockIdx.x * kSegObst, no = min(kSegObst, M - o0);
+  const int s0 = blockIdx.y * SB, ns = min(SB, N - s0);
+  FpSlot* fs = fss[w];
+  float px = 0.f, py = 0.f, sn = 0.f, cs = 0.f;
+  // the wave's first pose, in flight with the edges
+  float th = 0.f;
+  if (w < ns) {
+    const float* p = poses + 3 * (s0 + w);
+    px = p[0]; py = p[1]; th = p[2];
+  }
+  {
+    CullArgs A{};
+    A.ax = ax; A.ay = ay; A.bx = bx; A.by = by;
+    BatchInst in{};
+    CullLoad<MI> ld[kCullPer];
+#pragma unroll
+    for (int q = 0; q < kCullPer; ++q) {
+      const int k = tid + kCullThreads * q;
+      ld[q].e0 = ld[q].mi = 0;
+      if (k < no) {
+        ld[q].e0 = off[o0 + k];
+        ld[q].mi = off[o0 + k + 1] - ld[q].e0;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kCullPer; ++q) ld[q].load(A, in, E);
+    if (w < ns) {
+      sincosf(th, &sn, &cs);
+      if (lane < F.m) fs[lane] = cull_slot(F, lane, cs, sn);
+    }
+#pragma unroll
+    for (int q = 0; q < kCullPer; ++q) {
+      const int k = tid + kCullThreads * q;
+      float4 box;
+      int flags;
+      ld[q].finish(A, F, box, flags);
+      if (ld[q].mi == 0) box.x = kEmptyBox;
+      lbox[k] = box;
+      le0[k] = ld[q].e0;
+      lmeta[k] = (uint16_t)((ld[q].mi & 31) << 4 | (flags & 15));
+    }
+  }
+  __syncthreads();
+  const SegSource src{ax, ay, bx, by, lbox, le0, lmeta, o0};
+  int* cand = cands[w];
+  const uint64_t below = (1ull << lane) - 1ull;
+  for (int t = w; t < ns; t += kWaves4) {
+    const int s = s0 + t;
+    if (t != w) {
+      const float* p = poses + 3 * s;
+      px = p[0]; py = p[1];
+      sincosf(p[2], &sn, &cs);
+      if (lane < F.m) fs[lane] = cull_slot(F, lane, cs, sn);
+    }
+    const bool within = fmaxf(fabsf(px), fabsf(py)) < kCullMax;
+    const bool pose_ok = isfinite(px) && isfinite(py) && isfinite(cs) && isfinite(sn);
+    CullBest best{kEmptyKey, 0, make_int4(0, 0, 0, 0)};
+    float d2[kBoxRounds];   // NaN: no edge
+    uint32_t kb = 0xffffffffu;
+#pragma unroll
+    for (int r = 0; r < kBoxRounds; ++r) {
+      const float4 b = lbox[64 * r + lane];
+      const bool empty = b.x == kEmptyBox;
+      d2[r] = empty ? __builtin_nanf("") : cull_dist2(b, px, py, within);
+      kb = min(kb, empty ? 0xffffffffu : __float_as_uint(d2[r]));
+    }
+    const uint32_t kmin = fw_min_u32(kb);
+    if (!pose_ok) {
+      // every obstacle's sd is NaN: the segment's first one with an edge wins
+      for (int k0 = 0; k0 < no && best.key == kEmptyKey; k0 += 64) {
+        const uint64_t m = __ballot(lbox[k0 + lane].x != kEmptyBox);
+        if (m) best.key = (uint64_t)(uint32_t)(o0 + k0 + __ffsll((unsigned long long)m) - 1);
+      }
+    } else if (kmin != 0xffffffffu) {
+      const float first = cull_first(F, __uint_as_float(kmin));
+      float lo = -2.f, hi = first;   // lo < D^2 <= hi
+      for (int pass = 0; pass < 2; ++pass) {
+        int r0 = 0;   // rounds before it are done
+        do {
+          int n = 0;
+#pragma unroll
+          for (int r = 0; r < kBoxRounds; ++r) {
+            const bool t2 = d2[r] > lo && !(d2[r] > hi);
+            const uint64_t m = __ballot(t2);
+            const int c = (int)__popcll(m);
+            if (r < r0 || n + c > kCullCand) continue;
+            if (r != r0) continue;
+            if (t2) cand[n + (int)__popcll(m & below)] = 64 * r + lane;
+            n += c;
+            ++r0;
+          }
+          if (n > 0) cull_evaluate<MI>(F, fs, dlss[w], cand, picks[w], n, src, px, py, best);
+        } while (r0 < kBoxRounds);
+        const float bar = cull_bar2(F, best.least());
+        if (bar <= first) break;
+        lo = first;
+        hi = bar;
+      }
+    }
+    if (lane == 0)
+      partial[(size_t)s * gridDim.x + blockIdx.x] =
+          make_ulonglong2(best.key, ((uint64_t)(uint32_t)best.meta.y << 32) | (uint32_t)best.meta.z);
+  }
 }
 
 }  // namespace psdf

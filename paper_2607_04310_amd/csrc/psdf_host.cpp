@@ -1,6 +1,7 @@
 // Host-side validation, footprint preparation and launch heuristics.
 #include "psdf_host.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -15,6 +16,19 @@
 namespace psdf {
 
 namespace {
+// Whether the culled form of the per-stage minimum is the faster one.  It has
+// a floor of 12 to 14 us (its chain of loads, a barrier and one or two
+// evaluations; 22 us for the wider edge classes, whose obstacles are read edge
+// by edge), where the full form costs about N M m (m robot slots, half an
+// edge class).  Whole calls, full / culled: m = 6, four edges: N M = 0.82 M
+// 21.1 / 19.0 us, 0.41 M 16.3 / 19.5, 1 x 1000003 31.2 / 27.2, 3.3 M 57 / 22;
+// m = 4: 0.82 M 18.2 / 18.8, 1.3 M 24.0 / 19.9; eight edges: 0.41 M
+// 32 / 28, 0.33 M 26 / 28, 3.3 M 98 / 38.
+bool cull_plain(int m, int mbar, int N, int M) {
+  const double cost = (double)N * M * (m <= 8 ? m : kMaxFp) * (obst_class(mbar) == 4 ? 1 : 2);
+  return cost >= 4.6e6;
+}
+
 thread_local std::string g_err;
 }
 
@@ -166,7 +180,15 @@ int check_edges(const psdf_edges* in, psdf_edges* out) {
   return PSDF_OK;
 }
 
-LaunchShape choose_shape(int N, int M) {
+LaunchShape choose_shape(int m, int mbar, int N, int M) {
+  if (cull_plain(m, mbar, N, M)) {
+    // every stage block reads and bounds the segment's edges anew, so as few
+    // blocks as cover the chip: four waves (stages) at a time
+    const long segs = (M + kCullBlk - 1) / kCullBlk;
+    const long want = (1024 + segs - 1) / segs;      // stage blocks
+    const long sb = ((N + want - 1) / want + 3) / 4 * 4;
+    return LaunchShape{kCullBlk, (int)std::min<long>(sb, kMaxStageBlock)};
+  }
   // Enough waves to cover 1024 SIMDs about four deep, then as many stages per
   // work-group as that allows (each reuse amortises the obstacle load).
   const int waves = (M + 63) / 64;
@@ -185,11 +207,9 @@ LaunchShape g_override{0, 0};
 }  // namespace
 
 LaunchShape tuned_shape(int m, int mbar, int N, int M) {
-  (void)m;
-  (void)mbar;
   std::lock_guard<std::mutex> lk(g_shape_mu);
   if (g_override.blk) return g_override;
-  return choose_shape(N, M);
+  return choose_shape(m, mbar, N, M);
 }
 
 namespace {

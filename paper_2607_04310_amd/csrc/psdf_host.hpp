@@ -10,8 +10,11 @@ namespace psdf {
 
 constexpr int kMaxStageBlock = 64;   // stages per work-group in the plain kernel
 
+// Obstacles per work-group of the plain path's culled form.
+constexpr int kCullBlk = 1024;
+
 struct LaunchShape {
-  int blk;  // lanes (obstacles) per work-group: 64 or 256
+  int blk;  // obstacles per work-group: 64 or 256 (one per lane), or kCullBlk (culled)
   int sb;   // stages per work-group, 1..kMaxStageBlock
 };
 
@@ -38,8 +41,9 @@ void timer_end(hipStream_t st);
 // off or full.
 bool timer_kernel_events(hipEvent_t* start, hipEvent_t* stop);
 
-// Default launch shape of the plain kernel for N stages and M obstacles.
-LaunchShape choose_shape(int N, int M);
+// Default launch shape of the per-stage minimum for N stages and M obstacles
+// of at most mbar edges, and a footprint of m vertices.
+LaunchShape choose_shape(int m, int mbar, int N, int M);
 
 // Launch shape for a problem: an explicit override (psdf_set_launch_shape),
 // else choose_shape.

@@ -2,7 +2,8 @@
 //
 // Kernel sequence of one call (all on the caller's stream, no host sync):
 //   main_kernel      per-work-group partial minimum of (sd, obstacle) per stage
-//                    (psdf_kernels.hpp)
+//                    (psdf_kernels.hpp; many pairs: cull_main_kernel, which
+//                    evaluates only what a bound leaves, psdf_cull.hpp)
 //   epilogue_kernel  one wave per stage: reduce the partial keys, recompute the
 //                    winning obstacle with the wave-parallel adjoint
 //                    (psdf_winner.hpp), write keys, d, edge, obst, gradient
@@ -15,6 +16,7 @@
 #include <vector>
 
 #include "psdf.h"
+#include "psdf_cull.hpp"
 #include "psdf_kernels.hpp"
 #include "psdf_winner.hpp"
 
@@ -328,13 +330,34 @@ bool small_path(const psdf_edges& e) {
 }
 
 
+// The per-stage minimum in the form that the shape names; ev0 / ev1 (may be
+// null) are recorded by the dispatch at its start and end.  The culled form
+// reads the edges, with or without a staged table.
+static hipError_t launch_stage_min(const FpConst& F, const float* poses, int N,
+                                   const psdf_edges& e, uint64_t* partial, const LaunchShape& ls,
+                                   hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  static_assert(kCullBlk == kSegObst, "one work-group per segment");
+  const int cls = obst_class(e.mbar);
+  if (ls.blk != kCullBlk)
+    return PSDF_BY_MF(launch_main_mf, cls, ls, F, poses, N, e, partial, st, ev0, ev1);
+  const dim3 grid((e.M + kSegObst - 1) / kSegObst, (N + ls.sb - 1) / ls.sb);
+  ulonglong2* pk = reinterpret_cast<ulonglong2*>(partial);
+#define PSDF_CULL(MI)                                                                            \
+  hipExtLaunchKernelGGL(cull_main_kernel<MI>, grid, dim3(kCullThreads), 0, st, ev0, ev1, 0, F,   \
+                        poses, N, ls.sb, e.ax, e.ay, e.bx, e.by, e.obst_off, e.E, e.M, pk)
+  if (cls == 4) PSDF_CULL(4);
+  else if (cls == 8) PSDF_CULL(8);
+  else PSDF_CULL(16);
+#undef PSDF_CULL
+  return hipGetLastError();
+}
+
 hipError_t launch_plain(const FpConst& F, const float* poses, int N, const psdf_edges& e,
                         uint64_t* partial, const LaunchShape& ls, hipStream_t st) {
   if (e.M == 0) return hipSuccess;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   if (!timer_kernel_events(&ev0, &ev1)) ev0 = ev1 = nullptr;
-  return PSDF_BY_MF(launch_main_mf, obst_class(e.mbar), ls, F, poses, N, e, partial, st, ev0,
-                    ev1);
+  return launch_stage_min(F, poses, N, e, partial, ls, st, ev0, ev1);
 }
 
 hipError_t launch_epilogue(const FpConst& F, const float* poses, int N, const psdf_edges& e,
@@ -596,8 +619,7 @@ int psdf_time_stage_min(const float* footprint, int32_t m, const float* poses, i
   hipError_t err = hipSuccess;
   for (size_t k = 0; k < ev.size() && err == hipSuccess; ++k) err = hipEventCreate(&ev[k]);
   for (int r = 0; r < reps && err == hipSuccess; ++r)
-    err = PSDF_BY_MF(launch_main_mf, obst_class(e.mbar), ls, F, poses, N, e, partial, stream,
-                     ev[2 * r], ev[2 * r + 1]);
+    err = launch_stage_min(F, poses, N, e, partial, ls, stream, ev[2 * r], ev[2 * r + 1]);
   if (err == hipSuccess) err = hipEventSynchronize(ev.back());
   double total = 0.0;
   for (int r = 0; r < reps && err == hipSuccess; ++r) {

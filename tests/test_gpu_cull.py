@@ -134,6 +134,17 @@ def test_obstacles_without_a_bound(case):
     _check(insts, params=params)
 
 
+def test_long_footprint_in_a_dense_map():
+    """Hundreds of obstacles within the footprint's radius, few near its sides;
+    with a large eps_sat sets apart by less than it count as touching."""
+    from paper_2607_04310_amd import api
+    rng = np.random.default_rng(6)
+    car = inputs.rect_footprint(4.5, 1.8)
+    for params in (None, api.Params(eps_sat=0.3), api.hard_min()):
+        insts = [_big(rng, car), _inst(rng, car, 60, 4000, 8.0), _inst(rng, car, 20, 9000, 60.0)]
+        _check(insts, params=params)
+
+
 @pytest.mark.parametrize("bad", [np.nan, np.inf])
 def test_non_finite_inputs_and_ranges(bad):
     rng = np.random.default_rng(8)
@@ -160,3 +171,74 @@ def test_replays_see_changed_inputs():
         b.poses[:, 2] -= 0.2
         b.ax[::2] = torch.roll(b.ax, 8)[::2]          # breaks closed boundaries, moves corners
     _check(insts, change=change)
+
+
+def _plain_check(inst, mbar=4, params=None):
+    """psdf_grad, psdf_eval and psdf_constraints by themselves (culled at these
+    sizes) against the same calls under an explicit launch shape (full)."""
+    import torch
+    from paper_2607_04310_amd import api
+    es = api.EdgeSet(inst.edges, inst.obst_off, mbar)
+    es.M = len(inst.obst_off) - 1
+    poses = torch.tensor(inst.poses, device="cuda")
+
+    def calls():
+        a = api.psdf_grad(inst.footprint, poses, es, params)
+        b = api.psdf_eval(inst.footprint, poses, es, params)
+        c = api.psdf_constraints(inst.footprint, poses, es, 0.01, params)
+        torch.cuda.synchronize()
+        return [t.cpu().numpy() for t in (*a, *b, *c)]
+
+    got = calls()
+    es.stage(params)
+    staged = calls()
+    es.unstage()
+    api.set_launch_shape(256, 1)
+    try:
+        want = calls()
+    finally:
+        api.set_launch_shape()
+    for k, (g, s, w) in enumerate(zip(got, staged, want)):
+        for x in (g, s):
+            bad = np.flatnonzero((x.view(np.uint8) != w.view(np.uint8)).reshape(len(w), -1).any(1))
+            assert len(bad) == 0, (k, bad[:5], x[bad[:5]], w[bad[:5]])
+
+
+@pytest.mark.parametrize("N,M", [(200, 5000), (61, 20000), (3, 400001), (1, 1025000)])
+def test_plain_sizes(N, M):
+    rng = np.random.default_rng(N)
+    fp = inputs.hexagon_footprint(rng)
+    half = 0.5 * np.sqrt(M / 2.56)
+    inst = SimpleNamespace(footprint=fp, poses=inputs.path_poses(rng, N, -half / 2, half / 2),
+                           edges=inputs.random_rects(rng, M, 0.1, 0.8, -half, half),
+                           obst_off=inputs.csr_offsets([4] * M))
+    _plain_check(inst)
+
+
+@pytest.mark.parametrize("mbar,m", [(4, 3), (4, 8), (8, 5), (16, 4), (4, 16)])
+def test_plain_edge_classes_and_odd_obstacles(mbar, m):
+    from paper_2607_04310_amd import api
+    rng = np.random.default_rng(10 * mbar + m)
+    ang = 2 * np.pi * np.arange(m) / m
+    fp = np.stack([0.5 * np.cos(ang), 0.35 * np.sin(ang)], 1).astype(np.float32)
+    inst = _inst(rng, fp, 130, 12300, 30.0, mbar=mbar, odd=ODD)
+    inst.poses[7, 0] = np.nan
+    inst.poses[9, 2] = np.inf
+    inst.poses[11, 1] = -4e15
+    for params in (None, api.hard_min(), api.Params(eta=2.0, eps=1e-3)):
+        _plain_check(inst, mbar, params)
+    inst.edges[101, 2] = np.inf
+    inst.obst_off[5000] = inst.obst_off[4999] - 1
+    _plain_check(inst, mbar)
+
+
+def test_plain_crowd_and_empty_segments():
+    rng = np.random.default_rng(3)
+    fp = inputs.rect_footprint()
+    # 3000 rectangles over the robot, 9000 empty obstacles, 3000 far away
+    rect = np.concatenate([inputs.random_rects(rng, 3000, 0.1, 0.8, -0.4, 0.4),
+                           inputs.random_rects(rng, 3000, 0.1, 0.8, 90.0, 99.0)])
+    off = inputs.csr_offsets([4] * 3000 + [0] * 9000 + [4] * 3000)
+    inst = SimpleNamespace(footprint=fp, poses=inputs.uniform_poses(rng, 100, -0.5, 0.5),
+                           edges=rect, obst_off=off)
+    _plain_check(inst)
