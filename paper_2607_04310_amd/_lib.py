@@ -136,6 +136,26 @@ def lib():
     return _lib
 
 
+_native = None
+
+
+def native():
+    """The native calls of api.py (csrc/psdf_native.cpp); raises if they have
+    not been built.  They call the library that lib() has loaded."""
+    global _native
+    if _native is None:
+        lib()
+        try:
+            from . import _native as mod
+        except ImportError as e:
+            raise RuntimeError("the package's _native.so is missing or does not load: build it "
+                               "with `python -c 'import __graft_entry__ as g; g.build()'`") from e
+        from . import api
+        mod.bind(api)
+        _native = mod
+    return _native
+
+
 def check(rc):
     if rc != PSDF_OK:
         raise PsdfError(rc, lib().psdf_last_error().decode())

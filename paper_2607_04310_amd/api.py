@@ -2,7 +2,9 @@
 
 Every function here allocates its output tensors with torch on the poses'
 device and calls the library on torch's current stream; the arithmetic is
-all in the HIP kernels.
+all in the HIP kernels.  The per-step calls do so in native code
+(csrc/psdf_native.cpp), which takes plain arguments as they are and passes
+others through the conversions here (_fp_array, _poses).
 """
 from __future__ import annotations
 
@@ -15,6 +17,7 @@ import numpy as np
 import torch
 
 from . import _lib
+from ._lib import PsdfError  # noqa: F401
 
 DEFAULT_EPS = 1e-12
 DEFAULT_EPS_SAT = 1e-6
@@ -76,10 +79,7 @@ class EdgeSet:
         if table is None or table.numel() < max(nbytes, 16):
             table = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=self.ax.device)
         st = _lib.PsdfStaged()
-        ec, pc = self._plain(), params.c()
-        _lib.check(_lib.lib().psdf_stage_edges(ctypes.byref(ec), ctypes.byref(pc),
-                                               table.data_ptr(), table.numel(),
-                                               ctypes.byref(st), _lib.stream_handle()))
+        _lib.native().stage_edges(self, params, table, st)
         self._table, self._staged = table, st
         return self
 
@@ -103,8 +103,12 @@ class EdgeSet:
         return ec
 
 
+def _fp_array(footprint):
+    return np.ascontiguousarray(np.asarray(footprint, dtype=np.float32).reshape(-1, 2))
+
+
 def _fp(footprint):
-    fp = np.ascontiguousarray(np.asarray(footprint, dtype=np.float32).reshape(-1, 2))
+    fp = _fp_array(footprint)
     return fp, fp.ctypes.data_as(ctypes.c_void_p), int(fp.shape[0])
 
 
@@ -121,61 +125,18 @@ def workspace(N, M, device):
 
 def psdf_eval(footprint, poses, edges: EdgeSet, params: Params | None = None, ws=None):
     """phi, edge, obstacle and winner keys per stage (psdf_eval of the C ABI)."""
-    params = params or Params()
-    poses = _poses(poses)
-    N = poses.shape[0]
-    dev = poses.device
-    d = torch.empty(N, dtype=torch.float32, device=dev)
-    edge = torch.empty(N, dtype=torch.int32, device=dev)
-    obst = torch.empty(N, dtype=torch.int32, device=dev)
-    keys = torch.empty(N, dtype=torch.int64, device=dev)
-    ws = workspace(N, edges.M, dev) if ws is None else ws
-    fp, fpp, m = _fp(footprint)
-    ec, pc = edges.c(), params.c()
-    _lib.check(_lib.lib().psdf_eval(fpp, m, poses.data_ptr(), N, ctypes.byref(ec),
-                                    ctypes.byref(pc), d.data_ptr(), edge.data_ptr(),
-                                    obst.data_ptr(), keys.data_ptr(), ws.data_ptr(),
-                                    ws.numel(), _lib.stream_handle()))
-    return d, edge, obst, keys
+    return _lib.native().eval(footprint, poses, edges, params, ws)
 
 
 def psdf_grad(footprint, poses, edges: EdgeSet, params: Params | None = None, out=None,
               ws=None):
     """phi, edge, obstacle, dphi/d(x, y, theta) and winner keys per stage."""
-    params = params or Params()
-    poses = _poses(poses)
-    N = poses.shape[0]
-    dev = poses.device
-    if out is None:
-        out = (torch.empty(N, dtype=torch.float32, device=dev),
-               torch.empty(N, dtype=torch.int32, device=dev),
-               torch.empty(N, dtype=torch.int32, device=dev),
-               torch.empty((N, 3), dtype=torch.float32, device=dev),
-               torch.empty(N, dtype=torch.int64, device=dev))
-    d, edge, obst, grad, keys = out
-    ws = workspace(N, edges.M, dev) if ws is None else ws
-    fp, fpp, m = _fp(footprint)
-    ec, pc = edges.c(), params.c()
-    _lib.check(_lib.lib().psdf_grad(fpp, m, poses.data_ptr(), N, ctypes.byref(ec),
-                                    ctypes.byref(pc), d.data_ptr(), edge.data_ptr(),
-                                    obst.data_ptr(), grad.data_ptr(), keys.data_ptr(),
-                                    ws.data_ptr(), ws.numel(), _lib.stream_handle()))
-    return d, edge, obst, grad, keys
+    return _lib.native().grad(footprint, poses, edges, params, out, ws)
 
 
 def psdf_bwd(footprint, poses, edges: EdgeSet, keys, gout, params: Params | None = None):
     """gpose[s] = gout[s] * dphi_s/d(x, y, theta), from the keys of a psdf_eval."""
-    params = params or Params()
-    poses = _poses(poses)
-    N = poses.shape[0]
-    gout = gout.contiguous().to(torch.float32)
-    gpose = torch.empty((N, 3), dtype=torch.float32, device=poses.device)
-    fp, fpp, m = _fp(footprint)
-    ec, pc = edges.c(), params.c()
-    _lib.check(_lib.lib().psdf_bwd(fpp, m, poses.data_ptr(), N, ctypes.byref(ec),
-                                   ctypes.byref(pc), keys.data_ptr(), gout.data_ptr(),
-                                   gpose.data_ptr(), _lib.stream_handle()))
-    return gpose
+    return _lib.native().bwd(footprint, poses, edges, keys, gout, params)
 
 
 def psdf_constraints(footprint, poses, edges: EdgeSet, d_min, params: Params | None = None,
@@ -184,24 +145,7 @@ def psdf_constraints(footprint, poses, edges: EdgeSet, d_min, params: Params | N
     (phi - d_min, -dphi/dx, -dphi/dy, -dphi/dtheta) on the device, plus the
     winner keys; with ``host`` (a pinned CPU float32 (N, 4) tensor) the rows
     are also copied there on the stream."""
-    params = params or Params()
-    poses = _poses(poses)
-    N = poses.shape[0]
-    dev = poses.device
-    hj = torch.empty((N, 4), dtype=torch.float32, device=dev)
-    keys = torch.empty(N, dtype=torch.int64, device=dev)
-    ws = workspace(N, edges.M, dev) if ws is None else ws
-    if host is not None and (host.dtype != torch.float32 or tuple(host.shape) != (N, 4)
-                             or not host.is_contiguous() or host.is_cuda):
-        raise ValueError("host must be a contiguous CPU float32 tensor of shape (N, 4)")
-    fp, fpp, m = _fp(footprint)
-    ec, pc = edges.c(), params.c()
-    _lib.check(_lib.lib().psdf_constraints(fpp, m, poses.data_ptr(), N, ctypes.byref(ec),
-                                           ctypes.byref(pc), float(d_min), hj.data_ptr(),
-                                           None if host is None else host.data_ptr(),
-                                           keys.data_ptr(), ws.data_ptr(), ws.numel(),
-                                           _lib.stream_handle()))
-    return hj, keys
+    return _lib.native().constraints(footprint, poses, edges, d_min, params, host, ws)
 
 
 def psdf_bwd_geometry(footprint, poses, edges: EdgeSet, keys, gout, params: Params | None = None):
@@ -209,20 +153,7 @@ def psdf_bwd_geometry(footprint, poses, edges: EdgeSet, keys, gout, params: Para
     gradient of phi_s with respect to the edge endpoints (A_x, A_y, B_x, B_y)
     and the footprint vertices (caller's order), from the keys of a
     psdf_eval / psdf_grad on the same inputs."""
-    params = params or Params()
-    poses = _poses(poses)
-    N = poses.shape[0]
-    dev = poses.device
-    gout = gout.contiguous().to(torch.float32)
-    fp, fpp, m = _fp(footprint)
-    gedges = torch.empty((edges.E, 4), dtype=torch.float32, device=dev)
-    gfp = torch.empty((m, 2), dtype=torch.float32, device=dev)
-    ec, pc = edges.c(), params.c()
-    _lib.check(_lib.lib().psdf_bwd_geometry(fpp, m, poses.data_ptr(), N, ctypes.byref(ec),
-                                            ctypes.byref(pc), keys.data_ptr(), gout.data_ptr(),
-                                            gedges.data_ptr(), gfp.data_ptr(),
-                                            _lib.stream_handle()))
-    return gedges, gfp
+    return _lib.native().bwd_geometry(footprint, poses, edges, keys, gout, params)
 
 
 def time_stage_min(footprint, poses, edges: EdgeSet, reps, params: Params | None = None,
@@ -244,15 +175,7 @@ def time_stage_min(footprint, poses, edges: EdgeSet, reps, params: Params | None
 
 def psdf_sd_matrix(footprint, poses, edges: EdgeSet, params: Params | None = None, out=None):
     """sd[s, i] of every obstacle i at every stage s, before the minimum."""
-    params = params or Params()
-    poses = _poses(poses)
-    N = poses.shape[0]
-    sd = torch.empty((N, edges.M), dtype=torch.float32, device=poses.device) if out is None else out
-    fp, fpp, m = _fp(footprint)
-    ec, pc = edges.c(), params.c()
-    _lib.check(_lib.lib().psdf_sd_matrix(fpp, m, poses.data_ptr(), N, ctypes.byref(ec),
-                                         ctypes.byref(pc), sd.data_ptr(), _lib.stream_handle()))
-    return sd
+    return _lib.native().sd_matrix(footprint, poses, edges, params, out)
 
 
 def validate_edges(edges: EdgeSet):
@@ -269,22 +192,8 @@ def validate_edges(edges: EdgeSet):
 
 def psdf_encode_padded(A, B, S):
     """EncodeEdges (Alg. 1): padded (A, B, S) device tensors -> device EdgeSet."""
-    Mbar, mbar = int(S.shape[0]), int(S.shape[1])
-    dev = S.device
-    A = A.contiguous().to(torch.float32)
-    B = B.contiguous().to(torch.float32)
-    S8 = S.contiguous().to(torch.uint8)
-    cap = max(1, Mbar * mbar)
-    ax, ay, bx, by = (torch.empty(cap, dtype=torch.float32, device=dev) for _ in range(4))
-    off = torch.empty(Mbar + 1, dtype=torch.int32, device=dev)
-    wsb = int(_lib.lib().psdf_encode_ws_bytes(Mbar))
-    ws = torch.empty(max(1, wsb), dtype=torch.uint8, device=dev)
-    _lib.check(_lib.lib().psdf_encode_padded(A.data_ptr(), B.data_ptr(), S8.data_ptr(), Mbar, mbar,
-                                             ax.data_ptr(), ay.data_ptr(), bx.data_ptr(),
-                                             by.data_ptr(), off.data_ptr(), ws.data_ptr(),
-                                             wsb, _lib.stream_handle()))
-    E = int(off[-1].item()) if Mbar > 0 else 0
-    return EdgeSet.from_device(ax[:E], ay[:E], bx[:E], by[:E], off, max(1, min(mbar, 16)))
+    ax, ay, bx, by, off = _lib.native().encode_padded(A, B, S)
+    return EdgeSet.from_device(ax, ay, bx, by, off, max(1, min(int(S.shape[1]), 16)))
 
 
 class PsdfFunction(torch.autograd.Function):
@@ -518,9 +427,4 @@ def mlp_grad(theta, X, T, ws=None):
 
 def mlp_train_step(theta, m, v, step, lr, X, T, loss=None, ws=None):
     """One forward/backward/Adam step on the device (psdf_mlp_train_step)."""
-    B = int(X.shape[0])
-    ws = _mlp_ws(B, X.device) if ws is None else ws
-    _lib.check(_lib.lib().psdf_mlp_train_step(
-        theta.data_ptr(), m.data_ptr(), v.data_ptr(), int(step), float(lr), X.data_ptr(),
-        T.data_ptr(), B, loss.data_ptr() if loss is not None else None, ws.data_ptr(),
-        ws.numel(), _lib.stream_handle()))
+    _lib.native().mlp_train_step(theta, m, v, step, lr, X, T, loss, ws)
