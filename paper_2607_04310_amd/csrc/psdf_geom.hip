@@ -32,17 +32,16 @@
 namespace psdf {
 namespace {
 
-constexpr int kGeoWaves = 4;      // stages per work-group
+constexpr int kGeoWaves = 1;      // stages per work-group: one wave each spreads the stages over
+                                  // the CUs (the kernel is one stage's chain of steps; with the
+                                  // pose adjoint's pools and the sums over K lanes instead of
+                                  // 64, 10.5 -> 6.6 us at 50 stages)
 constexpr int kSlots = 4;         // contributions per lane
 constexpr int kRobot = 64;        // target ids: 2 j (A_j), 2 j + 1 (B_j), kRobot + l (v_l)
 
 struct GeoLds {
-  float tax[kMaxObst], tay[kMaxObst];    // A~_j
-  float vx[kMaxObst], vy[kMaxObst];      // v~_j = R^T (B_j - A_j)
-  float nx[kMaxObst], ny[kMaxObst];      // n'_j
-  float iv2[kMaxObst], il[kMaxObst];     // 1 / (|v|^2 + eps), 1 / (|v| + eps)
+  WinnerLds w;                           // the winner's local geometry
   float len[kMaxObst];                   // |v|
-  float px[2 * kMaxObst], py[2 * kMaxObst];   // V_obs
   alignas(16) int tgt[64][kSlots];
   alignas(16) float gx[64][kSlots];
   alignas(16) float gy[64][kSlots];
@@ -96,50 +95,22 @@ __global__ __launch_bounds__(64 * kGeoWaves) void geom_bwd_kernel(
     return;
   }
 
-  // ---- the winner's local geometry (as in winner_adjoint)
-  bool open_edge = false;
-  if (lane < mi) {
-    const float a0 = ax[e0 + lane], a1 = ay[e0 + lane];
-    const float b0 = bx[e0 + lane], b1 = by[e0 + lane];
-    const int nxt = lane + 1 < mi ? lane + 1 : 0;
-    const float n0 = ax[e0 + nxt], n1 = ay[e0 + nxt];
-    open_edge = __float_as_uint(b0) != __float_as_uint(n0) || __float_as_uint(b1) != __float_as_uint(n1);
-    float iv2, il, tx, ty, vx, vy;
-    edge_consts(b0 - a0, b1 - a1, F.eps, iv2, il);
-    local_point(a0, a1, cs, sn, px, py, tx, ty);
-    local_vector(b0 - a0, b1 - a1, cs, sn, vx, vy);
-    G.tax[lane] = tx; G.tay[lane] = ty; G.vx[lane] = vx; G.vy[lane] = vy;
-    G.nx[lane] = -vy * il; G.ny[lane] = vx * il;
-    G.iv2[lane] = iv2; G.il[lane] = il;
-    G.len[lane] = __builtin_amdgcn_sqrtf(fmaf(b0 - a0, b0 - a0, (b1 - a1) * (b1 - a1)));
-    G.px[lane] = tx; G.py[lane] = ty;
-    G.px[mi + lane] = tx + vx; G.py[mi + lane] = ty + vy;
-  }
-  const bool closed = mi >= 3 && __ballot(open_edge) == 0;
-  const int nv = closed ? mi : 2 * mi;
+  // ---- the winner's local geometry and active pool pair (as the pose adjoint
+  // takes them)
 #pragma unroll
   for (int q = 0; q < kSlots; ++q) G.tgt[lane][q] = -1;
-  wave_sync();
-
-  // ---- active pool pair: smallest (d^2, entry), entries as in winner_adjoint
-  const int PV = m * mi, P = PV + nv * m;
-  uint64_t best = ~0ull;
-  for (int e = lane; e < P; e += 64) {
-    float qx, qy, sax, say, svx, svy, siv;
-    if (e < PV) {
-      const int l = e / mi, j = e - l * mi;
-      qx = FL.vx[l]; qy = FL.vy[l];
-      sax = G.tax[j]; say = G.tay[j]; svx = G.vx[j]; svy = G.vy[j]; siv = G.iv2[j];
-    } else {
-      const int e2 = e - PV, k = e2 / m, l = e2 - k * m;
-      qx = G.px[k]; qy = G.py[k];
-      sax = FL.vx[l]; say = FL.vy[l]; svx = FL.ex[l]; svy = FL.ey[l]; siv = FL.einv[l];
-    }
-    const float d2 = seg_d2(qx, qy, sax, say, svx, svy, siv);
-    const uint64_t k2 = ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)e;
-    best = k2 < best ? k2 : best;
+  const EdgeArrays edges{ax, ay, bx, by, e0};
+  const WinnerPools wp =
+      mi <= 4 ? winner_pools4(F, FL, G.w, edges, mi, cs, sn, px, py, true)
+              : winner_pools(F, FL, G.w, edges, mi, cs, sn, px, py);
+  WinnerLds& W = G.w;
+  if (lane < mi) {
+    float a0, a1, b0, b1;
+    edges(lane, a0, a1, b0, b1);
+    G.len[lane] = __builtin_amdgcn_sqrtf(fmaf(b0 - a0, b0 - a0, (b1 - a1) * (b1 - a1)));
   }
-  best = wave_min_u64(best);
+  const int nv = wp.closed ? mi : 2 * mi;
+  wave_sync();
 
   // ---- axes: lane q < m + mi owns axis q; extremes by index (first on ties)
   const int K = m + mi;
@@ -152,7 +123,7 @@ __global__ __launch_bounds__(64 * kGeoWaves) void geom_bwd_kernel(
       alo = FL.pa[lane]; ahi = FL.pb[lane];
     } else {
       const int j = lane - m;
-      nxq = G.nx[j]; nyq = G.ny[j];
+      nxq = W.nx[j]; nyq = W.ny[j];
       alo = __builtin_huge_valf(); ahi = -__builtin_huge_valf();
     }
     float plo = __builtin_huge_valf(), phi = -__builtin_huge_valf();
@@ -164,7 +135,7 @@ __global__ __launch_bounds__(64 * kGeoWaves) void geom_bwd_kernel(
     if (lane >= m) { alo = plo; ahi = phi; }
     float lo = __builtin_huge_valf(), hi = -__builtin_huge_valf();
     for (int k = 0; k < nv; ++k) {
-      const float q = fmaf(G.px[k], nxq, G.py[k] * nyq);
+      const float q = fmaf(W.px[k], nxq, W.py[k] * nyq);
       if (q < lo) { lo = q; klo = k; }
       if (q > hi) { hi = q; khi = k; }
     }
@@ -184,19 +155,14 @@ __global__ __launch_bounds__(64 * kGeoWaves) void geom_bwd_kernel(
   };
   if (sep) {
     if (lane == 0) {
-      const int e = (int)(best & 0xffffffffu);
-      const float d2b = __uint_as_float((uint32_t)(best >> 32));
-      float qx, qy, sax, say, svx, svy, siv;
+      const float qx = wp.qx, qy = wp.qy, sax = wp.sx, say = wp.sy, svx = wp.vx, svy = wp.vy;
+      const float siv = wp.iv, d2b = wp.d2;
       int tq, ta, tb;
-      if (e < PV) {
-        const int l = e / mi, j = e - l * mi;
-        qx = FL.vx[l]; qy = FL.vy[l];
-        sax = G.tax[j]; say = G.tay[j]; svx = G.vx[j]; svy = G.vy[j]; siv = G.iv2[j];
+      if (wp.vtype) {
+        const int l = wp.e / mi, j = wp.e - l * mi;
         tq = kRobot + l; ta = 2 * j; tb = 2 * j + 1;
       } else {
-        const int e2 = e - PV, k = e2 / m, l = e2 - k * m;
-        qx = G.px[k]; qy = G.py[k];
-        sax = FL.vx[l]; say = FL.vy[l]; svx = FL.ex[l]; svy = FL.ey[l]; siv = FL.einv[l];
+        const int e2 = wp.e - m * mi, k = e2 / m, l = e2 - k * m;
         tq = point_target(k, mi); ta = kRobot + l; tb = kRobot + (l + 1 < m ? l + 1 : 0);
       }
       const float d = sqrtf(d2b);
@@ -239,14 +205,14 @@ __global__ __launch_bounds__(64 * kGeoWaves) void geom_bwd_kernel(
         // delta = beta_i - alpha_P: obstacle point khi, robot vertex rlo
         put(point_target(khi, mi), gd * nxq, gd * nyq);
         put(kRobot + rlo, -gd * nxq, -gd * nyq);
-        gnx = gd * (G.px[khi] - FL.vx[rlo]);
-        gny = gd * (G.py[khi] - FL.vy[rlo]);
+        gnx = gd * (W.px[khi] - FL.vx[rlo]);
+        gny = gd * (W.py[khi] - FL.vy[rlo]);
       } else {
         // delta = beta_P - alpha_i: robot vertex rhi, obstacle point klo
         put(kRobot + rhi, gd * nxq, gd * nyq);
         put(point_target(klo, mi), -gd * nxq, -gd * nyq);
-        gnx = gd * (FL.vx[rhi] - G.px[klo]);
-        gny = gd * (FL.vy[rhi] - G.py[klo]);
+        gnx = gd * (FL.vx[rhi] - W.px[klo]);
+        gny = gd * (FL.vy[rhi] - W.py[klo]);
       }
       if (lane < m) {
         // n = rot(-90)(e) / |e|, e = v_{l+1} - v_l:
@@ -262,7 +228,7 @@ __global__ __launch_bounds__(64 * kGeoWaves) void geom_bwd_kernel(
         // n' = rot90(u) k, k = 1 / (|u| + eps), u = B~_j - A~_j:
         // d/du = k rot90^T(gn) - k^2 (gn . rot90(u)) u / |u|
         const int j = lane - m;
-        const float ux = G.vx[j], uy = G.vy[j], k = G.il[j], L = G.len[j];
+        const float ux = W.vx[j], uy = W.vy[j], k = W.il[j], L = G.len[j];
         const float gr = fmaf(gnx, -uy, gny * ux);   // gn . rot90(u)
         const float c2 = L > 0.f ? k * k * gr / L : 0.f;
         const float gux = k * gny - c2 * ux, guy = -k * gnx - c2 * uy;
@@ -283,8 +249,9 @@ __global__ __launch_bounds__(64 * kGeoWaves) void geom_bwd_kernel(
   // flight at once instead of one read and branch per slot
   static_assert(kSlots == 4, "the sums read a lane's slots as one vector");
   float sx = 0.f, sy = 0.f;
-#pragma unroll 8
-  for (int l = 0; l < 64; ++l) {
+  // (only the axes' lanes, or lane 0, hold slots)
+#pragma unroll 4
+  for (int l = 0; l < K; ++l) {
     const int4 tg = *reinterpret_cast<const int4*>(G.tgt[l]);
     const float4 ux = *reinterpret_cast<const float4*>(G.gx[l]);
     const float4 uy = *reinterpret_cast<const float4*>(G.gy[l]);

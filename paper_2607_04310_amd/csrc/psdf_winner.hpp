@@ -243,6 +243,7 @@ __device__ __forceinline__ void wave_stages(const FpConst& F, const float* __res
 // iv = 1 / (|V|^2 + eps), and the reported edge.
 struct WinnerPools {
   float d2, qx, qy, sx, sy, vx, vy, iv;
+  int e;         // the entry
   bool vtype;    // Q is a robot vertex
   bool closed;
   int jstar;
@@ -310,7 +311,8 @@ __device__ __forceinline__ WinnerPools winner_pools4(const FpConst& F, const FpL
   const uint32_t emin = fw_min_u32(d == dmin ? e : none);
   const int w = __ffsll((unsigned long long)__ballot(d == dmin && e == emin)) - 1;
   r.d2 = __uint_as_float(dmin);
-  r.vtype = (int)emin < PV;
+  r.e = (int)emin;
+  r.vtype = r.e < PV;
   const bool btype = (int)emin >= PV + mi * m;
   auto from = [&](float x) { return __uint_as_float(lane_u32(__float_as_uint(x), w)); };
   r.qx = from(r.vtype ? rvx : (btype ? wx : tx));
@@ -398,7 +400,8 @@ __device__ __forceinline__ WinnerPools winner_pools(const FpConst& F, const FpLd
   wave_sync();
   const uint64_t ek = lane < mi ? (((uint64_t)W.epool[lane] << 32) | (uint32_t)lane) : ~0ull;
   r.jstar = (int)(wave_min_u64(ek) & 0xffffffffu);
-  entry((int)(best & 0xffffffffu), ej, ej2);
+  r.e = (int)(best & 0xffffffffu);
+  entry(r.e, ej, ej2);
   r.d2 = __uint_as_float((uint32_t)(best >> 32));
   return r;
 }
