@@ -404,7 +404,7 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
     const bool empty = STAGED ? b.x == kEmptyBox : ld[q].mi == 0;
     take[q] = !empty && !none && !far;
     const uint64_t m = __ballot(take[q]);
-    at[q] = n + (int)__popcll(m & ((1ull << lane) - 1ull));
+    at[q] = n + lanes_below(m);
     n += (int)__popcll(m);
   }
   if (lane == 0) s_n[w] = n;
@@ -512,7 +512,6 @@ __device__ __forceinline__ void cull_evaluate(const FpConst& F, const FpSlot* fs
                                               const Src& src, float px, float py,
                                               CullBest& best) {
   const int lane = threadIdx.x & 63;
-  const uint64_t below = (1ull << lane) - 1ull;
   wave_sync();
   float lb[kCullCand / 64];
   const bool cut = n > 64 / MI;
@@ -546,7 +545,7 @@ __device__ __forceinline__ void cull_evaluate(const FpConst& F, const FpSlot* fs
     for (int h = 0; h < kCullCand / 64; ++h) {
       const bool t = lane + 64 * h < n && !(lb[h] > to) && !(lb[h] <= from);
       const uint64_t m = __ballot(t);
-      if (t) pick[np + (int)__popcll(m & below)] = (uint8_t)(lane + 64 * h);
+      if (t) pick[np + lanes_below(m)] = (uint8_t)(lane + 64 * h);
       np += (int)__popcll(m);
     }
     wave_sync();
@@ -560,12 +559,16 @@ __device__ __forceinline__ void cull_evaluate(const FpConst& F, const FpSlot* fs
       src.edge(sl, m, lane & (MI - 1), !bad, ax, ay, bx, by);
       const float sd = group_sd<MI>(F, fs, dls, ax, ay, bx, by, m.z, (m.w & kRecClosed) != 0, !bad,
                                     px, py);
-      const uint64_t k =
-          act ? ((uint64_t)(bad ? 0u : orderable(sd)) << 32) | (uint32_t)m.x : kEmptyKey;
-      const uint64_t kw = fw_min_u64(k);
+      // the round's least sd, then its lowest obstacle
+      const uint32_t none = 0xffffffffu;
+      const uint32_t k = act ? (bad ? 0u : orderable(sd)) : none;
+      const uint32_t kmin = fw_min_u32(k);
+      const uint32_t omin = fw_min_u32(k == kmin && act ? (uint32_t)m.x : none);
+      const uint64_t kw = ((uint64_t)kmin << 32) | omin;
       if (kw < best.key) {
         best.key = kw;
-        const int f = __ffsll((unsigned long long)__ballot(k == kw)) - 1;
+        const int f =
+            __ffsll((unsigned long long)__ballot(act && k == kmin && (uint32_t)m.x == omin)) - 1;
         best.slot = (int)lane_u32((uint32_t)sl, f);
         best.meta = make_int4((int)(uint32_t)kw, (int)lane_u32((uint32_t)m.y, f),
                               (int)lane_u32((uint32_t)m.z, f), (int)lane_u32((uint32_t)m.w, f));
@@ -600,7 +603,6 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
   __shared__ FpLds fl;
   __shared__ WinnerLds wl;
   const int lane = threadIdx.x;
-  const uint64_t below = (1ull << lane) - 1ull;
   typedef const __attribute__((address_space(4))) CullStage StC;
   const CullStage& R = *(const CullStage*)((StC*)A.stages + blockIdx.x);
   const int g = R.row, nseg = R.nseg;
@@ -624,33 +626,37 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
   wave_sync();
   const uint64_t full = __ballot(cv > 0);
   if (cv > 0) {
-    segbase[__popcll(full & below)] = lane * kSegObst - start;
+    segbase[lanes_below(full)] = lane * kSegObst - start;
     if (start < kCullFlat) atomicOr(&starts[start >> 5], 1u << (start & 31));
   }
   wave_sync();
   const int nflat = min(total, 64 * kCullRounds);
-  // the slots of entries 64 r + lane, r = r0 .. r0 + 3; ord: segments with
-  // entries that start before, less one
-  auto slots = [&](int r0, int& ord, int n, int (&sl)[4]) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int r = r0 + u;
-      const uint64_t m = ((uint64_t)starts[2 * r + 1] << 32) | starts[2 * r];
-      sl[u] = 0;
-      if (r * 64 + lane < n)
-        sl[u] = segbase[ord + (int)__popcll(m & (below | (1ull << lane)))] + r * 64 + lane;
-      ord += (int)__popcll(m);
-    }
+  // the slot of entry 64 r + lane (0 past entry n); ord: segments with entries
+  // that start before round r, less one
+  auto slot_of = [&](int r, int& ord, int n) {
+    const uint64_t m = ((uint64_t)(uint32_t)uniform((int)starts[2 * r + 1]) << 32) |
+                       (uint32_t)uniform((int)starts[2 * r]);
+    int sl = 0;
+    if (r * 64 + lane < n)
+      sl = segbase[ord + lanes_below(m) + (int)((m >> lane) & 1ull)] + r * 64 + lane;
+    ord += (int)__popcll(m);
+    return sl;
   };
   int slot[kCullRounds];
   float d2[kCullRounds];
   uint32_t kb = 0xffffffffu;
   int ord0 = -1;
-  static_assert(kCullRounds == 4, "one group of rounds");
   float4 b0[kCullRounds];
-  slots(0, ord0, nflat, slot);
+  slot[0] = slot_of(0, ord0, nflat);
+  b0[0] = rec[slot[0]].box;
+  const bool longer = nflat > 64;
+  if (longer) {
 #pragma unroll
-  for (int r = 0; r < kCullRounds; ++r) b0[r] = rec[slot[r]].box;
+    for (int r = 1; r < kCullRounds; ++r) {
+      slot[r] = slot_of(r, ord0, nflat);
+      b0[r] = rec[slot[r]].box;
+    }
+  }
   // while these are in flight: the footprint at this stage
   float sn, cs;
   sincosf(th, &sn, &cs);
@@ -661,15 +667,19 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
     fl.nx[lane] = n.x; fl.ny[lane] = n.y; fl.pa[lane] = n.z; fl.pb[lane] = n.w;
     fs[lane] = FpSlot{rotated(a.x, a.y, a.z, a.w, cs, sn), c.x, c.y, e.w, c.z, c.w};
   }
+  d2[0] = dist2(b0[0]);
+  if (lane < nflat) kb = __float_as_uint(d2[0]);
+  if (longer) {
 #pragma unroll
-  for (int r = 0; r < kCullRounds; ++r) {
-    d2[r] = dist2(b0[r]);
-    if (r * 64 + lane < nflat) kb = min(kb, __float_as_uint(d2[r]));
+    for (int r = 1; r < kCullRounds; ++r) {
+      d2[r] = dist2(b0[r]);
+      if (r * 64 + lane < nflat) kb = min(kb, __float_as_uint(d2[r]));
+    }
   }
   // The entries past the registers, four rounds of loads in flight:
-  // f(slot, D^2, live) per round until it returns false (that round counts).  (r, ord) or, for a
-  // list longer than kCullFlat or of more than 64 segments, (seg, at) is
-  // where the walk stands.
+  // f(slot, D^2, live) per round until it returns false (that round counts).
+  // (r, ord) or, for a list longer than kCullFlat or of more than 64 segments,
+  // (seg, at) is where the walk stands.
   struct Walk { int r, ord, seg, at; };
   const bool flat = total <= kCullFlat && nseg <= 64;
   auto walk = [&](Walk& k, auto f) {
@@ -679,9 +689,11 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
         int sl[4], ord = k.ord;
         float4 b[4];
         const int r0 = k.r & ~3;
-        slots(r0, ord, total, sl);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) b[u] = rec[sl[u]].box;
+        for (int u = 0; u < 4; ++u) {
+          sl[u] = slot_of(r0 + u, ord, total);
+          b[u] = rec[sl[u]].box;
+        }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           if (!go || r0 + u < k.r || (r0 + u) * 64 >= total) continue;
@@ -750,7 +762,7 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
       auto take = [&](int sl, float x, bool live) {
         const bool t = live && x > lo && !(x > hi);
         const uint64_t m = __ballot(t);
-        const int at = n + (int)__popcll(m & below);
+        const int at = n + lanes_below(m);
         if (t && at < kCullCand) cand[at] = sl;
         n += (int)__popcll(m);
       };
@@ -890,7 +902,6 @@ void cull_main_kernel(
   __syncthreads();
   const SegSource src{ax, ay, bx, by, lbox, le0, lmeta, o0};
   int* cand = cands[w];
-  const uint64_t below = (1ull << lane) - 1ull;
   for (int t = w; t < ns; t += kWaves4) {
     const int s = s0 + t;
     if (t != w) {
@@ -932,7 +943,7 @@ void cull_main_kernel(
             const int c = (int)__popcll(m);
             if (r < r0 || n + c > kCullCand) continue;
             if (r != r0) continue;
-            if (t2) cand[n + (int)__popcll(m & below)] = 64 * r + lane;
+            if (t2) cand[n + lanes_below(m)] = 64 * r + lane;
             n += c;
             ++r0;
           }

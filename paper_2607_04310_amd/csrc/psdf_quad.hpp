@@ -152,6 +152,14 @@ __device__ __forceinline__ float group_max(float x) {
   if (G > 8) x = fmaxf(x, quad_dpp<kDppMirror>(x));
   return x;
 }
+template <int G>
+__device__ __forceinline__ uint32_t group_min_u32(uint32_t x) {
+  x = min(x, dpp_u32<kDppXor1>(x));
+  x = min(x, dpp_u32<kDppXor2>(x));
+  if (G > 4) x = min(x, dpp_u32<kDppHalfMirror>(x));
+  if (G > 8) x = min(x, dpp_u32<kDppMirror>(x));
+  return x;
+}
 // Lane k of the group's value (k a constant after unrolling).
 template <int G>
 __device__ __forceinline__ float group_lane(float x, int k) {
@@ -221,8 +229,8 @@ __device__ __forceinline__ float group_sd(const FpConst& F, const FpSlot* fs, fl
     mu = fminf(mu, fmaxf(d, 0.0f));
     if (j == 0) dl[l] = d;
   }
-  dv2 = group_min<G>(dv2);
-  de2 = group_min<G>(de2);
+  // squared distances are ordered as their bits
+  const float near2 = __uint_as_float(group_min_u32<G>(__float_as_uint(fminf(dv2, de2))));
   float dlo = 0.f;   // obstacle axis j
   if (__ballot(act && !sep)) {
     // the obstacle's interval on its own axis j (own_intervals)
@@ -248,14 +256,22 @@ __device__ __forceinline__ float group_sd(const FpConst& F, const FpSlot* fs, fl
     dlo = fminf(hi - rlo, rhi - lo);
     sep = sep || group_max<G>((dlo < -F.eps_sat) ? 1.f : 0.f) > 0.f;
   }
-  float sd = sqrtf(fminf(dv2, de2));
+  float sd = sqrtf(near2);
   if (__ballot(act && !sep)) {
     mu = fminf(mu, group_min<G>(fmaxf(dlo, 0.0f)));
     float depth = mu;
     if (!F.hard) {
       wave_sync();   // dl is written
+      // the robot axes' terms G at a time, a lane each; added in slot order
       float acc = 0.0f;
-      for (int l = 0; l < m; ++l) acc += expf(-F.eta * (fmaxf(dl[l], 0.0f) - mu));
+      for (int l0 = 0; l0 < m; l0 += G) {
+        const float t = l0 + j < m ? expf(-F.eta * (fmaxf(dl[l0 + j], 0.0f) - mu)) : 0.f;
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+          const float e = group_lane<G>(t, k);
+          if (l0 + k < m) acc += e;
+        }
+      }
       const float ej = expf(-F.eta * (fmaxf(dlo, 0.0f) - mu));
 #pragma unroll
       for (int k = 0; k < G; ++k) {

@@ -98,6 +98,12 @@ __device__ __forceinline__ uint64_t fw_min_u64(uint64_t x) {
   return min_u64(min_u64(lane_u64(x, 0), lane_u64(x, 16)), min_u64(lane_u64(x, 32), lane_u64(x, 48)));
 }
 
+// Bits of a wave-uniform mask below this lane.
+__device__ __forceinline__ int lanes_below(uint64_t m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                        __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
 // Inclusive prefix sum over the wave; *total gets the wave's sum.
 __device__ __forceinline__ int fw_scan_i32(int v, int* total) {
   uint32_t x = (uint32_t)v;
