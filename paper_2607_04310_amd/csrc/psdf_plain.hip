@@ -7,8 +7,9 @@
 //   epilogue_kernel  one wave per stage: reduce the partial keys, recompute the
 //                    winning obstacle with the wave-parallel adjoint
 //                    (psdf_winner.hpp), write keys, d, edge, obst, gradient
-// or, for at most 256 obstacles of at most four edges, small_kernel alone
-// (both steps for a stage in one launch, bit for bit the same outputs).
+// or, for at most 256 obstacles of at most four edges, small_kernel or
+// small_quad_kernel alone (both steps for a stage in one launch, bit for bit
+// the same outputs).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -18,6 +19,7 @@
 #include "psdf.h"
 #include "psdf_cull.hpp"
 #include "psdf_kernels.hpp"
+#include "psdf_quad.hpp"
 #include "psdf_winner.hpp"
 
 namespace psdf {
@@ -43,15 +45,12 @@ struct EpiOut {
 
 // One wave finishes stage s from its winning key: the winner's edge range
 // (e0, mi) comes from the aux word (have_aux) or from the offsets; the wave
-// recomputes the winner (winner_adjoint; at most MAXE edges) and lane 0 writes
-// the outputs.
-template <int MAXE>
+// recomputes the winner (winner_adjoint; at most MAXE edges, read through
+// edges(e0)) and lane 0 writes the outputs.
+template <int MAXE, class Edges>
 __device__ __forceinline__ void epilogue_finish(const FpConst& F, FpLds& FL, WinnerLds& WL,
-                                                const float* __restrict__ ax,
-                                                const float* __restrict__ ay,
-                                                const float* __restrict__ bx,
-                                                const float* __restrict__ by,
-                                                const int* __restrict__ off, int E, int M, int s,
+                                                Edges edges, const int* __restrict__ off, int E,
+                                                int M, int s,
                                                 float px, float py, float cs, float sn,
                                                 uint64_t key, int e0, int mi, bool have_aux,
                                                 float scale, const EpiOut& O) {
@@ -75,7 +74,7 @@ __device__ __forceinline__ void epilogue_finish(const FpConst& F, FpLds& FL, Win
   } else {
     int jstar = 0;
     dv = from_orderable((uint32_t)(key >> 32));
-    winner_adjoint<MAXE>(F, FL, WL, EdgeArrays{ax, ay, bx, by, e0}, mi, cs, sn, px, py,
+    winner_adjoint<MAXE>(F, FL, WL, edges(e0), mi, cs, sn, px, py,
                          O.mode != 0, dv, jstar, g);
     ov = i;
     ev = e0 + jstar;
@@ -169,8 +168,8 @@ __global__ __launch_bounds__(64 * kEpiWaves) void epilogue_kernel(
     have_aux = true;
   }
   wave_sync();
-  epilogue_finish<kMaxObst>(F, fl[w], wl[w], ax, ay, bx, by, off, E, M, s, px, py, cs, sn, key, e0, mi,
-                  have_aux, scale, O);
+  epilogue_finish<kMaxObst>(F, fl[w], wl[w], [&](int e) { return EdgeArrays{ax, ay, bx, by, e}; },
+                            off, E, M, s, px, py, cs, sn, key, e0, mi, have_aux, scale, O);
 }
 
 // Many columns (few stages, many obstacles): one work-group per stage
@@ -221,7 +220,7 @@ __global__ __launch_bounds__(kWideThreads) void epilogue_wide_kernel(
   sincosf(p[2], &sn, &cs);
   const uint64_t a = kmin != kEmptyKey ? s_aux : 0;
   if (lane == 0) O.keys[s] = kmin;
-  epilogue_finish<kMaxObst>(F, fl, wl, ax, ay, bx, by, off, E, M, s, px, py, cs, sn, kmin,
+  epilogue_finish<kMaxObst>(F, fl, wl, [&](int e) { return EdgeArrays{ax, ay, bx, by, e}; }, off, E, M, s, px, py, cs, sn, kmin,
                   (int)(uint32_t)(a >> 32), (int)(uint32_t)(a & 0xffffffffu), true, 1.0f, O);
 }
 
@@ -309,14 +308,150 @@ __global__ __launch_bounds__(64 * NW) void small_kernel(
       }
   }
   if (lane == 0) O.keys[s] = key;
-  epilogue_finish<4>(F, fl[0], wl[0], ax, ay, bx, by, off, E, M, s, px, py, cs, sn, key,
+  epilogue_finish<4>(F, fl[0], wl[0], [&](int e) { return EdgeArrays{ax, ay, bx, by, e}; }, off, E, M, s, px, py, cs, sn, key,
                   (int)(uint32_t)(a >> 32), (int)(uint32_t)(a & 0xffffffffu), true, 1.0f, O);
+}
+
+// small_kernel for few stages: a quad of lanes per obstacle (quad_eval, the
+// same value bit for bit), 16 obstacles per wave.  One stage's chain is all
+// such a call consists of, and this one is shorter: a lane loads and evaluates
+// one edge instead of four; the edge is loaded along with the offsets, where a
+// set of four-edge obstacles has it, and again only where the offsets say
+// otherwise; the rotated footprint is in registers, so nothing waits for a table
+// in LDS before the evaluation; the winner's edges reach the first wave through
+// LDS instead of memory.
+// Call replayed, six-vertex footprint, rectangles, small_kernel -> this:
+// 20 stages x 20 obstacles 7.8 -> 6.2 us, 20 x 64 7.4 -> 6.7, 100 x 100 7.8 ->
+// 7.0, 20 x 128 8.0 -> 7.0, 20000 x 16 37 -> 29; but 400 x 128 8.5 -> 9.1, 1000 x
+// 64 8.2 -> 9.2 and 4000 x 64 12.8 -> 20.
+constexpr int kQuadWaves = 8;
+// Which of the two: a quad costs about twice the instructions per obstacle,
+// so it is for calls that do not fill the chip (always for one wave, where
+// small_kernel's would be mostly empty).
+constexpr long kQuadWork = 8192;   // stages times waves squared, at most
+
+template <int MF>
+__global__ __launch_bounds__(64 * kQuadWaves) void small_quad_kernel(
+    FpConst F, const float* __restrict__ poses, int N, const float* __restrict__ ax,
+    const float* __restrict__ ay, const float* __restrict__ bx, const float* __restrict__ by,
+    const int* __restrict__ off, int E, int M, EpiOut O) {
+  __shared__ FpLds fl;
+  __shared__ WinnerLds wl;
+  __shared__ uint64_t wk[kQuadWaves], wa[kQuadWaves];
+  __shared__ float4 we[kQuadWaves][4];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, j = lane & 3;
+  const int s = blockIdx.x;
+  const int i = threadIdx.x >> 2, guess = threadIdx.x;   // edge 4 i + j
+  const bool active = i < M;
+  int e0 = 0, e1 = 0;
+  float a0 = 0.f, a1 = 0.f, b0 = 0.f, b1 = 0.f;
+  if (active) {
+    e0 = off[i];
+    e1 = off[i + 1];
+    if (guess < E) { a0 = ax[guess]; a1 = ay[guess]; b0 = bx[guess]; b1 = by[guess]; }
+  }
+  const float* p = poses + 3 * s;
+  const float px = p[0], py = p[1];
+  float sn, cs;
+  sincosf(p[2], &sn, &cs);
+  float4 rf[MF];
+#pragma unroll
+  for (int l = 0; l < MF; ++l) rf[l] = rotated_slot(F, l, cs, sn);
+  if (w == 0) stage_footprint(fl, F);
+
+  const int mi = e1 - e0;
+  const bool range = (mi < 0) || (mi > 4) || (e0 < 0) || (e0 > E - mi);
+  if (active && !range && mi > 0) {
+    const int at = e0 + min(j, mi - 1);
+    if (at != guess) { a0 = ax[at]; a1 = ay[at]; b0 = bx[at]; b1 = by[at]; }
+  }
+  // the flags of load_obstacle, across the quad
+  const int quad = lane & ~3;
+  auto any4 = [&](bool x) { return ((__ballot(x) >> quad) & 15ull) != 0; };
+  QuadEdge q;
+  q.mi = mi;
+  q.bad = any4(range || !(isfinite(a0) && isfinite(a1) && isfinite(b0) && isfinite(b1)));
+  const float f0 = quad_dpp<0x00>(a0), f1 = quad_dpp<0x00>(a1);
+  const float r0 = quad_dpp<0x39>(a0), r1 = quad_dpp<0x39>(a1);
+  const bool last = j + 1 >= mi;
+  const float n0 = last ? f0 : r0, n1 = last ? f1 : r1;
+  q.closed = !any4(mi < 3 || (j < mi && (__float_as_uint(b0) != __float_as_uint(n0) ||
+                                         __float_as_uint(b1) != __float_as_uint(n1))));
+  const float dx = b0 - a0, dy = b1 - a1;
+  float iv2, il;
+  edge_consts(dx, dy, F.eps, iv2, il);
+  q.ux = dx * il;
+  q.uy = dy * il;
+  q.len = __builtin_amdgcn_sqrtf(fmaf(dx, dx, dy * dy));
+  q.tax = a0 - px; q.tay = a1 - py;
+  q.tbx = b0 - px; q.tby = b1 - py;
+  const bool pose_ok = isfinite(cs) && isfinite(sn) && isfinite(px) && isfinite(py);
+  const float sd = quad_eval<MF>(F, q, rf, [&](float& olo, float& ohi) {
+    // own_intervals
+    float lo = __builtin_huge_valf(), hi = -__builtin_huge_valf();
+    auto visit = [&](float wx, float wy) {
+      const float v = fmaf(wy - a1, q.ux, -((wx - a0) * q.uy));
+      lo = fminf(lo, v);
+      hi = fmaxf(hi, v);
+    };
+    visit(quad_dpp<0x00>(a0), quad_dpp<0x00>(a1));
+    visit(quad_dpp<0x55>(a0), quad_dpp<0x55>(a1));
+    visit(quad_dpp<0xAA>(a0), quad_dpp<0xAA>(a1));
+    visit(quad_dpp<0xFF>(a0), quad_dpp<0xFF>(a1));
+    if (!q.closed) {
+      visit(quad_dpp<0x00>(b0), quad_dpp<0x00>(b1));
+      visit(quad_dpp<0x55>(b0), quad_dpp<0x55>(b1));
+      visit(quad_dpp<0xAA>(b0), quad_dpp<0xAA>(b1));
+      visit(quad_dpp<0xFF>(b0), quad_dpp<0xFF>(b1));
+    }
+    olo = lo;
+    ohi = hi;
+  });
+  uint32_t k = 0xffffffffu;
+  if (active && mi != 0) k = pose_ok ? orderable(sd) : 0u;
+  const uint32_t kmin = wave_min_u32(k);
+  uint64_t key = kEmptyKey, a = 0;
+  if (kmin != 0xffffffffu) {
+    const int first = __ffsll((unsigned long long)__ballot(k == kmin)) - 1;
+    key = ((uint64_t)kmin << 32) | (uint32_t)(16 * w + (first >> 2));
+    a = ((uint64_t)lane_u32((uint32_t)e0, first) << 32) | lane_u32((uint32_t)mi, first);
+    if (quad == (first & ~3)) we[w][j] = make_float4(a0, a1, b0, b1);
+  }
+  if (lane == 0) {
+    wk[w] = key;
+    wa[w] = a;
+  }
+  __syncthreads();
+  if (w != 0) return;
+  int best = 0;
+  const int nw = blockDim.x >> 6;
+  for (int v = 1; v < nw; ++v)
+    if (wk[v] < key) {
+      key = wk[v];
+      a = wa[v];
+      best = v;
+    }
+  if (lane == 0) O.keys[s] = key;
+  epilogue_finish<4>(
+      F, fl, wl,
+      [&](int) {
+        return [&](int e, float& x0, float& y0, float& x1, float& y1) {
+          const float4 v = we[best][e];
+          x0 = v.x; y0 = v.y; x1 = v.z; y1 = v.w;
+        };
+      },
+      off, E, M, s, px, py, cs, sn, key, (int)(uint32_t)(a >> 32),
+      (int)(uint32_t)(a & 0xffffffffu), true, 1.0f, O);
 }
 
 template <int MF>
 hipError_t launch_small_mf(const FpConst& F, const float* poses, int N, const psdf_edges& e,
                            const EpiOut& O, hipStream_t st) {
-  if (e.M <= 64)
+  const int nw = (e.M + 15) / 16;
+  if (nw <= kQuadWaves && (nw == 1 || (long)N * nw * nw <= kQuadWork))
+    small_quad_kernel<MF><<<N, 64 * nw, 0, st>>>(F, poses, N, e.ax, e.ay, e.bx, e.by, e.obst_off,
+                                                 e.E, e.M, O);
+  else if (e.M <= 64)
     small_kernel<MF, 1><<<N, 64, 0, st>>>(F, poses, N, e.ax, e.ay, e.bx, e.by, e.obst_off, e.E,
                                           e.M, O);
   else
