@@ -418,7 +418,11 @@ constexpr double kCullObstacles = 512;   // per stage, mean
 
 bool cull_pays(const psdf_batch_plan& p) {
   double pairs = 0.0;
-  for (const auto& d : p.desc) pairs += (double)d.N * d.M;
+  for (int k = 0; k < p.n_inst; ++k) {
+    pairs += (double)p.desc[k].N * p.desc[k].M;
+    // a needle of a footprint has no bound: one wave would evaluate all
+    if (p.desc[k].M > kSegObst && !std::isfinite(p.fp[k].cull_tau)) return false;
+  }
   return pairs >= kCullPairs && pairs >= kCullObstacles * p.total_stages;
 }
 

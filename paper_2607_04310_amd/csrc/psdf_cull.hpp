@@ -12,8 +12,20 @@
 // the axis test separates them, and sd is then their distance.  rel and the
 // terms of tau cover the rounding of the float evaluation, whose error grows
 // with the distance (measured 3e-7 of it), also where kappa is small.
-// Any other obstacle (invalid, open chain, not convex, a degenerate edge,
-// coordinates beyond 1e15) is irregular: it is always evaluated.
+// An open chain or a polygon that is not strictly convex has fewer axes than
+// its hull: only the robot's may separate it.  Some robot normal n is within
+// half an exterior angle, alpha, of the direction u to its box; every point of
+// the box lies beyond the nearest one along u and within its diagonal of it, so
+// the gap on n at distance r is at least cos(alpha) (r - diagonal tan(alpha)):
+// with the box enlarged by diagonal * tan(alpha) the bound above holds again (for
+// a sliver of a footprint that is the whole plane).  The second bound
+// (cull_evaluate) takes the box as it is.  16 x 50 stages x 16384 open chains,
+// everything evaluated -> enlarged boxes -> and the second bound: a triangle for
+// a footprint 1750 -> 770 -> 308 us (full evaluation 150), a hexagon 184 us (247); the
+// same with rectangles that have a vertex within a side: 142 -> 69 us (120) and
+// 28 us (196).
+// Any other obstacle (invalid, a degenerate edge, coordinates beyond 1e15) is
+// irregular: it is always evaluated.
 //
 // Two launches:
 //  * cull_list_kernel, one work-group per segment (kSegObst obstacles) of an
@@ -53,6 +65,7 @@ constexpr int kSegObst = kCullThreads * kCullPer;        // obstacles per segmen
 constexpr int kCullPad = 64;                             // list entries read past the last one
 constexpr float kCullGamma = 1e-3f;                      // metres
 constexpr float kCullMax = 1e15f;                        // coordinates beyond this: irregular
+constexpr float kCullPlane = 1e18f;                      // an enlargement to the whole plane
 
 // One segment of an instance's obstacles: [o0, o0 + no), list slots from
 // slot0, list length in cnt[its index].
@@ -69,8 +82,9 @@ struct CullStage {
 // A listed obstacle, one 64-byte record, so that the scan of the boxes brings
 // in what the evaluation reads next: the box (lo.x NaN: irregular), the
 // obstacle's index, first edge (global) and edge count, flags, and the points
-// of a closed polygon of at most four edges (A_j) or of one edge (A_0, B_0).
-constexpr int kRecClosed = 1, kRecBad = 2, kRecPoints = 4;
+// of a convex polygon of at most four edges (A_j) or of one edge (A_0, B_0), or
+// the box before its enlargement (kRecLoose).
+constexpr int kRecClosed = 1, kRecBad = 2, kRecPoints = 4, kRecLoose = 8;
 struct CullRec {
   float4 box;
   int4 meta;
@@ -148,16 +162,19 @@ __device__ __forceinline__ bool same_bits(float a, float b) {
   return __float_as_uint(a) == __float_as_uint(b);
 }
 
-// Box, flags and regularity of the obstacle with edges [e0, e0 + mi),
-// 1 <= mi <= MI and in range; the first edge (mi != 4) or all four (mi == 4)
+// Box (NaN: irregular) and flags of the obstacle with edges [e0, e0 + mi),
+// 1 <= mi <= MI and in range, and whether the box is a tight one, of a convex
+// obstacle; open: the factor of the enlargement of the others (FpConst); the first
+// edge (mi != 4) or all four (mi == 4)
 // are in v (ax, ay, bx, by), and with kRecPoints in the flags its points are
-// afterwards (v[0], v[1]: A_j).
+// afterwards (v[0], v[1]: A_j), with kRecLoose its box (v[0][0], v[1][0], v[0][1],
+// v[1][1]).
 template <int MI>
 __device__ __forceinline__ bool cull_obstacle(float (&v)[4][4], const float* __restrict__ gax,
                                               const float* __restrict__ gay,
                                               const float* __restrict__ gbx,
                                               const float* __restrict__ gby, int e0, int mi,
-                                              float minl2, float rel, float4& box,
+                                              float minl2, float rel, float open, float4& box,
                                               int& flags) {
   CullAcc c;
   c.lox = c.loy = __builtin_huge_valf();
@@ -208,19 +225,27 @@ __device__ __forceinline__ bool cull_obstacle(float (&v)[4][4], const float* __r
     cull_turn(c, ex, ey, ex0, ey0);
   }
   const bool bad = c.bad != c.bad;
-  flags = (c.closed ? kRecClosed : 0) | (bad ? kRecBad : 0) |
-          (MI == 4 && (c.closed || mi == 1) ? kRecPoints : 0);
   // a strictly convex polygon turns one way and its direction changes half
   // twice in one round (a star turns one way too, in more rounds)
   const bool convex = mi == 1 || (c.closed && (c.left || c.right) && c.flips <= 2);
   const float big = fmaxf(fmaxf(fabsf(c.lox), fabsf(c.loy)), fmaxf(fabsf(c.hix), fabsf(c.hiy)));
-  const bool regular = !bad && convex && c.longe && big < kCullMax;
+  const bool fine = !bad && c.longe && big < kCullMax;
   // enlarged by its own size (rounding of the evaluation) and by the
   // rounding of the enlargement itself
-  const float e = fmaf(rel, (c.hix - c.lox) + (c.hiy - c.loy), 2.5e-7f * big);
-  box = regular ? make_float4(c.lox - e, c.loy - e, c.hix + e, c.hiy + e)
-                : make_float4(__builtin_nanf(""), 0.f, 0.f, 0.f);
-  return regular;
+  const float size = (c.hix - c.lox) + (c.hiy - c.loy);
+  const float e = fmaf(rel, size, 2.5e-7f * big);
+  box = make_float4(__builtin_nanf(""), 0.f, 0.f, 0.f);
+  const bool bound = fine && e < kCullMax;
+  const bool loose = bound && !convex;
+  if (bound) box = make_float4(c.lox - e, c.loy - e, c.hix + e, c.hiy + e);
+  flags = (c.closed ? kRecClosed : 0) | (bad ? kRecBad : 0) | (loose ? kRecLoose : 0) |
+          (MI == 4 && !loose && (c.closed || mi == 1) ? kRecPoints : 0);
+  if (loose) {
+    v[0][0] = box.x; v[1][0] = box.y; v[0][1] = box.z; v[1][1] = box.w;
+    const float g = fminf(open * size, kCullPlane);
+    box = make_float4(box.x - g, box.y - g, box.z + g, box.w + g);
+  }
+  return bound && convex;
 }
 
 // The lo.x of a staged box whose obstacle has no edge.
@@ -259,12 +284,12 @@ struct CullLoad {
       for (int k = 0; k < 4; ++k) v[k][0] = *src[k];
     }
   }
-  __device__ __forceinline__ bool finish(const CullArgs& A, const FpConst& F, float4& box,
-                                         int& flags) {
+  __device__ __forceinline__ bool finish(const CullArgs& A, const FpConst& F, float open,
+                                         float4& box, int& flags) {
     box = make_float4(__builtin_nanf(""), 0.f, 0.f, 0.f);
     flags = kRecBad;
     return ok && cull_obstacle<MI>(v, A.ax, A.ay, A.bx, A.by, e0, mi, cull_minl2(F.eps),
-                                   F.cull_rel, box, flags);
+                                   F.cull_rel, open, box, flags);
   }
   __device__ __forceinline__ void record(CullRec* r, const float4& box, int o, int flags) const {
     r->box = box;
@@ -291,7 +316,9 @@ __global__ __launch_bounds__(256) void cull_stage_edges_kernel(CullArgs A, float
   ld.load(A, in, in.edge_off + in.E);
   float4 box;
   int flags;
-  ld.finish(A, fp_const(A.fps, S.inst), box, flags);
+  // (the list kernel does not know the loose boxes among the staged ones: as the
+  // whole plane they leave its bound of phi alone)
+  ld.finish(A, fp_const(A.fps, S.inst), __builtin_huge_valf(), box, flags);
   if (ld.mi == 0) box.x = kEmptyBox;
   sbox[S.slot0 + k] = box;
   ld.record(srec + S.slot0 + k, box, S.o0 + k, flags);
@@ -370,7 +397,7 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
     const float4& b = box[q];
     bool regular;
     if (STAGED) regular = b.x == b.x && b.x != kEmptyBox;
-    else regular = ld[q].finish(A, F, box[q], flags[q]);
+    else regular = ld[q].finish(A, F, F.cull_open, box[q], flags[q]);
     if (regular) {
       const float x0 = fmaxf(fabsf(b.x - plx), fabsf(b.x - phx));
       const float x1 = fmaxf(fabsf(b.z - plx), fabsf(b.z - phx));
@@ -436,7 +463,10 @@ template <int MI>
 struct RecSource {
   const CullArgs& A;
   const CullRec* rec;
-  __device__ __forceinline__ float4 box(int sl) const { return rec[sl].box; }
+  // the box for the second bound
+  __device__ __forceinline__ float4 box(int sl) const {
+    return (rec[sl].meta.w & kRecLoose) ? rec[sl].pts[0] : rec[sl].box;
+  }
   __device__ __forceinline__ int4 meta(int sl) const { return rec[sl].meta; }
   __device__ __forceinline__ void edge(int sl, const int4& m, int j, bool act, float& ax,
                                        float& ay, float& bx, float& by) const {
@@ -892,7 +922,7 @@ void cull_main_kernel(
       const int k = tid + kCullThreads * q;
       float4 box;
       int flags;
-      ld[q].finish(A, F, box, flags);
+      ld[q].finish(A, F, F.cull_open, box, flags);
       if (ld[q].mi == 0) box.x = kEmptyBox;
       lbox[k] = box;
       le0[k] = ld[q].e0;

@@ -69,8 +69,9 @@ struct FpConst {
   // Culling constants (psdf_cull.hpp): the smallest |v_l|; the distance above
   // which the axis test separates, with the rounding of its projections
   // divided by kappa; that or the largest sd of sets that are not separated;
-  // the relative rounding allowance of a bound.
-  float rmin, cull_tau, sd_floor, cull_rel;
+  // the relative rounding allowance of a bound; the tangent of half the largest
+  // exterior angle, with a margin (infinite for a sliver).
+  float rmin, cull_tau, sd_floor, cull_rel, cull_open;
 };
 
 // Four consecutive floats at any float address (global loads of several

@@ -24,9 +24,11 @@ namespace {
 // 21.1 / 19.0 us, 0.41 M 16.3 / 19.5, 1 x 1000003 31.2 / 27.2, 3.3 M 57 / 22;
 // m = 4: 0.82 M 18.2 / 18.8, 1.3 M 24.0 / 19.9; eight edges: 0.41 M
 // 32 / 28, 0.33 M 26 / 28, 3.3 M 98 / 38.
-bool cull_plain(int m, int mbar, int N, int M) {
-  const double cost = (double)N * M * (m <= 8 ? m : kMaxFp) * (obst_class(mbar) == 4 ? 1 : 2);
-  return cost >= 4.6e6;
+// A footprint without a bound (a needle) would have every obstacle evaluated.
+bool cull_plain(const FpConst& F, int mbar, int N, int M) {
+  const double cost =
+      (double)N * M * (F.m <= 8 ? F.m : kMaxFp) * (obst_class(mbar) == 4 ? 1 : 2);
+  return cost >= 4.6e6 && std::isfinite(F.cull_tau);
 }
 
 thread_local std::string g_err;
@@ -149,10 +151,13 @@ int prepare_footprint(const float* xy, int m, const psdf_params* params, FpConst
   f.rmax = (float)(rmax * (1.0 + 1e-6) + 1e-6);
   f.tau_sep = kappa > 1e-3 ? (float)((double)p.eps_sat / kappa + 1e-3) : INFINITY;
   f.rmin = (float)(rmin * (1.0 + 1e-6) + 1e-6);
-  f.cull_tau = kappa > 1e-3
+  // (a sliver's tau and rel are large before they are useless: 1.0 m and 0.2 at
+  // kappa = 1e-5)
+  f.cull_tau = kappa > 1e-5
                    ? (float)(((double)p.eps_sat + 4e-6 * (rmax + 1.0)) / kappa + 1e-3)
                    : INFINITY;
-  f.cull_rel = kappa > 1e-3 ? (float)(1e-5 + 2e-6 / kappa) : 1.0f;
+  f.cull_rel = kappa > 1e-5 ? (float)(1e-5 + 2e-6 / kappa) : 1.0f;
+  f.cull_open = kappa > 1e-3 ? (float)(1.01 * std::sqrt(1.0 - kappa * kappa) / kappa) : INFINITY;
   f.sd_floor = f.hard ? f.cull_tau
                       : std::fmax(f.cull_tau, (float)(1.001 * std::log((double)(m + kMaxObst)) / p.eta));
   for (int l = m; l < kMaxFp; ++l) {  // padded slots repeat slot m - 1
@@ -180,8 +185,8 @@ int check_edges(const psdf_edges* in, psdf_edges* out) {
   return PSDF_OK;
 }
 
-LaunchShape choose_shape(int m, int mbar, int N, int M) {
-  if (cull_plain(m, mbar, N, M)) {
+LaunchShape choose_shape(const FpConst& F, int mbar, int N, int M) {
+  if (cull_plain(F, mbar, N, M)) {
     // every stage block reads and bounds the segment's edges anew, so as few
     // blocks as cover the chip: four waves (stages) at a time
     const long segs = (M + kCullBlk - 1) / kCullBlk;
@@ -206,10 +211,10 @@ std::mutex g_shape_mu;
 LaunchShape g_override{0, 0};
 }  // namespace
 
-LaunchShape tuned_shape(int m, int mbar, int N, int M) {
+LaunchShape tuned_shape(const FpConst& F, int mbar, int N, int M) {
   std::lock_guard<std::mutex> lk(g_shape_mu);
   if (g_override.blk) return g_override;
-  return choose_shape(m, mbar, N, M);
+  return choose_shape(F, mbar, N, M);
 }
 
 namespace {

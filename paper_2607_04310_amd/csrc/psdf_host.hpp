@@ -43,11 +43,11 @@ bool timer_kernel_events(hipEvent_t* start, hipEvent_t* stop);
 
 // Default launch shape of the per-stage minimum for N stages and M obstacles
 // of at most mbar edges, and a footprint of m vertices.
-LaunchShape choose_shape(int m, int mbar, int N, int M);
+LaunchShape choose_shape(const FpConst& F, int mbar, int N, int M);
 
 // Launch shape for a problem: an explicit override (psdf_set_launch_shape),
 // else choose_shape.
-LaunchShape tuned_shape(int m, int mbar, int N, int M);
+LaunchShape tuned_shape(const FpConst& F, int mbar, int N, int M);
 
 hipError_t launch_plain(const FpConst& F, const float* poses, int N, const psdf_edges& e,
                         uint64_t* partial, const LaunchShape& ls, hipStream_t st);

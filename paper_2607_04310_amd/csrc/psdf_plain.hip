@@ -780,7 +780,7 @@ static int plain_run(const float* footprint, int32_t m, const float* poses, int3
     const EpiOut O{keys, nullptr, mode, 0.0f, d, edge, obst, grad, nullptr};
     return hip_status(PSDF_BY_MF(launch_small_mf, F, poses, N, e, O, stream));
   }
-  const LaunchShape ls = tuned_shape(F.m, e.mbar, N, e.M);
+  const LaunchShape ls = tuned_shape(F, e.mbar, N, e.M);
   uint64_t* partial = static_cast<uint64_t*>(ws);
   hipError_t err = launch_plain(F, poses, N, e, partial, ls, stream);
   if (err == hipSuccess)
@@ -806,7 +806,7 @@ int psdf_time_stage_min(const float* footprint, int32_t m, const float* poses, i
   if ((reinterpret_cast<uintptr_t>(ws) & 15u) != 0)
     return set_error(PSDF_EINVAL, "workspace is not 16-byte aligned");
   if (reps > 100000) return set_error(PSDF_EINVAL, "reps = %d, at most 100000", reps);
-  const LaunchShape ls = tuned_shape(F.m, e.mbar, N, e.M);
+  const LaunchShape ls = tuned_shape(F, e.mbar, N, e.M);
   uint64_t* partial = static_cast<uint64_t*>(ws);
   // one event pair per launch, recorded by the dispatch itself at its start
   // and end: the mean is the kernel's own duration, whatever the host's
@@ -925,7 +925,7 @@ int psdf_constraints(const float* footprint, int32_t m, const float* poses, int3
     const EpiOut O{keys, nullptr, 1, d_min, nullptr, nullptr, nullptr, nullptr, hj};
     err = PSDF_BY_MF(launch_small_mf, F, poses, N, e, O, stream);
   } else {
-    const LaunchShape ls = tuned_shape(F.m, e.mbar, N, e.M);
+    const LaunchShape ls = tuned_shape(F, e.mbar, N, e.M);
     uint64_t* partial = static_cast<uint64_t*>(ws);
     err = launch_plain(F, poses, N, e, partial, ls, stream);
     if (err == hipSuccess)

@@ -242,3 +242,70 @@ def test_plain_crowd_and_empty_segments():
     inst = SimpleNamespace(footprint=fp, poses=inputs.uniform_poses(rng, 100, -0.5, 0.5),
                            edges=rect, obst_off=off)
     _plain_check(inst)
+
+
+def _chain_map(rng, M, half, kind, scale=1.0):
+    """M obstacles that are not strictly convex polygons: chains of two to four
+    edges, rectangles with a corner in the middle of a side, arrowheads."""
+    rows = []
+    for i in range(M):
+        c, a = rng.uniform(-half, half, 2), rng.uniform(0, 2 * np.pi)
+        R = np.array([[np.cos(a), -np.sin(a)], [np.sin(a), np.cos(a)]])
+        if kind == "chains":
+            k = int(rng.integers(3, 6))
+            P = (c + scale * np.cumsum(rng.normal(0, 0.3, (k, 2)), 0)).astype(np.float32)
+            rows.append(np.concatenate([P[:-1], P[1:]], 1))
+        elif kind == "collinear":
+            w, h = scale * rng.uniform(0.1, 0.8, 2)
+            rows.append(_closed((c + np.array([[-w, -h], [w, -h], [0, h], [-w, h]]) @ R.T)
+                                if i % 2 else
+                                (c + np.array([[-w, 0], [0, 0], [w, 0], [0, h]]) @ R.T)))
+        else:
+            w, h = scale * rng.uniform(0.2, 0.8, 2)
+            rows.append(_closed(c + np.array([[-w, -h], [0, -h / 3], [w, -h], [0, h]]) @ R.T))
+    sizes = [len(r) for r in rows]
+    return np.concatenate(rows).astype(np.float32), inputs.csr_offsets(sizes)
+
+
+SLIVERS = [np.array([[-0.5, 0.0], [0.5, -w], [0.5, w]], np.float32)
+           for w in (0.02, 1e-3, 4e-4, 3e-5, 2e-6)]   # half exterior angles up to 90 - 1e-4 degrees
+
+
+@pytest.mark.parametrize("kind", ["chains", "collinear", "arrows"])
+def test_maps_without_convex_obstacles(kind):
+    """Batches and plain calls; footprints from blunt to needle."""
+    import torch
+    from paper_2607_04310_amd import api
+    rng = np.random.default_rng([11, len(kind)])
+    fps = [inputs.rect_footprint(), inputs.hexagon_footprint(rng),
+           inputs.random_convex_footprint(rng, 3)] + SLIVERS[:3]
+    insts = [_big(rng, fps[0])]
+    for k, fp in enumerate(fps):
+        edges, off = _chain_map(rng, 1800, 30.0, kind, scale=(1.0, 0.2, 4.0)[k % 3])
+        insts.append(SimpleNamespace(footprint=fp, poses=inputs.path_poses(rng, 20, -20, 20),
+                                     edges=edges, obst_off=off))
+    _check(insts, mbar=4)
+    for k, fp in enumerate(fps):
+        edges, off = _chain_map(rng, 30011, 80.0, kind)
+        es = api.EdgeSet(edges, off, 4)
+        poses = torch.tensor(inputs.uniform_poses(rng, 70, -80, 80)).cuda()
+        a = api.psdf_grad(fp, poses, es)
+        m = api.psdf_sd_matrix(fp, poses, es).min(1).values
+        assert torch.equal(a[0], m), (kind, k)
+
+
+@pytest.mark.parametrize("k", range(len(SLIVERS)))
+def test_sliver_footprints(k):
+    import torch
+    from paper_2607_04310_amd import api
+    rng = np.random.default_rng([12, k])
+    fp = SLIVERS[k]
+    insts = [_big(rng, inputs.rect_footprint()), _inst(rng, fp, 30, 1000, 15.0),
+             _inst(rng, fp, 30, 3000, 15.0, odd=ODD[:4])]
+    _check(insts)
+    es = api.EdgeSet(inputs.random_rects(rng, 30011, 0.1, 0.8, -60, 60),
+                     inputs.csr_offsets([4] * 30011), 4)
+    poses = torch.tensor(inputs.uniform_poses(rng, 70, -60, 60)).cuda()
+    a = api.psdf_grad(fp, poses, es)
+    m = api.psdf_sd_matrix(fp, poses, es).min(1).values
+    assert torch.equal(a[0], m)
