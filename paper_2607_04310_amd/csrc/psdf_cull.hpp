@@ -45,9 +45,9 @@
 //    obstacle has sd >= LB > T >= phi.  The wave then ends the stage
 //    (write_stage).
 // What it measured (graph replay per call, one card; full evaluation before):
-// 64 instances x 50 stages x 16384 rectangles 544 -> 43 us (list 17 us for
-// 67 MB of edges, stage 20 us), 512 uneven instances (23 800 stages, 2.7 M
-// edges) 581 -> 76 us (list 18, stage 58 us).
+// 64 instances x 50 stages x 16384 rectangles 539 -> 41 us (list 17.5 us for
+// 67 MB of edges, stage 19 us), 512 uneven instances (23 800 stages, 2.7 M
+// edges) 583 -> 72 us (list 19.5, stage 51 us).
 // Lists have a fixed place per segment and are rewritten by every call:
 // no counter to reset, nothing kept between calls, no capacity to exceed.
 #pragma once
@@ -614,11 +614,11 @@ __device__ __forceinline__ void cull_evaluate(const FpConst& F, const FpSlot* fs
 // One wave per stage, MI lanes per evaluated obstacle.  Bound by its chain
 // (list, footprint, candidates, the adjoint: 7 to 12 us) where the batch has
 // few stages, by VALU issue where it has many.  The footprint's slots in a
-// loop (group_sd) instead of an instance per footprint size: 79 VGPRs and six
+// loop (group_sd) instead of an instance per footprint size: 71 VGPRs and seven
 // waves per SIMD instead of 113 and four, and one launch for all sizes (512
 // uneven instances: stage 177 -> 55 us).  A second bound on the candidates,
 // and lists longer than the registers walked with four loads in flight, keep
-// the crowded stages short (64 x 50 x 16384: 36 -> 20 us).  The segments'
+// the crowded stages short (64 x 50 x 16384: 36 -> 19 us).  The segments'
 // lists are read as one: lane s holds the
 // length of segment s, their prefix sums place each segment's start as a bit
 // in LDS, and entry f's segment is the number of bits up to f.

@@ -1,7 +1,7 @@
 """The culled evaluation of a batch, and the bound-threshold screened call
 that takes it (with and without staged boxes), give the full evaluation's
 outputs bit for bit: instances at the edges of the segments and list rounds, obstacles
-that no bound covers (open chains, stars, degenerate edges, non-finite and
+with a loose bound or none (open chains, stars, degenerate edges, non-finite and
 huge coordinates, invalid ranges), footprints and constants at the ends of
 their ranges, non-finite poses, graph replays with changed inputs."""
 from types import SimpleNamespace
