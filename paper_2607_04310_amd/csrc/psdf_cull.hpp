@@ -389,8 +389,12 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
 
   int flags[kCullPer];
   // least upper bound of phi at every stage: an obstacle has a vertex on each
-  // side of its box (up to the enlargement), so one within the largest
-  // distance from B to the nearest-lying side
+  // side of its box, so one within the largest distance from B to the
+  // nearest-lying side.  The stored side is off by the enlargement and its
+  // rounding (e of cull_obstacle and half an ulp, in x and in y: at most 1.5
+  // times rel * size + 3.7e-7 * big), which is given back: without the second
+  // term footprints ahead of their origin lost their nearest obstacle by up to
+  // an ulp of the coordinates (6 cm at 600 km)
   float ub = __builtin_huge_valf();
 #pragma unroll
   for (int q = 0; q < kCullPer; ++q) {
@@ -405,7 +409,9 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
       const float y1 = fmaxf(fabsf(b.w - ply), fabsf(b.w - phy));
       const float xs = fminf(x0, x1), xl = fmaxf(x0, x1), ys = fminf(y0, y1), yl = fmaxf(y0, y1);
       const float far2 = fminf(fmaf(xs, xs, yl * yl), fmaf(xl, xl, ys * ys));
-      ub = fminf(ub, fmaf(4.0f * F.cull_rel, (b.z - b.x) + (b.w - b.y), sqrtf(far2)));
+      const float big = fmaxf(fmaxf(fabsf(b.x), fabsf(b.z)), fmaxf(fabsf(b.y), fabsf(b.w)));
+      const float off_side = fmaf(4.0f * F.cull_rel, (b.z - b.x) + (b.w - b.y), 6e-7f * big);
+      ub = fminf(ub, off_side + sqrtf(far2));
     }
   }
   ub = fw_min_f32(ub);
