@@ -100,6 +100,7 @@ __global__ __launch_bounds__(64 * kGeoWaves) void geom_bwd_kernel(
 #pragma unroll
   for (int q = 0; q < kSlots; ++q) G.tgt[lane][q] = -1;
   const EdgeArrays edges{ax, ay, bx, by, e0};
+  wave_sync();   // FL is written
   const WinnerPools wp =
       mi <= 4 ? winner_pools4(F, FL, G.w, edges, mi, cs, sn, px, py, true)
               : winner_pools(F, FL, G.w, edges, mi, cs, sn, px, py);

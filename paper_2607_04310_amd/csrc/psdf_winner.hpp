@@ -267,7 +267,9 @@ __device__ __forceinline__ uint32_t stride4_min(uint32_t x) {
 
 // At most four edges: lane 4 l + j holds robot slot l and edge j, so every
 // pair is one lane's (no index division, no LDS pass over the pairs).
-// stage: also writes the obstacle's geometry to W.
+// stage: also writes the obstacle's geometry to W.  FL must be visible to the
+// wave (a wave_sync or barrier after stage_footprint): every lane reads other
+// lanes' slots of it at once.
 template <class Edge>
 __device__ __forceinline__ WinnerPools winner_pools4(const FpConst& F, const FpLds& FL,
                                                      WinnerLds& W, Edge edge, int mi, float c,
@@ -343,7 +345,8 @@ __device__ __forceinline__ WinnerPools winner_pools4(const FpConst& F, const FpL
 }
 
 // Any edge count up to kMaxObst: the pairs strided over the lanes, the
-// obstacle's geometry (always written) and the per-edge minima in LDS.
+// obstacle's geometry (always written) and the per-edge minima in LDS.  FL must
+// be visible to the wave, as above.
 template <class Edge>
 __device__ __forceinline__ WinnerPools winner_pools(const FpConst& F, const FpLds& FL,
                                                     WinnerLds& W, Edge edge, int mi, float c,
