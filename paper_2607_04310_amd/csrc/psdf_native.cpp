@@ -9,7 +9,9 @@
 
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/device_lazy_init.h>
 
 #include <cmath>
 #include <cstring>
@@ -187,7 +189,13 @@ psdf_params params_of(PyObject* o) {
   return p;
 }
 
-hipStream_t stream() { return c10::hip::getCurrentHIPStream().stream(); }
+// torch's current stream.  A call on host tensors may be the process's first
+// use of the device: without it getCurrentHIPStream indexes per-device tables
+// that do not exist where there is no usable GPU (torch raises here).
+hipStream_t stream() {
+  torch::utils::device_lazy_init(at::kCUDA);
+  return c10::hip::getCurrentHIPStream().stream();
+}
 
 void check(int rc) {
   if (rc == PSDF_OK) return;
@@ -197,13 +205,14 @@ void check(int rc) {
   throw PyError();
 }
 
-// The call, with the interpreter lock released; the message of an error is
-// the thread's own, so it is read after the lock is back.
+// The call on torch's current stream, with the interpreter lock released; the
+// message of an error is the thread's own, so it is read after the lock is back.
 template <class F>
 void call(F f) {
+  const hipStream_t st = stream();
   int rc;
   Py_BEGIN_ALLOW_THREADS
-  rc = f();
+  rc = f(st);
   Py_END_ALLOW_THREADS
   check(rc);
 }
@@ -241,10 +250,10 @@ PyObject* eval(PyObject* const* a) {   // footprint, poses, edges, params, ws
   const at::Tensor d = empty(poses, at::kFloat, {N}), edge = empty(poses, at::kInt, {N}),
                    obst = empty(poses, at::kInt, {N}), keys = empty(poses, at::kLong, {N}),
                    ws = workspace(a[4], poses, N, e.c.M);
-  call([&] {
+  call([&](hipStream_t st) {
     return psdf_eval(fp.xy(), fp.m(), data<float>(poses), N, &e.c, &pr, data<float>(d),
                      data<int32_t>(edge), data<int32_t>(obst), data<uint64_t>(keys),
-                     data<void>(ws), (size_t)ws.numel(), stream());
+                     data<void>(ws), (size_t)ws.numel(), st);
   });
   return tuple({d, edge, obst, keys});
 }
@@ -272,10 +281,10 @@ PyObject* grad(PyObject* const* a) {   // footprint, poses, edges, params, out, 
     for (int k = 0; k < 5; ++k) o[k] = tensor(PySequence_Fast_GET_ITEM(s.get(), k));
   }
   const at::Tensor ws = workspace(a[5], poses, N, e.c.M);
-  call([&] {
+  call([&](hipStream_t st) {
     return psdf_grad(fp.xy(), fp.m(), data<float>(poses), N, &e.c, &pr, data<float>(o[0]),
                      data<int32_t>(o[1]), data<int32_t>(o[2]), data<float>(o[3]),
-                     data<uint64_t>(o[4]), data<void>(ws), (size_t)ws.numel(), stream());
+                     data<uint64_t>(o[4]), data<void>(ws), (size_t)ws.numel(), st);
   });
   if (a[4] == Py_None) return tuple({o[0], o[1], o[2], o[3], o[4]});
   Ref s = own(PySequence_Tuple(a[4]));   // the caller's tensors themselves
@@ -291,9 +300,9 @@ PyObject* bwd(PyObject* const* a) {   // footprint, poses, edges, keys, gout, pa
   const Edges e(a[2], true);
   const Footprint fp(a[0]);
   const at::Tensor gpose = empty(poses, at::kFloat, {N, 3});
-  call([&] {
+  call([&](hipStream_t st) {
     return psdf_bwd(fp.xy(), fp.m(), data<float>(poses), N, &e.c, &pr, data<uint64_t>(keys),
-                    data<float>(g), data<float>(gpose), stream());
+                    data<float>(g), data<float>(gpose), st);
   });
   return THPVariable_Wrap(gpose);
 }
@@ -319,10 +328,10 @@ PyObject* constraints(PyObject* const* a) {   // footprint, poses, edges, d_min,
   const Footprint fp(a[0]);
   const at::Tensor hj = empty(poses, at::kFloat, {N, 4}), keys = empty(poses, at::kLong, {N}),
                    ws = workspace(a[6], poses, N, e.c.M);
-  call([&] {
+  call([&](hipStream_t st) {
     return psdf_constraints(fp.xy(), fp.m(), data<float>(poses), N, &e.c, &pr, d_min,
                             data<float>(hj), host, data<uint64_t>(keys), data<void>(ws),
-                            (size_t)ws.numel(), stream());
+                            (size_t)ws.numel(), st);
   });
   return tuple({hj, keys});
 }
@@ -337,10 +346,10 @@ PyObject* bwd_geometry(PyObject* const* a) {   // footprint, poses, edges, keys,
   const Footprint fp(a[0]);
   const at::Tensor gedges = empty(poses, at::kFloat, {e.c.E, 4}),
                    gfp = empty(poses, at::kFloat, {fp.m(), 2});
-  call([&] {
+  call([&](hipStream_t st) {
     return psdf_bwd_geometry(fp.xy(), fp.m(), data<float>(poses), N, &e.c, &pr,
                              data<uint64_t>(keys), data<float>(g), data<float>(gedges),
-                             data<float>(gfp), stream());
+                             data<float>(gfp), st);
   });
   return tuple({gedges, gfp});
 }
@@ -352,9 +361,9 @@ PyObject* sd_matrix(PyObject* const* a) {   // footprint, poses, edges, params, 
   const Edges e(a[2], true);
   const Footprint fp(a[0]);
   const at::Tensor sd = a[4] == Py_None ? empty(poses, at::kFloat, {N, e.c.M}) : tensor(a[4]);
-  call([&] {
+  call([&](hipStream_t st) {
     return psdf_sd_matrix(fp.xy(), fp.m(), data<float>(poses), N, &e.c, &pr, data<float>(sd),
-                          stream());
+                          st);
   });
   if (a[4] == Py_None) return THPVariable_Wrap(sd);
   Py_INCREF(a[4]);
@@ -379,10 +388,10 @@ PyObject* encode_padded(PyObject* const* a) {   // A, B, S -> (ax, ay, bx, by, o
                    off = empty(S, at::kInt, {(int64_t)Mbar + 1});
   const size_t wsb = psdf_encode_ws_bytes(Mbar);
   const at::Tensor ws = empty(S, at::kByte, {(int64_t)(wsb > 1 ? wsb : 1)});
-  call([&] {
+  call([&](hipStream_t st) {
     return psdf_encode_padded(data<float>(A), data<float>(B), data<uint8_t>(S), Mbar, mbar,
                               data<float>(ax), data<float>(ay), data<float>(bx), data<float>(by),
-                              data<int32_t>(off), data<void>(ws), wsb, stream());
+                              data<int32_t>(off), data<void>(ws), wsb, st);
   });
   int64_t E = 0;
   if (Mbar > 0) {
@@ -399,24 +408,23 @@ PyObject* stage_edges(PyObject* const* a) {   // edges, params, table, PsdfStage
   const psdf_params pr = params_of(a[1]);
   const Edges e(a[0], false);
   const at::Tensor table = tensor(a[2]);
-  Py_buffer b;
-  if (PyObject_GetBuffer(a[3], &b, PyBUF_WRITABLE) != 0) throw PyError();
-  const bool ok = b.len == (Py_ssize_t)sizeof(psdf_staged);
-  psdf_staged st{};
-  if (ok) std::memcpy(&st, b.buf, sizeof st);
-  int rc = PSDF_OK;
-  if (ok) {
-    Py_BEGIN_ALLOW_THREADS
-    rc = psdf_stage_edges(&e.c, &pr, table.data_ptr(), (size_t)table.numel(), &st, stream());
-    Py_END_ALLOW_THREADS
-    std::memcpy(b.buf, &st, sizeof st);
-  }
-  PyBuffer_Release(&b);
-  if (!ok) {
+  struct Record {
+    Py_buffer b{};
+    ~Record() {
+      if (b.obj) PyBuffer_Release(&b);
+    }
+  } r;
+  if (PyObject_GetBuffer(a[3], &r.b, PyBUF_WRITABLE) != 0) throw PyError();
+  if (r.b.len != (Py_ssize_t)sizeof(psdf_staged)) {
     PyErr_SetString(PyExc_TypeError, "not a PsdfStaged record");
     throw PyError();
   }
-  check(rc);
+  psdf_staged* rec = static_cast<psdf_staged*>(r.b.buf);
+  psdf_staged out = *rec;
+  call([&](hipStream_t st) {
+    return psdf_stage_edges(&e.c, &pr, table.data_ptr(), (size_t)table.numel(), &out, st);
+  });
+  *rec = out;
   Py_RETURN_NONE;
 }
 
@@ -435,11 +443,11 @@ PyObject* mlp_train_step(PyObject* const* a) {
     const size_t n = psdf_mlp_ws_bytes(B);
     ws = empty(X, at::kByte, {(int64_t)(n > 4 ? n : 4)});
   }
-  call([&] {
+  call([&](hipStream_t st) {
     return psdf_mlp_train_step(data<float>(th), data<float>(m), data<float>(v), step, lr,
                                data<float>(X), data<float>(T), B,
                                loss.defined() ? data<float>(loss) : nullptr, data<void>(ws),
-                               (size_t)ws.numel(), stream());
+                               (size_t)ws.numel(), st);
   });
   Py_RETURN_NONE;
 }
@@ -454,6 +462,8 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
   try {
     return F(args);
   } catch (const PyError&) {
+  } catch (python_error& e) {
+    e.restore();
   } catch (const c10::Error& e) {
     PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
   } catch (const std::exception& e) {
