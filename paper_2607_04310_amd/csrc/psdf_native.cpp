@@ -205,15 +205,29 @@ void check(int rc) {
   throw PyError();
 }
 
+// The interpreter lock, released in a scope; back also when an exception (a
+// tensor without storage, an error of the device) leaves it.
+class Unlocked {
+ public:
+  Unlocked() : s_(PyEval_SaveThread()) {}
+  Unlocked(const Unlocked&) = delete;
+  Unlocked& operator=(const Unlocked&) = delete;
+  ~Unlocked() { PyEval_RestoreThread(s_); }
+
+ private:
+  PyThreadState* s_;
+};
+
 // The call on torch's current stream, with the interpreter lock released; the
 // message of an error is the thread's own, so it is read after the lock is back.
 template <class F>
 void call(F f) {
   const hipStream_t st = stream();
   int rc;
-  Py_BEGIN_ALLOW_THREADS
-  rc = f(st);
-  Py_END_ALLOW_THREADS
+  {
+    const Unlocked unlocked;
+    rc = f(st);
+  }
   check(rc);
 }
 
@@ -395,11 +409,8 @@ PyObject* encode_padded(PyObject* const* a) {   // A, B, S -> (ax, ay, bx, by, o
   });
   int64_t E = 0;
   if (Mbar > 0) {
-    int32_t last = 0;
-    Py_BEGIN_ALLOW_THREADS
-    last = off.select(0, Mbar).item<int32_t>();
-    Py_END_ALLOW_THREADS
-    E = last;
+    const Unlocked unlocked;
+    E = off.select(0, Mbar).item<int32_t>();
   }
   return tuple({ax.slice(0, 0, E), ay.slice(0, 0, E), bx.slice(0, 0, E), by.slice(0, 0, E), off});
 }

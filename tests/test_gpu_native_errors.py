@@ -1,0 +1,48 @@
+"""Errors inside the native calls reach the caller as the exceptions that the
+same arguments raise in Python, and the interpreter goes on."""
+import numpy as np
+import pytest
+
+from paper_2607_04310_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture()
+def scene():
+    import torch
+    from paper_2607_04310_amd import api
+    inst = inputs.c1(0)
+    es = api.EdgeSet(inst.edges, inst.obst_off)
+    return api, torch, inst, es, torch.tensor(inst.poses, device="cuda")
+
+
+def _sparse(torch, n, dtype):
+    """A tensor without storage: its data pointer cannot be taken."""
+    return torch.sparse_coo_tensor(torch.zeros(1, 0, dtype=torch.long), torch.zeros(0, dtype=dtype),
+                                   (n,)).cuda()
+
+
+def test_tensors_without_a_pointer(scene):
+    api, torch, inst, es, poses = scene
+    want = api.psdf_grad(inst.footprint, poses, es)
+    N = poses.shape[0]
+    out = [torch.empty_like(t) for t in want]
+    out[0] = _sparse(torch, N, torch.float32)
+    for _ in range(3):
+        with pytest.raises(RuntimeError):
+            api.psdf_grad(inst.footprint, poses, es, out=out)
+    with pytest.raises(RuntimeError):
+        api.psdf_sd_matrix(inst.footprint, poses, es, out=out[0])
+    th = torch.zeros(4545, device="cuda")
+    X = torch.zeros(16, 4, device="cuda")
+    with pytest.raises(RuntimeError):
+        api.mlp_train_step(th, th.clone(), th.clone(), 1, 1e-3, X, X[:, 0].contiguous(),
+                           loss=_sparse(torch, 1, torch.float32))
+    # a NULL pointer is the library's to refuse
+    out[0] = torch.empty(N, device="meta")
+    with pytest.raises(api.PsdfError) as e:
+        api.psdf_grad(inst.footprint, poses, es, out=out)
+    assert e.value.code == -1
+    got = api.psdf_grad(inst.footprint, poses, es)
+    assert all(torch.equal(g, w) for g, w in zip(got, want))
