@@ -68,6 +68,15 @@ double as_double(PyObject* o) {
   return v;
 }
 
+// int(o) as a C int32 argument, float(o)
+int32_t int_of(PyObject* o) {
+  const Ref r = own(PyNumber_Long(o));
+  const unsigned long v = PyLong_AsUnsignedLongMask(r.get());
+  if (PyErr_Occurred()) throw PyError();
+  return (int32_t)v;
+}
+float float_of(PyObject* o) { return (float)as_double(own(PyNumber_Float(o)).get()); }
+
 // api.<name>(o)
 Ref convert(const char* name, PyObject* o) {
   Ref f = own(PyObject_GetAttrString(g_api, name));
@@ -324,7 +333,7 @@ PyObject* bwd(PyObject* const* a) {   // footprint, poses, edges, keys, gout, pa
 PyObject* constraints(PyObject* const* a) {   // footprint, poses, edges, d_min, params, host, ws
   const at::Tensor poses = poses_of(a[1]);
   const int32_t N = (int32_t)poses.size(0);
-  const float d_min = (float)as_double(a[3]);
+  const float d_min = float_of(a[3]);
   const psdf_params pr = params_of(a[4]);
   float* host = nullptr;
   at::Tensor h;
@@ -443,8 +452,8 @@ PyObject* stage_edges(PyObject* const* a) {   // edges, params, table, PsdfStage
 PyObject* mlp_train_step(PyObject* const* a) {
   const at::Tensor th = tensor(a[0]), m = tensor(a[1]), v = tensor(a[2]), X = tensor(a[5]),
                    T = tensor(a[6]);
-  const int32_t step = (int32_t)as_long(a[3]);
-  const float lr = (float)as_double(a[4]);
+  const int32_t step = int_of(a[3]);
+  const float lr = float_of(a[4]);
   const int32_t B = (int32_t)X.size(0);
   at::Tensor loss, ws;
   if (a[7] != Py_None) loss = tensor(a[7]);

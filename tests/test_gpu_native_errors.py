@@ -46,3 +46,23 @@ def test_tensors_without_a_pointer(scene):
     assert e.value.code == -1
     got = api.psdf_grad(inst.footprint, poses, es)
     assert all(torch.equal(g, w) for g, w in zip(got, want))
+
+
+def test_numbers_in_any_form(scene):
+    api, torch, inst, es, poses = scene
+    rng = np.random.default_rng(0)
+    X = torch.tensor(rng.normal(size=(64, 4)).astype(np.float32), device="cuda")
+    T = X[:, 0].contiguous()
+    start = torch.tensor(rng.normal(0, 0.3, 4545).astype(np.float32), device="cuda")
+    res = []
+    for step, lr in ((5, 1e-3), (5.0, "1e-3"), (np.float32(5.9), np.float64(1e-3)),
+                     (torch.tensor(5), torch.tensor(1e-3, dtype=torch.float64))):
+        th, m, v = start.clone(), torch.zeros_like(start), torch.zeros_like(start)
+        api.mlp_train_step(th, m, v, step, lr, X, T)
+        res.append(th)
+    assert not torch.equal(res[0], start)
+    assert all(torch.equal(r, res[0]) for r in res[1:])
+    want = api.psdf_constraints(inst.footprint, poses, es, 0.25)
+    for d_min in ("0.25", np.float32(0.25), torch.tensor([0.25])):
+        got = api.psdf_constraints(inst.footprint, poses, es, d_min)
+        assert all(torch.equal(g, w) for g, w in zip(got, want))

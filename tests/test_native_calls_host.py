@@ -37,3 +37,12 @@ def test_no_device(name):
     r = _run(CALLS[name])
     assert r.returncode == 0, (r.returncode, r.stderr[-500:])
     assert r.stdout.startswith("RuntimeError") and "GPU" in r.stdout, r.stdout
+
+
+@pytest.mark.parametrize("step", ["500.0", "np.float32(7)", "torch.tensor(3.0)", "True", "'12'"])
+def test_step_and_rate_convert_as_int_and_float(step):
+    """step and lr are int(step) and float(lr): any of these forms gets as far
+    as the missing device."""
+    r = _run(f"""th = torch.zeros(4545)
+api.mlp_train_step(th, th.clone(), th.clone(), {step}, '1e-3', torch.zeros(4, 4), torch.zeros(4))""")
+    assert r.returncode == 0 and r.stdout.startswith("RuntimeError"), (r.stdout, r.stderr[-300:])
