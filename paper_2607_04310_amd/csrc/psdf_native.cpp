@@ -17,6 +17,7 @@
 #include <cstring>
 #include <stdexcept>
 #include <string>
+#include <utility>
 
 #include "psdf.h"
 
@@ -30,7 +31,10 @@ class Ref {
   explicit Ref(PyObject* p = nullptr) : p_(p) {}
   Ref(Ref&& o) noexcept : p_(o.p_) { o.p_ = nullptr; }
   Ref(const Ref&) = delete;
-  Ref& operator=(const Ref&) = delete;
+  Ref& operator=(Ref&& o) noexcept {
+    std::swap(p_, o.p_);
+    return *this;
+  }
   ~Ref() { Py_XDECREF(p_); }
   PyObject* get() const { return p_; }
   PyObject* release() {
@@ -288,6 +292,7 @@ PyObject* grad(PyObject* const* a) {   // footprint, poses, edges, params, out, 
   const Edges e(a[2], true);
   const Footprint fp(a[0]);
   at::Tensor o[5];   // d, edge, obst, grad, keys
+  Ref given;         // the caller's tensors themselves, read once: out may be an iterator
   if (a[4] == Py_None) {
     o[0] = empty(poses, at::kFloat, {N});
     o[1] = empty(poses, at::kInt, {N});
@@ -295,13 +300,13 @@ PyObject* grad(PyObject* const* a) {   // footprint, poses, edges, params, out, 
     o[3] = empty(poses, at::kFloat, {N, 3});
     o[4] = empty(poses, at::kLong, {N});
   } else {
-    Ref s = own(PySequence_Fast(a[4], "out is not a sequence of five tensors"));
-    if (PySequence_Fast_GET_SIZE(s.get()) != 5) {
+    given = own(PySequence_Tuple(a[4]));
+    if (PyTuple_GET_SIZE(given.get()) != 5) {
       PyErr_Format(PyExc_ValueError, "out holds %zd tensors, 5 wanted (d, edge, obst, grad, keys)",
-                   PySequence_Fast_GET_SIZE(s.get()));
+                   PyTuple_GET_SIZE(given.get()));
       throw PyError();
     }
-    for (int k = 0; k < 5; ++k) o[k] = tensor(PySequence_Fast_GET_ITEM(s.get(), k));
+    for (int k = 0; k < 5; ++k) o[k] = tensor(PyTuple_GET_ITEM(given.get(), k));
   }
   const at::Tensor ws = workspace(a[5], poses, N, e.c.M);
   call([&](hipStream_t st) {
@@ -309,9 +314,7 @@ PyObject* grad(PyObject* const* a) {   // footprint, poses, edges, params, out, 
                      data<int32_t>(o[1]), data<int32_t>(o[2]), data<float>(o[3]),
                      data<uint64_t>(o[4]), data<void>(ws), (size_t)ws.numel(), st);
   });
-  if (a[4] == Py_None) return tuple({o[0], o[1], o[2], o[3], o[4]});
-  Ref s = own(PySequence_Tuple(a[4]));   // the caller's tensors themselves
-  return s.release();
+  return given.get() ? given.release() : tuple({o[0], o[1], o[2], o[3], o[4]});
 }
 
 PyObject* bwd(PyObject* const* a) {   // footprint, poses, edges, keys, gout, params

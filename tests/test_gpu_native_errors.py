@@ -66,3 +66,18 @@ def test_numbers_in_any_form(scene):
     for d_min in ("0.25", np.float32(0.25), torch.tensor([0.25])):
         got = api.psdf_constraints(inst.footprint, poses, es, d_min)
         assert all(torch.equal(g, w) for g, w in zip(got, want))
+
+
+def test_out_as_any_iterable(scene):
+    api, torch, inst, es, poses = scene
+    want = api.psdf_grad(inst.footprint, poses, es)
+    own = [torch.empty_like(t) for t in want]
+    for out in ((t for t in own), dict(enumerate(own)).values(), iter(own), own, tuple(own)):
+        for t in own:
+            t.zero_()
+        got = api.psdf_grad(inst.footprint, poses, es, out=out)
+        assert len(got) == 5 and all(g is o for g, o in zip(got, own))
+        assert all(torch.equal(g, w) for g, w in zip(got, want))
+    for out in (iter(own[:4]), own + own[:1], [], 3):
+        with pytest.raises((ValueError, TypeError)):
+            api.psdf_grad(inst.footprint, poses, es, out=out)
