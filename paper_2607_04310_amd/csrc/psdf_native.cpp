@@ -15,7 +15,7 @@
 
 #include <cmath>
 #include <cstring>
-#include <stdexcept>
+#include <exception>
 #include <string>
 #include <utility>
 
@@ -341,8 +341,10 @@ PyObject* constraints(PyObject* const* a) {   // footprint, poses, edges, d_min,
   float* host = nullptr;
   at::Tensor h;
   if (a[5] != Py_None) {
-    h = tensor(a[5]);
-    if (h.scalar_type() != at::kFloat || h.dim() != 2 || h.size(0) != N || h.size(1) != 4 ||
+    const bool is_tensor = THPVariable_Check(a[5]);
+    if (is_tensor) h = tensor(a[5]);
+    else own(PyObject_GetAttrString(a[5], "dtype"));   // an array is a value error, as below
+    if (!is_tensor || h.scalar_type() != at::kFloat || h.dim() != 2 || h.size(0) != N || h.size(1) != 4 ||
         !h.is_contiguous() || h.is_cuda()) {
       PyErr_SetString(PyExc_ValueError,
                       "host must be a contiguous CPU float32 tensor of shape (N, 4)");
@@ -485,14 +487,8 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
   try {
     return F(args);
   } catch (const PyError&) {
-  } catch (python_error& e) {
-    e.restore();
-  } catch (const c10::Error& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
-  } catch (...) {
-    PyErr_SetString(PyExc_RuntimeError, "unknown C++ exception");
+  } catch (...) {   // as torch's own calls raise it (OutOfMemoryError, IndexError, ...)
+    torch::translate_exception_to_python(std::current_exception());
   }
   return nullptr;
 }

@@ -81,3 +81,16 @@ def test_out_as_any_iterable(scene):
     for out in (iter(own[:4]), own + own[:1], [], 3):
         with pytest.raises((ValueError, TypeError)):
             api.psdf_grad(inst.footprint, poses, es, out=out)
+
+
+def test_exception_classes(scene):
+    api, torch, inst, es, poses = scene
+    M = 1 << 20   # sd would take 262140 x 2^20 floats, more than the card holds
+    es = api.EdgeSet(np.tile(inst.edges[:1], (M, 1)), np.arange(M + 1, dtype=np.int32), 1)
+    many = torch.zeros(262140, 3, device="cuda")
+    with pytest.raises(torch.OutOfMemoryError):
+        api.psdf_sd_matrix(inst.footprint, many, es)
+    with pytest.raises(ValueError):
+        api.psdf_constraints(inst.footprint, poses, es, 0.0, host=np.zeros((poses.shape[0], 4), np.float32))
+    with pytest.raises(IndexError):
+        api.psdf_encode_padded(poses, poses, poses[:, 0])

@@ -46,3 +46,10 @@ def test_step_and_rate_convert_as_int_and_float(step):
     r = _run(f"""th = torch.zeros(4545)
 api.mlp_train_step(th, th.clone(), th.clone(), {step}, '1e-3', torch.zeros(4, 4), torch.zeros(4))""")
     assert r.returncode == 0 and r.stdout.startswith("RuntimeError"), (r.stdout, r.stderr[-300:])
+
+
+def test_exception_types():
+    """What torch raises keeps its class (a 0-dimensional X has no rows)."""
+    r = _run("""th = torch.zeros(4545)
+api.mlp_train_step(th, th.clone(), th.clone(), 1, 1e-3, torch.tensor(1.0), torch.zeros(1))""")
+    assert r.returncode == 0 and r.stdout.startswith("IndexError"), (r.stdout, r.stderr[-300:])
