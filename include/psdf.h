@@ -338,8 +338,10 @@ enum {
  * that the instances' stage rows [pose_off, pose_off + N) tile the packed
  * rows [0, sum N) (else PSDF_EINVAL),
  * allocates the plan's device tables and scratch (freed by
- * psdf_batch_plan_destroy) on the current device.  Calls that use one plan
- * must not overlap in time (the plan's scratch is shared). */
+ * psdf_batch_plan_destroy) on the current device; where the tables of the
+ * culled evaluation (64 bytes per obstacle) do not fit, the plan takes the full
+ * evaluation.  Calls that use one plan must not overlap in time (the plan's
+ * scratch is shared). */
 int psdf_batch_plan_create(psdf_batch_plan** plan, const psdf_batch_desc* desc, int32_t n_inst,
                            const float* footprints, int32_t mbar, const psdf_params* params,
                            int32_t flags);

@@ -426,6 +426,21 @@ bool cull_pays(const psdf_batch_plan& p) {
   return pairs >= kCullPairs && pairs >= kCullObstacles * p.total_stages;
 }
 
+// Gives the culled evaluation's tables back: the plan takes the full one.
+void cull_free(psdf_batch_plan* p) {
+  (void)hipFree(p->d_frows);
+  (void)hipFree(p->d_segs);
+  (void)hipFree(p->d_cstages);
+  (void)hipFree(p->d_crec);
+  (void)hipFree(p->d_ccnt);
+  p->d_frows = nullptr;
+  p->d_segs = nullptr;
+  p->d_cstages = nullptr;
+  p->d_crec = nullptr;
+  p->d_ccnt = nullptr;
+  p->cull_ready = p->culled = false;
+}
+
 // Segments, stage records and lists of the culled evaluation.
 hipError_t cull_create(psdf_batch_plan* p) {
   std::vector<CullSeg> segs;
@@ -858,13 +873,9 @@ void psdf_batch_plan_destroy(psdf_batch_plan* p) {
   (void)hipFree(p->d_frag);
   (void)hipFree(p->d_hcount);
   (void)hipFree(p->d_hrest);
-  (void)hipFree(p->d_frows);
-  (void)hipFree(p->d_segs);
-  (void)hipFree(p->d_cstages);
-  (void)hipFree(p->d_crec);
   (void)hipFree(p->d_sbox);
   (void)hipFree(p->d_srec);
-  (void)hipFree(p->d_ccnt);
+  cull_free(p);
   (void)hipSetDevice(cur);
   delete p;
 }
@@ -1035,9 +1046,18 @@ int psdf_batch_plan_create(psdf_batch_plan** out, const psdf_batch_desc* desc, i
   if (rc) { psdf_batch_plan_destroy(p); return rc; }
   if (!(flags & PSDF_BATCH_EXHAUSTIVE) && p->sum_M + kCullPad < 0x7fffffffu &&
       (sh.cull == 1 || cull_pays(*p))) {
-    rc = hip_status(cull_create(p));
-    if (rc) { psdf_batch_plan_destroy(p); return rc; }
-    p->culled = sh.cull != 0;
+    const hipError_t ce = cull_create(p);
+    if (ce == hipErrorOutOfMemory) {
+      // the full evaluation needs none of these tables (64 bytes per obstacle)
+      cull_free(p);
+      (void)hipGetLastError();
+    } else if (ce != hipSuccess) {
+      rc = hip_status(ce);
+      psdf_batch_plan_destroy(p);
+      return rc;
+    } else {
+      p->culled = sh.cull != 0;
+    }
   }
   *out = p;
   return PSDF_OK;
