@@ -464,9 +464,9 @@ int psdf_batch_screened_bound(psdf_batch_plan* plan, const float* poses, const f
  * changing them in place, stage again (a stale circle can make the
  * certificate exclude the true winner).  The first call allocates device
  * memory held by the plan: 16 bytes per obstacle for the circles and
- * 40 * edge class + 16 bytes for the rows, and 80 bytes for the boxes and
- * records of a batch that psdf_batch culls; each call enqueues one or two
- * kernels on `stream`.  Same limits as psdf_batch_screened. */
+ * 40 * edge class + 16 bytes for the rows, and, where they fit, 80 bytes for the
+ * boxes and records of a batch that psdf_batch culls; each call enqueues one or
+ * two kernels on `stream`.  Same limits as psdf_batch_screened. */
 int psdf_batch_stage(psdf_batch_plan* plan, const float* ax, const float* ay, const float* bx,
                      const float* by, const int32_t* obst_off, hipStream_t stream);
 

@@ -92,6 +92,7 @@ struct psdf_batch_plan {
   CullRec* d_crec = nullptr;
   float4* d_sbox = nullptr;     // taken once per edge set (psdf_batch_stage)
   CullRec* d_srec = nullptr;
+  bool box_staged = false;      // the last staging took them
   int* d_ccnt = nullptr;
   // graph
   hipStream_t cap_stream = nullptr;
@@ -496,6 +497,20 @@ hipError_t cull_create(psdf_batch_plan* p) {
   return err;
 }
 
+// Room for the staged boxes and records (80 bytes per obstacle); without it the
+// culled form reads the edges, and staging takes the circles and rows alone.
+bool stage_boxes(psdf_batch_plan* p) {
+  if (p->d_sbox) return true;
+  if (hipMalloc(&p->d_sbox, p->sum_M * sizeof(float4)) == hipSuccess) {
+    if (hipMalloc(&p->d_srec, p->sum_M * sizeof(CullRec)) == hipSuccess) return true;
+    (void)hipFree(p->d_sbox);
+  }
+  p->d_sbox = nullptr;
+  p->d_srec = nullptr;
+  (void)hipGetLastError();
+  return false;
+}
+
 // staged: from the boxes and records taken by psdf_batch_stage.
 hipError_t cull_enqueue(psdf_batch_plan* p, const CullArgs& a, bool staged, hipStream_t st) {
   if (p->n_segs > 0) {
@@ -686,7 +701,7 @@ static int screened_run(psdf_batch_plan* p, bool bound, const float* theta, int3
     timer_begin(stream);
     const hipError_t e = cull_enqueue(
         p, cull_args(p, poses, ax, ay, bx, by, off, d, edge, obst, grad, keys),
-        p->circ_staged, stream);
+        p->circ_staged && p->box_staged, stream);
     timer_end(stream);
     return hip_status(e);
   }
@@ -785,15 +800,8 @@ int psdf_batch_stage(psdf_batch_plan* p, const float* ax, const float* ay, const
       err = hipMalloc(&p->d_rows, p->sum_M * (size_t)(40 * p->mi_class + 16));
       if (err != hipSuccess) p->d_rows = nullptr;
     }
-    if (err == hipSuccess && p->cull_ready && !p->d_sbox) {
-      err = hipMalloc(&p->d_sbox, p->sum_M * sizeof(float4));
-      if (err != hipSuccess) p->d_sbox = nullptr;
-    }
-    if (err == hipSuccess && p->cull_ready && !p->d_srec) {
-      err = hipMalloc(&p->d_srec, p->sum_M * sizeof(CullRec));
-      if (err != hipSuccess) p->d_srec = nullptr;
-    }
     if (err != hipSuccess) return hip_status(err);
+    const bool boxes = p->cull_ready && stage_boxes(p);
     const dim3 grid((p->max_M + 255) / 256, p->n_inst);
 #define PSDF_STAGE_BATCH(MI)                                                               \
   stage_batch_kernel<MI><<<grid, 256, 0, stream>>>(p->d_fp, p->d_inst, ax, ay, bx, by, off, \
@@ -802,7 +810,7 @@ int psdf_batch_stage(psdf_batch_plan* p, const float* ax, const float* ay, const
     else if (p->mi_class == 8) PSDF_STAGE_BATCH(8);
     else PSDF_STAGE_BATCH(16);
 #undef PSDF_STAGE_BATCH
-    if (p->cull_ready) {
+    if (boxes) {
       const CullArgs ca = cull_args(p, nullptr, ax, ay, bx, by, off, nullptr, nullptr, nullptr,
                                     nullptr, nullptr);
       // a grid's second dimension holds 65535 segments
@@ -817,6 +825,7 @@ int psdf_batch_stage(psdf_batch_plan* p, const float* ax, const float* ay, const
     }
     err = hipGetLastError();
     if (err != hipSuccess) return hip_status(err);
+    p->box_staged = boxes;
   }
   p->circ_staged = true;
   const void* src[5] = {ax, ay, bx, by, off};

@@ -50,7 +50,7 @@ void fake_clear() { launches.clear(); }
 // ---- the runtime
 int hipMalloc(void** p, size_t n) {
   *p = nullptr;
-  if (mallocs++ == fail_at || n > limit - used) return last_error = kOutOfMemory;
+  if (mallocs++ == fail_at || used > limit || n > limit - used) return last_error = kOutOfMemory;
   *p = std::calloc(1, n ? n : 1);
   blocks[*p] = n;
   used += n;

@@ -55,3 +55,24 @@ emit(out)
     rest = got[5:]
     assert rest.count(["batch_kernel", True]) == 5          # the five culled tables
     assert rest.count(["batch_kernel", True]) + rest.count(["cull_list", True]) == len(rest)
+
+
+def test_no_room_for_the_staged_boxes(tmp_path_factory):
+    """Staging takes the circles and rows, as it did, where the boxes and records
+    of the culled form do not fit; the bound form then reads the edges."""
+    got = script("""
+insts = [(HEX, 300, 16384, 65536)]
+out = []
+rc, p = plan(insts)
+before = hip.fake_used()
+rows = 16384 * (16 + 40 * 4 + 16)
+for limit in (before + rows, before + rows + 16 * 16384, before + rows + 80 * 16384):
+    hip.fake_limit(limit)
+    out.append([*stage(p), hip.fake_used() - before, bound(p), run(p)])
+lib.psdf_batch_plan_destroy(p)
+emit([out, hip.fake_used()])
+""", tmp_path_factory)
+    rows, both = 16384 * 192, ["cull_list", "cull_stage_kernel"]
+    assert got[1] == 0
+    assert got[0] == [[0, ["other"], rows, both, both], [0, ["other"], rows, both, both],
+                      [0, ["other", "cull_stage_edges"], rows + 80 * 16384, both, both]]
