@@ -36,8 +36,9 @@ def launches():
     return out
 
 
-def kernels(words=("cull_list", "cull_stage_kernel", "cull_stage_edges", "cull_main", "batch_kernel",
-                   "screen_bound", "main_staged", "main_kernel", "small_quad", "small_kernel")):
+def kernels(words=("cull_list", "cull_stage_kernel", "cull_stage_edges", "cull_main", "stage_batch",
+                   "batch_kernel", "screen_bound", "main_staged", "main_kernel", "small_quad",
+                   "small_kernel")):
     """The launches by the kernels' names (mangled names hold them)."""
     return [next((w for w in words if w in k[0]), "other") for k in launches()]
 

@@ -74,5 +74,5 @@ emit([out, hip.fake_used()])
 """, tmp_path_factory)
     rows, both = 16384 * 192, ["cull_list", "cull_stage_kernel"]
     assert got[1] == 0
-    assert got[0] == [[0, ["other"], rows, both, both], [0, ["other"], rows, both, both],
-                      [0, ["other", "cull_stage_edges"], rows + 80 * 16384, both, both]]
+    assert got[0] == [[0, ["stage_batch"], rows, both, both], [0, ["stage_batch"], rows, both, both],
+                      [0, ["stage_batch", "cull_stage_edges"], rows + 80 * 16384, both, both]]
