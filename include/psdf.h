@@ -373,10 +373,11 @@ int psdf_batch(psdf_batch_plan* plan, const float* poses, const float* ax, const
  * item) on `stream` as a burst of back-to-back calls, in two rounds over
  * all candidates after ten warm-up calls (the better burst counts),
  * synchronising it (and, where psdf_batch would be culled, that form),
- * keeps the fastest in the plan and in a
- * process-wide cache keyed by the batch's size signature (later plans of the
+ * keeps the fastest in the plan, and the fastest shape of the full evaluation in
+ * a process-wide cache keyed by the batch's size signature (later plans of the
  * same signature start from it; with PSDF_TUNE_CACHE set to a file path the
- * cache is also read from and appended to that file).  Outputs are left
+ * cache is also read from and appended to that file).  Whether the culled form
+ * was the faster holds for this plan alone.  Outputs are left
  * holding a valid result.  best_ms (host, may be NULL) gets the best time. */
 int psdf_batch_autotune(psdf_batch_plan* plan, const float* poses, const float* ax,
                         const float* ay, const float* bx, const float* by,

@@ -24,10 +24,6 @@ struct Shape {
   int sb;       // stages per work item
   int nw;       // waves per work-group (obstacles per tile = 64 nw)
   int direct;   // 1: one work-group per item instead of a persistent grid
-  // what the autotuner chose: -1 not tuned (the size rule decides), 0 this
-  // shape, 1 the culled evaluation; in the cache file 2 * (cull + 1) is added
-  // to direct, so that a line without it leaves the choice to the size rule
-  int cull = -1;
 };
 
 }  // namespace psdf
@@ -134,9 +130,11 @@ void cache_load_locked() {
   if (!f) return;
   char key[128];
   int sb, nw, direct;
+  // (a last number of 2 to 5 was direct plus the tuned form times two: the form
+  // is the plan's own, see psdf_batch_autotune)
   while (std::fscanf(f, "%127s %d %d %d", key, &sb, &nw, &direct) == 4)
     if (sb >= 1 && sb <= kMaxStageBlock && (nw == 1 || nw == 4) && direct >= 0 && direct <= 5)
-      g_cache[key] = Shape{sb, nw, direct & 1, direct / 2 - 1};
+      g_cache[key] = Shape{sb, nw, direct & 1};
   std::fclose(f);
 }
 
@@ -146,7 +144,7 @@ void cache_store(const std::string& key, Shape s) {
   g_cache[key] = s;
   if (const char* path = std::getenv("PSDF_TUNE_CACHE")) {
     if (FILE* f = std::fopen(path, "a")) {
-      std::fprintf(f, "%s %d %d %d\n", key.c_str(), s.sb, s.nw, s.direct + 2 * (s.cull + 1));
+      std::fprintf(f, "%s %d %d %d\n", key.c_str(), s.sb, s.nw, s.direct);
       std::fclose(f);
     }
   }
@@ -1053,8 +1051,7 @@ int psdf_batch_plan_create(psdf_batch_plan** out, const psdf_batch_desc* desc, i
   }
   int rc = build_items(p, sh);
   if (rc) { psdf_batch_plan_destroy(p); return rc; }
-  if (!(flags & PSDF_BATCH_EXHAUSTIVE) && p->sum_M + kCullPad < 0x7fffffffu &&
-      (sh.cull == 1 || cull_pays(*p))) {
+  if (!(flags & PSDF_BATCH_EXHAUSTIVE) && p->sum_M + kCullPad < 0x7fffffffu && cull_pays(*p)) {
     const hipError_t ce = cull_create(p);
     if (ce == hipErrorOutOfMemory) {
       // the full evaluation needs none of these tables (64 bytes per obstacle)
@@ -1065,7 +1062,7 @@ int psdf_batch_plan_create(psdf_batch_plan** out, const psdf_batch_desc* desc, i
       psdf_batch_plan_destroy(p);
       return rc;
     } else {
-      p->culled = sh.cull != 0;
+      p->culled = true;
     }
   }
   *out = p;
@@ -1148,8 +1145,9 @@ int psdf_batch_autotune(psdf_batch_plan* p, const float* poses, const float* ax,
   Shape best_sh = p->shape;
   for (int cand = 0; cand < kCand; ++cand)
     if (t_best[cand] < best) { best = t_best[cand]; best_sh = shape_of(cand); }
-  best_sh.cull = p->cull_ready ? (t_cull < best ? 1 : 0) : -1;
-  p->culled = rc ? was_culled : best_sh.cull == 1;
+  // the form is this plan's own: which is faster depends on the map and the
+  // footprints, and the cache's signature knows sizes only
+  p->culled = rc ? was_culled : t_cull < best;
   best = std::min(best, t_cull);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);

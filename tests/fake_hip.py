@@ -66,6 +66,11 @@ def run(p):
     return kernels()
 
 
+def autotune(p):
+    assert lib.psdf_batch_autotune(p, *[ONE] * 11, None, None) == 0
+    launches()
+
+
 def bound(p):
     assert lib.psdf_batch_screened_bound(p, *[ONE] * 11, None, None, None, None) == 0
     return kernels()

@@ -26,7 +26,7 @@ std::map<const void*, std::string>& names() {
 }
 std::map<void*, size_t> blocks;
 size_t used = 0, limit = ~size_t(0);
-long fail_at = -1, mallocs = 0;
+long fail_at = -1, mallocs = 0, launched = 0;
 int last_error = kOk;
 std::vector<Config> configs;
 std::string launches;
@@ -36,6 +36,7 @@ void note(const void* f, Dim3 g, Dim3 b) {
   char buf[96];
   std::snprintf(buf, sizeof buf, " %u %u %u\n", g.x, g.y, b.x);
   launches += names()[f] + buf;
+  ++launched;
 }
 }  // namespace
 
@@ -94,24 +95,40 @@ int hipGetSymbolAddress(void** p, const void*) {
   *p = symbol;
   return kOk;
 }
+// a kernel takes a millisecond
 int hipEventCreate(void** e) {
-  *e = handle;
+  *e = new long(0);
   return kOk;
 }
 int hipEventCreateWithFlags(void** e, unsigned) { return hipEventCreate(e); }
-int hipEventDestroy(void*) { return kOk; }
-int hipEventRecord(void*, void*) { return kOk; }
-int hipEventSynchronize(void*) { return kOk; }
-int hipEventElapsedTime(float* ms, void*, void*) {
-  *ms = 1.0f;
+int hipEventDestroy(void* e) {
+  delete static_cast<long*>(e);
   return kOk;
 }
-int hipStreamCreateWithFlags(void** s, unsigned) { return hipEventCreate(s); }
+int hipEventRecord(void* e, void*) {
+  *static_cast<long*>(e) = launched;
+  return kOk;
+}
+int hipEventSynchronize(void*) { return kOk; }
+int hipEventElapsedTime(float* ms, void* a, void* b) {
+  *ms = (float)(*static_cast<long*>(b) - *static_cast<long*>(a));
+  return kOk;
+}
+int hipStreamCreateWithFlags(void** s, unsigned) {
+  *s = handle;
+  return kOk;
+}
 int hipStreamDestroy(void*) { return kOk; }
 int hipStreamWaitEvent(void*, void*, unsigned) { return kOk; }
 int hipStreamBeginCapture(void*, int) { return kOk; }
-int hipStreamEndCapture(void*, void** g) { return hipEventCreate(g); }
-int hipGraphInstantiate(void** e, void*, void*, char*, size_t) { return hipEventCreate(e); }
+int hipStreamEndCapture(void*, void** g) {
+  *g = handle;
+  return kOk;
+}
+int hipGraphInstantiate(void** e, void*, void*, char*, size_t) {
+  *e = handle;
+  return kOk;
+}
 int hipGraphLaunch(void*, void*) { return kOk; }
 int hipGraphDestroy(void*) { return kOk; }
 int hipGraphExecDestroy(void*) { return kOk; }

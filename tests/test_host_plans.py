@@ -76,3 +76,57 @@ emit([out, hip.fake_used()])
     assert got[1] == 0
     assert got[0] == [[0, ["stage_batch"], rows, both, both], [0, ["stage_batch"], rows, both, both],
                       [0, ["stage_batch", "cull_stage_edges"], rows + 80 * 16384, both, both]]
+
+
+NEEDLE = "[[-0.5, 0.0], [0.5, -2e-6], [0.5, 2e-6]]"
+
+
+def test_tuning_decides_for_its_own_plan(tmp_path_factory):
+    """What autotuning found, the culled or the full evaluation, holds for the
+    plan that was tuned: the choice depends on the map and the footprints, which
+    the cache's size signature does not know.  (On this runtime the form of fewer
+    launches is the faster: the full one for one footprint size, where they are
+    equal, the culled one for two.)"""
+    got = script("""
+one = [(HEX, 300, 16384, 65536)]
+two = [(HEX, 300, 16384, 65536), (HEX[::2], 300, 16384, 65536)]
+T, X = _lib.PSDF_BATCH_AUTOTUNE, _lib.PSDF_BATCH_EXHAUSTIVE
+out = []
+for insts in (one, two):
+    rc, p = plan(insts, flags=T)
+    autotune(p)
+    rc, later = plan(insts)
+    out.append([run(p)[0], run(later)[0]])
+    rc, x = plan(insts, flags=T | X)
+    autotune(x)
+    rc, later = plan(insts)
+    out.append([run(x)[0], run(later)[0]])
+emit(out)
+""", tmp_path_factory)
+    assert got == [["batch_kernel", "cull_list"], ["batch_kernel", "cull_list"],
+                   ["cull_list", "cull_list"], ["batch_kernel", "cull_list"]]
+
+
+def test_cache_files(tmp_path_factory, tmp_path):
+    """Lines of a cache file give a shape and never the form, also those written
+    with the form in their last number; a footprint without a bound is not culled."""
+    path = tmp_path / "tune"
+    got = script(f"""
+insts = [(HEX, 300, 16384, 65536)]
+rc, p = plan(insts, flags=_lib.PSDF_BATCH_AUTOTUNE)
+autotune(p)
+line = open({str(path)!r}).read().split()
+emit(line)
+""", tmp_path_factory, env={"PSDF_TUNE_CACHE": str(path)})
+    assert len(got) == 4 and got[3] in ("0", "1")
+    sig = got[0]
+    for last in range(6):
+        path.write_text(f"{sig} 8 4 {last}\n")
+        got = script(f"""
+info = [ctypes.c_int32() for _ in range(5)]
+rc, p = plan([(HEX, 300, 16384, 65536)])
+lib.psdf_batch_plan_info(p, *[ctypes.byref(i) for i in info])
+rc, q = plan([({NEEDLE}, 300, 16384, 65536)])
+emit([run(p)[0], run(q)[0], info[0].value, info[1].value, info[4].value])
+""", tmp_path_factory, env={"PSDF_TUNE_CACHE": str(path)})
+        assert got == ["cull_list", "batch_kernel", 8, 256, last & 1], last
