@@ -443,10 +443,10 @@ int psdf_batch_screened(psdf_batch_plan* plan, const float* theta, int32_t pool,
  * than 512 obstacles have LB_i <= T, when the bound of the obstacles outside
  * its instance's horizon list is not above T, or when that list is unusable.
  * Same assumptions, limits and optional outputs as psdf_batch_screened
- * (stage_cand counts the seed).  Without the optional outputs, a batch that
- * psdf_batch culls is evaluated the same way here (boxes instead of circles,
- * lists that leave no stage to a full evaluation), from the staged boxes
- * where psdf_batch_stage took them. */
+ * (stage_cand counts the seed).  Without the optional outputs, a plan that
+ * psdf_batch evaluates culled is evaluated the same way here (boxes instead of
+ * circles, lists that leave no stage to a full evaluation), from the staged
+ * boxes where psdf_batch_stage took them. */
 int psdf_batch_screened_bound(psdf_batch_plan* plan, const float* poses, const float* ax,
                               const float* ay, const float* bx, const float* by,
                               const int32_t* obst_off, float* d, int32_t* edge, int32_t* obst,

@@ -691,7 +691,7 @@ static int screened_run(psdf_batch_plan* p, bool bound, const float* theta, int3
                          "from (stage again, or psdf_batch_unstage)");
     circ = p->d_circ;
   }
-  if (bound && p->cull_ready && !stage_cand && !stage_cert && !cand_keys) {
+  if (bound && p->culled && !stage_cand && !stage_cert && !cand_keys) {
     // the same scheme with boxes for circles and lists that leave no stage
     // uncertified: nothing to fall back from, two launches.  (On 64 x 50 x
     // 16384 the circles' 512-entry lists leave some stages of most draws to
@@ -799,7 +799,7 @@ int psdf_batch_stage(psdf_batch_plan* p, const float* ax, const float* ay, const
       if (err != hipSuccess) p->d_rows = nullptr;
     }
     if (err != hipSuccess) return hip_status(err);
-    const bool boxes = p->cull_ready && stage_boxes(p);
+    const bool boxes = p->culled && stage_boxes(p);
     const dim3 grid((p->max_M + 255) / 256, p->n_inst);
 #define PSDF_STAGE_BATCH(MI)                                                               \
   stage_batch_kernel<MI><<<grid, 256, 0, stream>>>(p->d_fp, p->d_inst, ax, ay, bx, by, off, \

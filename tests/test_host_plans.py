@@ -130,3 +130,24 @@ rc, q = plan([({NEEDLE}, 300, 16384, 65536)])
 emit([run(p)[0], run(q)[0], info[0].value, info[1].value, info[4].value])
 """, tmp_path_factory, env={"PSDF_TUNE_CACHE": str(path)})
         assert got == ["cull_list", "batch_kernel", 8, 256, last & 1], last
+
+
+def test_bound_form_follows_the_plan(tmp_path_factory):
+    """psdf_batch_screened_bound is culled where psdf_batch is: not after an
+    explicit shape, nor where tuning found the full evaluation faster."""
+    got = script("""
+one = [(HEX, 300, 16384, 65536)]
+out = []
+rc, p = plan(one)
+out.append([bound(p), stage(p)[1]])
+lib.psdf_batch_set_shape(p, 8, 64, 1)
+out.append([run(p)[0], "screen_bound" in bound(p), stage(p)[1]])
+rc, p = plan(one, flags=_lib.PSDF_BATCH_AUTOTUNE)
+stage(p)
+autotune(p)
+out.append([run(p)[0], "screen_bound" in bound(p), stage(p)[1]])
+emit(out)
+""", tmp_path_factory)
+    both = ["cull_list", "cull_stage_kernel"]
+    assert got == [[both, ["stage_batch", "cull_stage_edges"]],
+                   ["batch_kernel", True, ["stage_batch"]], ["batch_kernel", True, ["stage_batch"]]]
