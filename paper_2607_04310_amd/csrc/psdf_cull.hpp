@@ -18,12 +18,12 @@
 // the box lies beyond the nearest one along u and within its diagonal of it, so
 // the gap on n at distance r is at least cos(alpha) (r - diagonal tan(alpha)):
 // with the box enlarged by diagonal * tan(alpha) the bound above holds again (for
-// a sliver of a footprint that is the whole plane).  The second bound
-// (cull_evaluate) takes the box as it is.  16 x 50 stages x 16384 open chains,
-// everything evaluated -> enlarged boxes -> and the second bound: a triangle for
-// a footprint 1750 -> 770 -> 308 us (full evaluation 150), a hexagon 184 us (247); the
-// same with rectangles that have a vertex within a side: 142 -> 69 us (120) and
-// 28 us (196).
+// a sliver of a footprint that is the whole plane).  Such an obstacle is stored
+// with its box as it is and a mark; whoever takes a distance to it enlarges it,
+// the list's bound of phi and the second bound (cull_evaluate) don't.  16 x 50
+// stages x 16384 chains of three edges, a hexagon for a footprint, boxes stored
+// enlarged (or, staged, as the whole plane) -> marked: 178 -> 27 us, from staged boxes
+// 358 -> 18 (full evaluation 240); an equilateral triangle 181 -> 27 and 334 -> 19 (151).
 // Any other obstacle (invalid, a degenerate edge, coordinates beyond 1e15) is
 // irregular: it is always evaluated.
 //
@@ -79,12 +79,26 @@ struct CullStage {
   int row, inst, slot0, seg0, nseg, M, obst_off, edge_off;
 };
 
+// A stored box is (lo.x, lo.y, hi.x, hi.y); lo.x NaN: irregular; with lo.x and
+// hi.x exchanged: a loose obstacle's (CullBox).
+struct CullBox {
+  float lox, loy, hix, hiy;
+  bool loose;
+};
+__device__ __forceinline__ CullBox cull_box(const float4& b) {
+  return CullBox{fminf(b.x, b.z), b.y, fmaxf(b.x, b.z), b.w, b.x > b.z};
+}
+
+__device__ __forceinline__ float cull_enlarged(const FpConst& F, const CullBox& b) {
+  const float size = (b.hix - b.lox) + (b.hiy - b.loy);
+  return b.loose ? fminf(F.cull_open * size, kCullPlane) : 0.f;
+}
+
 // A listed obstacle, one 64-byte record, so that the scan of the boxes brings
-// in what the evaluation reads next: the box (lo.x NaN: irregular), the
-// obstacle's index, first edge (global) and edge count, flags, and the points
-// of a convex polygon of at most four edges (A_j) or of one edge (A_0, B_0), or
-// the box before its enlargement (kRecLoose).
-constexpr int kRecClosed = 1, kRecBad = 2, kRecPoints = 4, kRecLoose = 8;
+// in what the evaluation reads next: the box, the obstacle's index, first edge
+// (global) and edge count, flags, and the points of a closed polygon of at most
+// four edges (A_j) or of one edge (A_0, B_0).
+constexpr int kRecClosed = 1, kRecBad = 2, kRecPoints = 4;
 struct CullRec {
   float4 box;
   int4 meta;
@@ -162,20 +176,16 @@ __device__ __forceinline__ bool same_bits(float a, float b) {
   return __float_as_uint(a) == __float_as_uint(b);
 }
 
-// Box (NaN: irregular) and flags of the obstacle with edges [e0, e0 + mi),
-// 1 <= mi <= MI and in range, and whether the box is a tight one, of a convex
-// obstacle; open: the factor of the enlargement of the others (FpConst); the first
-// edge (mi != 4) or all four (mi == 4)
-// are in v (ax, ay, bx, by), and with kRecPoints in the flags its points are
-// afterwards (v[0], v[1]: A_j), with kRecLoose its box (v[0][0], v[1][0], v[0][1],
-// v[1][1]).
+// Box (NaN: irregular; loose: marked) and flags of the obstacle with edges
+// [e0, e0 + mi), 1 <= mi <= MI and in range; the first edge (mi != 4) or all four
+// (mi == 4) are in v (ax, ay, bx, by), and with kRecPoints in the flags its points
+// are afterwards (v[0], v[1]: A_j).
 template <int MI>
-__device__ __forceinline__ bool cull_obstacle(float (&v)[4][4], const float* __restrict__ gax,
+__device__ __forceinline__ void cull_obstacle(float (&v)[4][4], const float* __restrict__ gax,
                                               const float* __restrict__ gay,
                                               const float* __restrict__ gbx,
                                               const float* __restrict__ gby, int e0, int mi,
-                                              float minl2, float rel, float open, float4& box,
-                                              int& flags) {
+                                              float minl2, float rel, float4& box, int& flags) {
   CullAcc c;
   c.lox = c.loy = __builtin_huge_valf();
   c.hix = c.hiy = -__builtin_huge_valf();
@@ -234,22 +244,16 @@ __device__ __forceinline__ bool cull_obstacle(float (&v)[4][4], const float* __r
   // rounding of the enlargement itself
   const float size = (c.hix - c.lox) + (c.hiy - c.loy);
   const float e = fmaf(rel, size, 2.5e-7f * big);
-  box = make_float4(__builtin_nanf(""), 0.f, 0.f, 0.f);
-  const bool bound = fine && e < kCullMax;
-  const bool loose = bound && !convex;
-  if (bound) box = make_float4(c.lox - e, c.loy - e, c.hix + e, c.hiy + e);
-  flags = (c.closed ? kRecClosed : 0) | (bad ? kRecBad : 0) | (loose ? kRecLoose : 0) |
-          (MI == 4 && !loose && (c.closed || mi == 1) ? kRecPoints : 0);
-  if (loose) {
-    v[0][0] = box.x; v[1][0] = box.y; v[0][1] = box.z; v[1][1] = box.w;
-    const float g = fminf(open * size, kCullPlane);
-    box = make_float4(box.x - g, box.y - g, box.z + g, box.w + g);
-  }
-  return bound && convex;
+  const float lox = c.lox - e, hix = c.hix + e;
+  box = fine && e < kCullMax
+            ? make_float4(convex ? lox : hix, c.loy - e, convex ? hix : lox, c.hiy + e)
+            : make_float4(__builtin_nanf(""), 0.f, 0.f, 0.f);
+  flags = (c.closed ? kRecClosed : 0) | (bad ? kRecBad : 0) |
+          (MI == 4 && (c.closed || mi == 1) ? kRecPoints : 0);
 }
 
 // The lo.x of a staged box whose obstacle has no edge.
-constexpr float kEmptyBox = __builtin_huge_valf();
+constexpr float kEmptyBox = -__builtin_huge_valf();
 
 __device__ __forceinline__ float cull_minl2(float eps) {
   const float l = 4e6f * eps;
@@ -284,12 +288,13 @@ struct CullLoad {
       for (int k = 0; k < 4; ++k) v[k][0] = *src[k];
     }
   }
-  __device__ __forceinline__ bool finish(const CullArgs& A, const FpConst& F, float open,
-                                         float4& box, int& flags) {
+  __device__ __forceinline__ void finish(const CullArgs& A, const FpConst& F, float4& box,
+                                         int& flags) {
     box = make_float4(__builtin_nanf(""), 0.f, 0.f, 0.f);
     flags = kRecBad;
-    return ok && cull_obstacle<MI>(v, A.ax, A.ay, A.bx, A.by, e0, mi, cull_minl2(F.eps),
-                                   F.cull_rel, open, box, flags);
+    if (ok)
+      cull_obstacle<MI>(v, A.ax, A.ay, A.bx, A.by, e0, mi, cull_minl2(F.eps), F.cull_rel, box,
+                        flags);
   }
   __device__ __forceinline__ void record(CullRec* r, const float4& box, int o, int flags) const {
     r->box = box;
@@ -316,9 +321,7 @@ __global__ __launch_bounds__(256) void cull_stage_edges_kernel(CullArgs A, float
   ld.load(A, in, in.edge_off + in.E);
   float4 box;
   int flags;
-  // (the list kernel does not know the loose boxes among the staged ones: as the
-  // whole plane they leave its bound of phi alone)
-  ld.finish(A, fp_const(A.fps, S.inst), __builtin_huge_valf(), box, flags);
+  ld.finish(A, fp_const(A.fps, S.inst), box, flags);
   if (ld.mi == 0) box.x = kEmptyBox;
   sbox[S.slot0 + k] = box;
   ld.record(srec + S.slot0 + k, box, S.o0 + k, flags);
@@ -398,19 +401,21 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
   float ub = __builtin_huge_valf();
 #pragma unroll
   for (int q = 0; q < kCullPer; ++q) {
-    const float4& b = box[q];
-    bool regular;
-    if (STAGED) regular = b.x == b.x && b.x != kEmptyBox;
-    else regular = ld[q].finish(A, F, F.cull_open, box[q], flags[q]);
-    if (regular) {
-      const float x0 = fmaxf(fabsf(b.x - plx), fabsf(b.x - phx));
-      const float x1 = fmaxf(fabsf(b.z - plx), fabsf(b.z - phx));
-      const float y0 = fmaxf(fabsf(b.y - ply), fabsf(b.y - phy));
-      const float y1 = fmaxf(fabsf(b.w - ply), fabsf(b.w - phy));
+    if (!STAGED) {
+      ld[q].finish(A, F, box[q], flags[q]);
+      if (ld[q].mi == 0) box[q].x = kEmptyBox;
+    }
+    if (box[q].x == box[q].x && box[q].x != kEmptyBox) {
+      const CullBox b = cull_box(box[q]);
+      const float x0 = fmaxf(fabsf(b.lox - plx), fabsf(b.lox - phx));
+      const float x1 = fmaxf(fabsf(b.hix - plx), fabsf(b.hix - phx));
+      const float y0 = fmaxf(fabsf(b.loy - ply), fabsf(b.loy - phy));
+      const float y1 = fmaxf(fabsf(b.hiy - ply), fabsf(b.hiy - phy));
       const float xs = fminf(x0, x1), xl = fmaxf(x0, x1), ys = fminf(y0, y1), yl = fmaxf(y0, y1);
       const float far2 = fminf(fmaf(xs, xs, yl * yl), fmaf(xl, xl, ys * ys));
-      const float big = fmaxf(fmaxf(fabsf(b.x), fabsf(b.z)), fmaxf(fabsf(b.y), fabsf(b.w)));
-      const float off_side = fmaf(4.0f * F.cull_rel, (b.z - b.x) + (b.w - b.y), 6e-7f * big);
+      const float big =
+          fmaxf(fmaxf(fabsf(b.lox), fabsf(b.hix)), fmaxf(fabsf(b.loy), fabsf(b.hiy)));
+      const float off_side = fmaf(4.0f * F.cull_rel, (b.hix - b.lox) + (b.hiy - b.loy), 6e-7f * big);
       ub = fminf(ub, off_side + sqrtf(far2));
     }
   }
@@ -430,12 +435,12 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
   int at[kCullPer];
 #pragma unroll
   for (int q = 0; q < kCullPer; ++q) {
-    const float4 b = box[q];
-    const float gx = fmaxf(fmaxf(b.x - phx, plx - b.z), 0.f);
-    const float gy = fmaxf(fmaxf(b.y - phy, ply - b.w), 0.f);
-    const bool far = b.x == b.x && fmaf(gx, gx, gy * gy) > bar2 && !all;
-    const bool empty = STAGED ? b.x == kEmptyBox : ld[q].mi == 0;
-    take[q] = !empty && !none && !far;
+    const CullBox b = cull_box(box[q]);
+    const float g = cull_enlarged(F, b);
+    const float gx = fmaxf(fmaxf(b.lox - phx, plx - b.hix) - g, 0.f);
+    const float gy = fmaxf(fmaxf(b.loy - phy, ply - b.hiy) - g, 0.f);
+    const bool far = box[q].x == box[q].x && fmaf(gx, gx, gy * gy) > bar2 && !all;
+    take[q] = box[q].x != kEmptyBox && !none && !far;
     const uint64_t m = __ballot(take[q]);
     at[q] = n + lanes_below(m);
     n += (int)__popcll(m);
@@ -469,10 +474,7 @@ template <int MI>
 struct RecSource {
   const CullArgs& A;
   const CullRec* rec;
-  // the box for the second bound
-  __device__ __forceinline__ float4 box(int sl) const {
-    return (rec[sl].meta.w & kRecLoose) ? rec[sl].pts[0] : rec[sl].box;
-  }
+  __device__ __forceinline__ float4 box(int sl) const { return rec[sl].box; }
   __device__ __forceinline__ int4 meta(int sl) const { return rec[sl].meta; }
   __device__ __forceinline__ void edge(int sl, const int4& m, int j, bool act, float& ax,
                                        float& ay, float& bx, float& by) const {
@@ -500,12 +502,21 @@ struct CullBest {
   }
 };
 
-// Squared distance from (px, py) to a box; -1 for an irregular obstacle, or
-// with ok false (last as unsigned bits, within every bar).
-__device__ __forceinline__ float cull_dist2(const float4& b, float px, float py, bool ok) {
-  const float gx = fmaxf(fmaxf(b.x - px, px - b.z), 0.f);
-  const float gy = fmaxf(fmaxf(b.y - py, py - b.w), 0.f);
-  return (b.x == b.x && ok) ? fmaf(gx, gx, gy * gy) : -1.f;
+// Squared distance from (px, py) to a stored box, a loose one enlarged (taken off
+// the differences, which are exact to their own rounding); -1 for an irregular
+// obstacle, or with ok false (last as unsigned bits, within every bar).
+__device__ __forceinline__ float cull_dist2(const FpConst& F, const float4& s, float px, float py,
+                                            bool ok) {
+  const CullBox b = cull_box(s);
+  float gx = fmaxf(b.lox - px, px - b.hix), gy = fmaxf(b.loy - py, py - b.hiy);
+  if (__ballot(b.loose)) {
+    const float e = cull_enlarged(F, b);
+    gx -= e;
+    gy -= e;
+  }
+  gx = fmaxf(gx, 0.f);
+  gy = fmaxf(gy, 0.f);
+  return (s.x == s.x && ok) ? fmaf(gx, gx, gy * gy) : -1.f;
 }
 
 // The bar of a least sd (a NaN: of tau) as a squared distance to a box.
@@ -557,8 +568,9 @@ __device__ __forceinline__ void cull_evaluate(const FpConst& F, const FpSlot* fs
     lb[h] = 0.f;
     if (cut && lane + 64 * h < n) {
       const float4 b = src.box(cand[lane + 64 * h]);
-      const float cx = 0.5f * (b.x + b.z) - px, cy = 0.5f * (b.y + b.w) - py;
-      const float hx = 0.5f * (b.z - b.x), hy = 0.5f * (b.w - b.y);
+      const CullBox t = cull_box(b);
+      const float cx = 0.5f * (t.lox + t.hix) - px, cy = 0.5f * (t.loy + t.hiy) - py;
+      const float hx = 0.5f * (t.hix - t.lox), hy = 0.5f * (t.hiy - t.loy);
       float depth = __builtin_huge_valf();
       for (int l = 0; l < F.m; ++l) {
         const float nx = fs[l].r.w, ny = -fs[l].r.z;
@@ -653,7 +665,7 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
   starts[lane] = starts[64 + lane] = 0u;
 
   const bool within = fmaxf(fabsf(px), fabsf(py)) < kCullMax;
-  auto dist2 = [&](const float4& b) { return cull_dist2(b, px, py, within); };
+  auto dist2 = [&](const float4& b) { return cull_dist2(F, b, px, py, within); };
 
   // ---- the list as one
   static_assert(kCullFlat == 64 * 64, "two words of starts per lane");
@@ -928,7 +940,7 @@ void cull_main_kernel(
       const int k = tid + kCullThreads * q;
       float4 box;
       int flags;
-      ld[q].finish(A, F, F.cull_open, box, flags);
+      ld[q].finish(A, F, box, flags);
       if (ld[q].mi == 0) box.x = kEmptyBox;
       lbox[k] = box;
       le0[k] = ld[q].e0;
@@ -955,7 +967,8 @@ void cull_main_kernel(
     for (int r = 0; r < kBoxRounds; ++r) {
       const float4 b = lbox[64 * r + lane];
       const bool empty = b.x == kEmptyBox;
-      d2[r] = empty ? __builtin_nanf("") : cull_dist2(b, px, py, within);
+      const float x = cull_dist2(F, b, px, py, within);
+      d2[r] = empty ? __builtin_nanf("") : x;
       kb = min(kb, empty ? 0xffffffffu : __float_as_uint(d2[r]));
     }
     const uint32_t kmin = fw_min_u32(kb);

@@ -1,0 +1,94 @@
+"""The evaluation that a call takes by itself is not the slower one on maps that
+are not made of convex polygons, with footprints from blunt to needle: against
+the full evaluation of every pair on the same inputs (the best of several
+bursts of each), with the same outputs bit for bit."""
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+
+from paper_2607_04310_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+HALF = 40.0       # 16384 obstacles of about a metre in 80 m x 80 m
+FOOTPRINTS = {
+    "hexagon": inputs.hexagon_footprint(np.random.default_rng(3)),
+    "triangle": np.array([[0.5, 0.0], [-0.25, 0.433], [-0.25, -0.433]], np.float32),
+    "20 degrees": np.array([[-0.5, 0.0], [0.5, -0.176], [0.5, 0.176]], np.float32),
+    "5 degrees": np.array([[-0.5, 0.0], [0.5, -0.0437], [0.5, 0.0437]], np.float32),
+    "0.1 degrees": np.array([[-0.5, 0.0], [0.5, -8.7e-4], [0.5, 8.7e-4]], np.float32),
+}
+
+
+def _closed(P):
+    return np.concatenate([P, np.roll(P, -1, 1)], 2)
+
+
+def _map(rng, M, kind):
+    """(edges, offsets, mbar): `chains` of three edges, rectangles with a vertex
+    within a side (`side`), `arrows` with a reflex corner."""
+    c, a = rng.uniform(-HALF, HALF, (M, 1, 2)), rng.uniform(0, 2 * np.pi, M)
+    R = np.stack([np.stack([np.cos(a), -np.sin(a)], 1), np.stack([np.sin(a), np.cos(a)], 1)], 1)
+    w, h = rng.uniform(0.1, 0.8, (2, M, 1))
+    z = 0 * w
+    corner = lambda *xy: np.stack([np.concatenate(p, 1) for p in xy], 1) @ R.transpose(0, 2, 1) + c
+    if kind == "chains":
+        P = c + np.cumsum(rng.normal(0, 0.3, (M, 4, 2)), 1)
+        e = np.concatenate([P[:, :-1], P[:, 1:]], 2)
+    elif kind == "side":
+        e = _closed(corner((-w, -h), (z, -h), (w, -h), (z, h)))
+    else:
+        e = _closed(corner((-w, -h), (z, -h / 3), (w, -h), (z, h)))
+    return e.reshape(-1, 4).astype(np.float32), inputs.csr_offsets([e.shape[1]] * M), 4
+
+
+def _time(torch, call, n=10):
+    for _ in range(3):
+        call()
+    best = float("inf")
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(n):
+            call()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) / n)
+    return best
+
+
+def _batch(kind, fp):
+    import torch
+    from paper_2607_04310_amd import api
+    rng = np.random.default_rng(5)
+    insts = []
+    for _ in range(16):
+        edges, off, mbar = _map(rng, 16384, kind)
+        insts.append(SimpleNamespace(footprint=fp, poses=inputs.path_poses(rng, 50, -HALF / 2, HALF / 2),
+                                     edges=edges, obst_off=off))
+    a = api.Batch(insts, mbar=mbar)
+    b = api.Batch(insts, mbar=mbar, exhaustive=True)
+    want = [t.clone() for t in b.run()]
+    full = _time(torch, b.run)
+    out = {}
+    for form, call in (("culled", a.run), ("bound", a.screened_bound)):
+        got = call()
+        assert all(torch.equal(g.view(torch.uint8), w.view(torch.uint8)) for g, w in zip(got, want)), form
+        out[form] = _time(torch, call)
+    a.stage()
+    got = a.screened_bound()
+    assert all(torch.equal(g.view(torch.uint8), w.view(torch.uint8)) for g, w in zip(got, want))
+    out["staged"] = _time(torch, a.screened_bound)
+    a.close()
+    b.close()
+    print(kind, {k: round(1e3 * v, 1) for k, v in dict(full=full, **out).items()}, flush=True)
+    return full, out
+
+
+@pytest.mark.parametrize("kind", ["chains", "side", "arrows"])
+@pytest.mark.parametrize("fp", ["hexagon", "triangle"])
+def test_staging_does_not_slow_the_bound_form(kind, fp):
+    """From staged boxes a call reads less; a tenth is left to noise."""
+    full, out = _batch(kind, FOOTPRINTS[fp])
+    assert out["staged"] <= 1.1 * out["bound"], (full, out)
