@@ -18,12 +18,17 @@
 // the box lies beyond the nearest one along u and within its diagonal of it, so
 // the gap on n at distance r is at least cos(alpha) (r - diagonal tan(alpha)):
 // with the box enlarged by diagonal * tan(alpha) the bound above holds again (for
-// a sliver of a footprint that is the whole plane).  Such an obstacle is stored
-// with its box as it is and a mark; whoever takes a distance to it enlarges it,
-// the list's bound of phi and the second bound (cull_evaluate) don't.  16 x 50
-// stages x 16384 chains of three edges, a hexagon for a footprint, boxes stored
-// enlarged (or, staged, as the whole plane) -> marked: 178 -> 27 us, from staged boxes
-// 358 -> 18 (full evaluation 240); an equilateral triangle 181 -> 27 and 334 -> 19 (151).
+// a sliver of a footprint that is the whole plane).  At one stage more is known:
+// a gap on a robot axis above its rounding (cull_separates) makes the evaluation
+// call the two separated, and the box as it is bounds the distance.  Such an
+// obstacle is stored with its box as it is and a mark; the list enlarges it, and
+// tries the stages' axes where that leaves too many (cull_list_kernel), the stage
+// kernel tries its axes, the plain kernel enlarges.  16 x 50 stages x 16384 chains of
+// three edges, enlarged boxes stored -> enlarged where used -> and axes tried, us:
+// hexagon 178 -> 27 -> 25 (full evaluation 240), equilateral triangle 181 -> 27 -> 26
+// (153), corner of 20 degrees 202 -> 56 -> 40 (150), of 5 degrees 331 -> 265 -> 60
+// (152); from staged boxes 358 -> 18 -> 16, 334 -> 19 -> 17, 344 -> 49 -> 32 and
+// 376 -> 256 -> 51.
 // Any other obstacle (invalid, a degenerate edge, coordinates beyond 1e15) is
 // irregular: it is always evaluated.
 //
@@ -89,9 +94,34 @@ __device__ __forceinline__ CullBox cull_box(const float4& b) {
   return CullBox{fminf(b.x, b.z), b.y, fmaxf(b.x, b.z), b.w, b.x > b.z};
 }
 
+// What a loose obstacle's box is enlarged by on every side (0 for the others).
 __device__ __forceinline__ float cull_enlarged(const FpConst& F, const CullBox& b) {
   const float size = (b.hix - b.lox) + (b.hiy - b.loy);
   return b.loose ? fminf(F.cull_open * size, kCullPlane) : 0.f;
+}
+
+// The least of (W - p) . n over the points W of a box.
+__device__ __forceinline__ float cull_axis(const CullBox& b, float px, float py, float nx,
+                                           float ny) {
+  const float cx = 0.5f * (b.lox + b.hix) - px, cy = 0.5f * (b.loy + b.hiy) - py;
+  const float hx = 0.5f * (b.hix - b.lox), hy = 0.5f * (b.hiy - b.loy);
+  return fmaf(cx, nx, fmaf(cy, ny, -fmaf(hx, fabsf(nx), hy * fabsf(ny))));
+}
+
+// Rounding of a gap on a robot axis between a box and the footprint, and of the
+// evaluation's own projections of the obstacle on it: a dozen half ulps of the
+// coordinates that enter, at most.
+__device__ __forceinline__ float cull_axis_error(const FpConst& F, const CullBox& b, float px,
+                                                 float py) {
+  const float cx = 0.5f * (b.lox + b.hix) - px, cy = 0.5f * (b.loy + b.hiy) - py;
+  const float hx = 0.5f * (b.hix - b.lox), hy = 0.5f * (b.hiy - b.loy);
+  return fmaf(2e-6f, (fabsf(cx) + fabsf(cy)) + (hx + hy) + F.rmax, F.eps_sat + 1e-4f);
+}
+
+// Whether that gap makes the evaluation call the two separated.
+__device__ __forceinline__ bool cull_separates(const FpConst& F, const CullBox& b, float px,
+                                               float py, float gap) {
+  return gap > cull_axis_error(F, b, px, py);
 }
 
 // A listed obstacle, one 64-byte record, so that the scan of the boxes brings
@@ -331,11 +361,14 @@ __global__ __launch_bounds__(256) void cull_stage_edges_kernel(CullArgs A, float
 // rectangles), or of every staged box (17 MB in 7.5 us, the chain of loads
 // and two barriers).  Each thread holds kCullPer obstacles whose loads are all
 // in flight together.
+constexpr int kAxisStages = kCullThreads / kMaxFp;   // stages whose axes are held at once
 template <int MI, bool STAGED>
 __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
   __shared__ float red[4][kCullThreads / 64];
   __shared__ float s_h[kCullThreads / 64];
   __shared__ int s_n[kCullThreads / 64];
+  __shared__ float4 s_axes[kAxisStages * kMaxFp];   // n_l (world), cn_l
+  __shared__ float2 s_pos[kAxisStages];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   typedef const __attribute__((address_space(4))) CullSeg SegC;
   const CullSeg& S = *(const CullSeg*)((SegC*)A.segs + blockIdx.x);
@@ -429,29 +462,91 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
   const float bar = (H + F.rmax + kCullGamma) * (1.0f + 2.0f * F.cull_rel);
   const float bar2 = bar * bar;
 
-  // the list, in obstacle order within each wave
-  int n = 0;
-  bool take[kCullPer];
-  int at[kCullPer];
+  // the list, in obstacle order within each wave; open: loose obstacles that only
+  // the stages' own axes can leave out
+  bool take[kCullPer], open[kCullPer];
 #pragma unroll
   for (int q = 0; q < kCullPer; ++q) {
     const CullBox b = cull_box(box[q]);
-    const float g = cull_enlarged(F, b);
-    const float gx = fmaxf(fmaxf(b.lox - phx, plx - b.hix) - g, 0.f);
-    const float gy = fmaxf(fmaxf(b.loy - phy, ply - b.hiy) - g, 0.f);
+    const float ox = fmaxf(b.lox - phx, plx - b.hix), oy = fmaxf(b.loy - phy, ply - b.hiy);
+    const float gx = fmaxf(ox, 0.f), gy = fmaxf(oy, 0.f);
     const bool far = box[q].x == box[q].x && fmaf(gx, gx, gy * gy) > bar2 && !all;
-    take[q] = box[q].x != kEmptyBox && !none && !far;
-    const uint64_t m = __ballot(take[q]);
-    at[q] = n + lanes_below(m);
-    n += (int)__popcll(m);
+    const float e = cull_enlarged(F, b);
+    const float ex = fmaxf(ox - e, 0.f), ey = fmaxf(oy - e, 0.f);
+    open[q] = box[q].x == box[q].x && far && !none && b.loose && !(fmaf(ex, ex, ey * ey) > bar2);
+    take[q] = box[q].x != kEmptyBox && !none && (!far || open[q]);
   }
-  if (lane == 0) s_n[w] = n;
-  __syncthreads();
-  int base = S.slot0, total = 0;
+  // takes the counts (listed, and open among them: at most kSegObst each)
+  int at[kCullPer], base, total;
+  auto count = [&]() {
+    int n = 0, no = 0;
 #pragma unroll
-  for (int i = 0; i < kCullThreads / 64; ++i) {
-    base += i < w ? s_n[i] : 0;
-    total += s_n[i];
+    for (int q = 0; q < kCullPer; ++q) {
+      const uint64_t m = __ballot(take[q]);
+      at[q] = n + lanes_below(m);
+      n += (int)__popcll(m);
+      no += (int)__popcll(__ballot(open[q]));
+    }
+    if (lane == 0) s_n[w] = n | no << 16;
+    __syncthreads();
+    base = S.slot0;
+    total = no = 0;
+#pragma unroll
+    for (int i = 0; i < kCullThreads / 64; ++i) {
+      const int c = s_n[i] & 0xffff;
+      base += i < w ? c : 0;
+      total += c;
+      no += s_n[i] >> 16;
+    }
+    return no;
+  };
+  // The axes here cost about 30 us at 50 stages and three axes, and more with
+  // both; an open obstacle per segment left on the list costs every stage a 64th
+  // of a round, one to three times: worth it where a few hundred are open.  16 x 50
+  // x 16384 chains of three edges, without -> with: corner of 5 degrees 164 -> 60
+  // us, of 0.1 degrees 269 -> 115, but 20 degrees, with fewer open, 38 -> 55.
+  if (count() > 64 * (F.m + 1)) {
+    for (int t0 = 0; t0 < in.N; t0 += kAxisStages) {
+      __syncthreads();   // the last stages' axes are read
+      {
+        const int t = t0 + tid / kMaxFp, l = tid % kMaxFp;
+        float4 v = make_float4(0.f, 0.f, -__builtin_huge_valf(), 0.f);   // no such stage: separated
+        float2 at_p = make_float2(0.f, 0.f);
+        if (t < in.N) {
+          const float* p = A.poses + 3 * (in.pose_off + t);
+          float sn, cs;
+          sincosf(p[2], &sn, &cs);
+          if (isfinite(p[0]) && isfinite(p[1]) && isfinite(cs) && isfinite(sn)) {
+            const FpRow* r = A.rows + S.inst * kMaxFp + l;
+            const float ux = r->q[0].z, uy = r->q[0].w;
+            v = make_float4(fmaf(sn, ux, cs * uy), -fmaf(cs, ux, -(sn * uy)), r->q[3].y, 0.f);
+            at_p = make_float2(p[0], p[1]);
+          }
+        }
+        s_axes[tid] = v;
+        if (l == 0) s_pos[tid / kMaxFp] = at_p;
+      }
+      __syncthreads();
+      for (int t = 0; t < min(kAxisStages, in.N - t0); ++t) {
+        const float2 p = s_pos[t];
+        float gap[kCullPer];
+#pragma unroll
+        for (int q = 0; q < kCullPer; ++q) gap[q] = -__builtin_huge_valf();
+        for (int l = 0; l < F.m; ++l) {
+          const float4 n = s_axes[t * kMaxFp + l];
+#pragma unroll
+          for (int q = 0; q < kCullPer; ++q)
+            gap[q] = fmaxf(gap[q], cull_axis(cull_box(box[q]), p.x, p.y, n.x, n.y) - n.z);
+        }
+#pragma unroll
+        for (int q = 0; q < kCullPer; ++q)
+          open[q] = open[q] && cull_separates(F, cull_box(box[q]), p.x, p.y, gap[q]);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kCullPer; ++q) take[q] = take[q] && !open[q];
+    __syncthreads();   // s_n and the last stages' axes are read
+    count();
   }
 #pragma unroll
   for (int q = 0; q < kCullPer; ++q)
@@ -519,6 +614,23 @@ __device__ __forceinline__ float cull_dist2(const FpConst& F, const float4& s, f
   return (s.x == s.x && ok) ? fmaf(gx, gx, gy * gy) : -1.f;
 }
 
+// The same at a stage whose rotated footprint fs is visible to the wave: a loose
+// obstacle's box as it is, where a robot axis is sure to separate it, else 0.
+__device__ __forceinline__ float cull_stage_dist2(const FpConst& F, const FpSlot* fs,
+                                                  const float4& s, float px, float py, bool ok) {
+  const CullBox b = cull_box(s);
+  const float gx = fmaxf(fmaxf(b.lox - px, px - b.hix), 0.f);
+  const float gy = fmaxf(fmaxf(b.loy - py, py - b.hiy), 0.f);
+  float d2 = fmaf(gx, gx, gy * gy);
+  if (__ballot(b.loose)) {
+    float gap = -__builtin_huge_valf();
+    for (int l = 0; l < F.m; ++l)
+      gap = fmaxf(gap, cull_axis(b, px, py, fs[l].r.w, -fs[l].r.z) - fs[l].cn);
+    if (b.loose && !cull_separates(F, b, px, py, gap)) d2 = 0.f;
+  }
+  return (s.x == s.x && ok) ? d2 : -1.f;
+}
+
 // The bar of a least sd (a NaN: of tau) as a squared distance to a box.
 __device__ __forceinline__ float cull_bar2(const FpConst& F, float sd) {
   const float b = (fmaxf(sd, F.cull_tau) + F.rmax + kCullGamma) * (1.0f + 2.0f * F.cull_rel);
@@ -569,15 +681,11 @@ __device__ __forceinline__ void cull_evaluate(const FpConst& F, const FpSlot* fs
     if (cut && lane + 64 * h < n) {
       const float4 b = src.box(cand[lane + 64 * h]);
       const CullBox t = cull_box(b);
-      const float cx = 0.5f * (t.lox + t.hix) - px, cy = 0.5f * (t.loy + t.hiy) - py;
-      const float hx = 0.5f * (t.hix - t.lox), hy = 0.5f * (t.hiy - t.loy);
-      float depth = __builtin_huge_valf();
-      for (int l = 0; l < F.m; ++l) {
-        const float nx = fs[l].r.w, ny = -fs[l].r.z;
-        const float w = fmaf(cx, nx, fmaf(cy, ny, -fmaf(hx, fabsf(nx), hy * fabsf(ny))));
-        depth = fminf(depth, fs[l].cn - w);
-      }
-      const float low = -depth - fmaf(F.cull_rel, F.rmax + 2.0f * fabsf(depth), F.eps_sat + 1e-4f);
+      float gap = -__builtin_huge_valf();
+      for (int l = 0; l < F.m; ++l)
+        gap = fmaxf(gap, cull_axis(t, px, py, fs[l].r.w, -fs[l].r.z) - fs[l].cn);
+      const float low = gap - fmaf(F.cull_rel, F.rmax + 2.0f * fabsf(gap),
+                                   cull_axis_error(F, t, px, py));
       lb[h] = b.x == b.x ? low : -__builtin_huge_valf();   // irregular: always
     }
   }
@@ -632,7 +740,7 @@ __device__ __forceinline__ void cull_evaluate(const FpConst& F, const FpSlot* fs
 // One wave per stage, MI lanes per evaluated obstacle.  Bound by its chain
 // (list, footprint, candidates, the adjoint: 7 to 12 us) where the batch has
 // few stages, by VALU issue where it has many.  The footprint's slots in a
-// loop (group_sd) instead of an instance per footprint size: 71 VGPRs and seven
+// loop (group_sd) instead of an instance per footprint size: 72 VGPRs and seven
 // waves per SIMD instead of 113 and four, and one launch for all sizes (512
 // uneven instances: stage 177 -> 55 us).  A second bound on the candidates,
 // and lists longer than the registers walked with four loads in flight, keep
@@ -665,7 +773,7 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
   starts[lane] = starts[64 + lane] = 0u;
 
   const bool within = fmaxf(fabsf(px), fabsf(py)) < kCullMax;
-  auto dist2 = [&](const float4& b) { return cull_dist2(F, b, px, py, within); };
+  auto dist2 = [&](const float4& b) { return cull_stage_dist2(F, fs, b, px, py, within); };
 
   // ---- the list as one
   static_assert(kCullFlat == 64 * 64, "two words of starts per lane");
@@ -715,6 +823,7 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
     fl.nx[lane] = n.x; fl.ny[lane] = n.y; fl.pa[lane] = n.z; fl.pb[lane] = n.w;
     fs[lane] = FpSlot{rotated(a.x, a.y, a.z, a.w, cs, sn), c.x, c.y, e.w, c.z, c.w};
   }
+  wave_sync();   // fs and fl are written
   d2[0] = dist2(b0[0]);
   if (lane < nflat) kb = __float_as_uint(d2[0]);
   if (longer) {
@@ -779,15 +888,16 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
   auto walk_from = [&](bool all) {
     return flat && !all ? Walk{kCullRounds, ord0, 0, 0} : Walk{0, -1, 0, 0};
   };
-  if (!in_regs) {
+  // (any distance within the bar of tau serves as the least one: cull_first)
+  const uint32_t near = __float_as_uint(cull_bar2(F, F.cull_tau));
+  if (!in_regs && !__ballot(kb <= near)) {
     Walk k = walk_from(false);
     walk(k, [&](int, float x, bool live) {
       if (live) kb = min(kb, __float_as_uint(x));
-      return true;
+      return !__ballot(kb <= near);
     });
   }
   const uint32_t kmin = fw_min_u32(kb);
-  wave_sync();   // fs and fl are written
 
   CullBest best{kEmptyKey, 0, make_int4(0, 0, 0, 0)};
   const bool pose_ok = isfinite(px) && isfinite(py) && isfinite(cs) && isfinite(sn);

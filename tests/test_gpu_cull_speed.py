@@ -92,3 +92,10 @@ def test_staging_does_not_slow_the_bound_form(kind, fp):
     """From staged boxes a call reads less; a tenth is left to noise."""
     full, out = _batch(kind, FOOTPRINTS[fp])
     assert out["staged"] <= 1.1 * out["bound"], (full, out)
+
+
+@pytest.mark.parametrize("kind", ["chains", "side", "arrows"])
+@pytest.mark.parametrize("fp", ["hexagon", "triangle", "20 degrees", "5 degrees"])
+def test_batch_is_not_slower_than_the_full_evaluation(kind, fp):
+    full, out = _batch(kind, FOOTPRINTS[fp])
+    assert max(out.values()) <= 1.1 * full, (full, out)
