@@ -50,9 +50,10 @@
  *    point-segment pool distance (lowest index on ties), grad[3s..3s+2] =
  *    dphi/d(x, y, theta).  An empty edge set gives d = +inf, obst = edge = -1,
  *    grad = 0; a non-finite pose gives d = NaN, obst = edge = -1, grad = NaN.
- *  - Problems of many (stage, obstacle) pairs are evaluated culled: a bound on
- *    every pair leaves a few obstacles per stage that are evaluated.  The
- *    outputs are those of the full evaluation bit for bit, for every input.
+ *  - Problems of many (stage, obstacle) pairs are evaluated culled where the
+ *    sizes, the footprints and eps let that be the faster way: a bound on every
+ *    pair leaves a few obstacles per stage that are evaluated.  The outputs are
+ *    those of the full evaluation bit for bit, for every input.
  *  - keys (device uint64[N]) receives the winner of each stage:
  *    (orderable(sd) << 32) | obstacle, where orderable maps floats to
  *    unsigned integers in the same order (NaN lowest).  psdf_bwd consumes it.

@@ -417,6 +417,7 @@ constexpr double kCullObstacles = 512;   // per stage, mean
 
 bool cull_pays(const psdf_batch_plan& p) {
   double pairs = 0.0;
+  if (p.n_inst > 0 && !cull_edges_bounded(p.fp[0])) return false;   // one eps for all
   for (int k = 0; k < p.n_inst; ++k) {
     pairs += (double)p.desc[k].N * p.desc[k].M;
     // a needle of a footprint has no bound: one wave would evaluate all

@@ -286,7 +286,7 @@ __device__ __forceinline__ void cull_obstacle(float (&v)[4][4], const float* __r
 constexpr float kEmptyBox = -__builtin_huge_valf();
 
 __device__ __forceinline__ float cull_minl2(float eps) {
-  const float l = 4e6f * eps;
+  const float l = kCullEdge * eps;
   return fmaxf(l * l, 1e-24f);
 }
 

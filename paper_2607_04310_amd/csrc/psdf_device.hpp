@@ -39,6 +39,9 @@ namespace psdf {
 constexpr int kMaxFp = 16;    // footprint vertices
 constexpr int kMaxObst = 16;  // edges per obstacle
 constexpr uint64_t kEmptyKey = ~0ull;
+// Culled forms: an edge shorter than this times eps leaves its obstacle without a
+// bound (its normal is shrunk, and its frame's distances are off).
+constexpr float kCullEdge = 4e6f;
 
 // Footprint constants in the robot-local frame (counter-clockwise), prepared
 // once on the host in double precision and rounded to float.  Slots l >= m

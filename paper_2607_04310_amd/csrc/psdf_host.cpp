@@ -28,7 +28,7 @@ namespace {
 bool cull_plain(const FpConst& F, int mbar, int N, int M) {
   const double cost =
       (double)N * M * (F.m <= 8 ? F.m : kMaxFp) * (obst_class(mbar) == 4 ? 1 : 2);
-  return cost >= 4.6e6 && std::isfinite(F.cull_tau);
+  return cost >= 4.6e6 && std::isfinite(F.cull_tau) && cull_edges_bounded(F);
 }
 
 thread_local std::string g_err;

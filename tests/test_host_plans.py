@@ -151,3 +151,18 @@ emit(out)
     both = ["cull_list", "cull_stage_kernel"]
     assert got == [[both, ["stage_batch", "cull_stage_edges"]],
                    ["batch_kernel", True, ["stage_batch"]], ["batch_kernel", True, ["stage_batch"]]]
+
+
+def test_eps_that_leaves_edges_without_a_bound(tmp_path_factory):
+    """An edge shorter than 4e6 eps leaves its obstacle without a bound: beyond a
+    centimetre, where ordinary maps have such edges, calls take the full evaluation."""
+    got = script("""
+out = []
+for eps in (1e-12, 2e-9, 3e-9, 1e-7, 1e-3):
+    par = params(eps=eps)
+    rc, p = plan([(HEX, 300, 16384, 65536)], par=par)
+    out.append([run(p)[0], bound(p)[0] == "cull_list", plain(HEX, 50, 65536, par=par)[0]])
+emit(out)
+""", tmp_path_factory)
+    culled, full = ["cull_list", True, "cull_main"], ["batch_kernel", False, "main_kernel"]
+    assert got == [culled, culled, full, full, full]
