@@ -447,7 +447,8 @@ int psdf_batch_screened(psdf_batch_plan* plan, const float* theta, int32_t pool,
  * (stage_cand counts the seed).  Without the optional outputs, a plan that
  * psdf_batch evaluates culled is evaluated the same way here (boxes instead of
  * circles, lists that leave no stage to a full evaluation), from the staged
- * boxes where psdf_batch_stage took them. */
+ * boxes where psdf_batch_stage took them, and with an eps above 1e-6, where no
+ * circle bounds the evaluation, every pair is evaluated. */
 int psdf_batch_screened_bound(psdf_batch_plan* plan, const float* poses, const float* ax,
                               const float* ay, const float* bx, const float* by,
                               const int32_t* obst_off, float* d, int32_t* edge, int32_t* obst,

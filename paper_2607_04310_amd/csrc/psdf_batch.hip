@@ -692,7 +692,12 @@ static int screened_run(psdf_batch_plan* p, bool bound, const float* theta, int3
                          "from (stage again, or psdf_batch_unstage)");
     circ = p->d_circ;
   }
-  if (bound && p->culled && !stage_cand && !stage_cert && !cand_keys) {
+  const bool outputs_alone = !stage_cand && !stage_cert && !cand_keys;
+  // nothing bounds the evaluation: all pairs, as psdf_batch takes them (a culled
+  // plan's eps is smaller)
+  if (bound && outputs_alone && p->n_inst > 0 && !circles_bounded(p->fp[0]))
+    return run(p, poses, ax, ay, bx, by, off, d, edge, obst, grad, keys, stream, false);
+  if (bound && p->culled && outputs_alone) {
     // the same scheme with boxes for circles and lists that leave no stage
     // uncertified: nothing to fall back from, two launches.  (On 64 x 50 x
     // 16384 the circles' 512-entry lists leave some stages of most draws to

@@ -39,6 +39,11 @@ inline int obst_class(int mbar) { return mbar <= 4 ? 4 : (mbar <= 8 ? 8 : 16); }
 // (4 cm) 23 us and full 182, but eps 1e-7 (0.4 m) 1460 and eps 1e-6 2140.
 inline bool cull_edges_bounded(const FpConst& F) { return kCullEdge * F.eps <= 0.01f; }
 
+// Whether eps leaves the screens' circles a bound of the evaluation.  Its frame of
+// an edge of length L is shrunk by eps / L, which moves a distance r by r eps / L;
+// the circles have a millimetre to spare: 0.1 m edges at 100 m.
+inline bool circles_bounded(const FpConst& F) { return F.eps <= 1e-6f; }
+
 // Kernel timer: bracket one launch of the dominant kernel with events.
 void timer_begin(hipStream_t st);
 void timer_end(hipStream_t st);

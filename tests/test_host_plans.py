@@ -166,3 +166,23 @@ emit(out)
 """, tmp_path_factory)
     culled, full = ["cull_list", True, "cull_main"], ["batch_kernel", False, "main_kernel"]
     assert got == [culled, culled, full, full, full]
+
+
+def test_bound_form_where_eps_leaves_no_bound(tmp_path_factory):
+    """Where eps moves the evaluation's distances by more than the circles have to
+    spare, the bound form evaluates every pair, as psdf_batch does; below, plans
+    that are not culled for their eps are screened by circles, as they were."""
+    got = script("""
+out = []
+for insts in ([(HEX, 300, 16384, 65536)], [(HEX, 20, 100, 400)]):
+    for eps in (3e-9, 1e-6, 2e-6, 1e-2):
+        rc, p = plan(insts, par=params(eps=eps))
+        out.append(["screen_bound" in bound(p), run(p)])
+        out[-1].append(bound(p) == out[-1][1])
+        assert stage(p)[0] == 0
+        out[-1].append(bound(p) == out[-1][1])
+        del out[-1][1]
+emit(out)
+""", tmp_path_factory)
+    assert got == 2 * [[True, False, False], [True, False, False],
+                       [False, True, True], [False, True, True]]
