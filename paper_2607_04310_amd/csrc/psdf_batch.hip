@@ -415,15 +415,26 @@ __global__ __launch_bounds__(64) void batch_finish_kernel(
 constexpr double kCullPairs = 4e6;
 constexpr double kCullObstacles = 512;   // per stage, mean
 
+// A needle of a footprint, against obstacles that are no convex polygons: a stage
+// may walk the list of all, about 17 us per segment where the chip is not full of
+// stages, against 9 us per million pairs in full.  Chains of three edges, corner of
+// 0.1 degrees, full / culled: 1 x 250 x 16384 76 / 289 us, 4 x 200 x 16384 154 / 258,
+// 1 x 2000 x 16384 318 / 283; up to 64 stages the list leaves most of them out,
+// unless the corner is below a degree: 16 x 50 x 16384 5 degrees 152 / 60.
+constexpr double kNeedlePairs = 1.6e6;   // per segment of the largest instance
+
 bool cull_pays(const psdf_batch_plan& p) {
-  double pairs = 0.0;
+  double pairs = 0.0, needle = 0.0;
   if (p.n_inst > 0 && !cull_edges_bounded(p.fp[0])) return false;   // one eps for all
   for (int k = 0; k < p.n_inst; ++k) {
     pairs += (double)p.desc[k].N * p.desc[k].M;
+    const float open = p.fp[k].cull_open;
+    if (open > kThinNeedle || (open > kNeedle && p.desc[k].N > kAxisHorizon))
+      needle = std::max(needle, kNeedlePairs * ((p.desc[k].M + kSegObst - 1) / kSegObst));
     // a needle of a footprint has no bound: one wave would evaluate all
     if (p.desc[k].M > kSegObst && !std::isfinite(p.fp[k].cull_tau)) return false;
   }
-  return pairs >= kCullPairs && pairs >= kCullObstacles * p.total_stages;
+  return pairs >= kCullPairs && pairs >= kCullObstacles * p.total_stages && pairs >= needle;
 }
 
 // Gives the culled evaluation's tables back: the plan takes the full one.

@@ -361,6 +361,7 @@ __global__ __launch_bounds__(256) void cull_stage_edges_kernel(CullArgs A, float
 // rectangles), or of every staged box (17 MB in 7.5 us, the chain of loads
 // and two barriers).  Each thread holds kCullPer obstacles whose loads are all
 // in flight together.
+constexpr int kAxisHorizon = 64;   // stages whose axes are tried on the list of any instance
 constexpr int kAxisStages = kCullThreads / kMaxFp;   // stages whose axes are held at once
 template <int MI, bool STAGED>
 __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
@@ -500,12 +501,16 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
     }
     return no;
   };
-  // The axes here cost about 30 us at 50 stages and three axes, and more with
-  // both; an open obstacle per segment left on the list costs every stage a 64th
-  // of a round, one to three times: worth it where a few hundred are open.  16 x 50
-  // x 16384 chains of three edges, without -> with: corner of 5 degrees 164 -> 60
-  // us, of 0.1 degrees 269 -> 115, but 20 degrees, with fewer open, 38 -> 55.
-  if (count() > 64 * (F.m + 1)) {
+  // The axes here cost half a microsecond a stage (three axes, one work-group per
+  // CU), one after the other; an open obstacle per segment left on the list costs
+  // every stage, which run beside each other, a 64th of a round, one to three times.
+  // Worth it where a few hundred are open, and the horizon is short or the lists
+  // many.  Chains of three edges, without -> with: 16 x 50 stages x 16384, corner of
+  // 5 degrees 164 -> 60 us, of 0.1 degrees 269 -> 115, but 20 degrees, with fewer
+  // open, 38 -> 55; 5 degrees, 16 x 100 x 16384 189 -> 80, 16 x 250 x 16384 190 ->
+  // 158, but 16 x 200 x 4096 91 -> 157, 1 x 2000 x 16384 217 -> 1260, 1 x 20000 x
+  // 2048 235 -> 12300 (full evaluation 376).
+  if (count() > 64 * (F.m + 1) && in.N <= max(kAxisHorizon, 16 * ((in.M + kSegObst - 1) / kSegObst))) {
     for (int t0 = 0; t0 < in.N; t0 += kAxisStages) {
       __syncthreads();   // the last stages' axes are read
       {
@@ -527,20 +532,27 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
         if (l == 0) s_pos[tid / kMaxFp] = at_p;
       }
       __syncthreads();
-      for (int t = 0; t < min(kAxisStages, in.N - t0); ++t) {
-        const float2 p = s_pos[t];
-        float gap[kCullPer];
+      // two stages at a time (their table rows exist past the last stage)
+      for (int t = 0; t < min(kAxisStages, in.N - t0); t += 2) {
+        const float2 p0 = s_pos[t], p1 = s_pos[t + 1];
+        float gap0[kCullPer], gap1[kCullPer];
 #pragma unroll
-        for (int q = 0; q < kCullPer; ++q) gap[q] = -__builtin_huge_valf();
+        for (int q = 0; q < kCullPer; ++q) gap0[q] = gap1[q] = -__builtin_huge_valf();
         for (int l = 0; l < F.m; ++l) {
-          const float4 n = s_axes[t * kMaxFp + l];
+          const float4 n0 = s_axes[t * kMaxFp + l], n1 = s_axes[(t + 1) * kMaxFp + l];
 #pragma unroll
-          for (int q = 0; q < kCullPer; ++q)
-            gap[q] = fmaxf(gap[q], cull_axis(cull_box(box[q]), p.x, p.y, n.x, n.y) - n.z);
+          for (int q = 0; q < kCullPer; ++q) {
+            const CullBox b = cull_box(box[q]);
+            gap0[q] = fmaxf(gap0[q], cull_axis(b, p0.x, p0.y, n0.x, n0.y) - n0.z);
+            gap1[q] = fmaxf(gap1[q], cull_axis(b, p1.x, p1.y, n1.x, n1.y) - n1.z);
+          }
         }
 #pragma unroll
-        for (int q = 0; q < kCullPer; ++q)
-          open[q] = open[q] && cull_separates(F, cull_box(box[q]), p.x, p.y, gap[q]);
+        for (int q = 0; q < kCullPer; ++q) {
+          const CullBox b = cull_box(box[q]);
+          open[q] = open[q] && cull_separates(F, b, p0.x, p0.y, gap0[q]) &&
+                    cull_separates(F, b, p1.x, p1.y, gap1[q]);
+        }
       }
     }
 #pragma unroll

@@ -39,6 +39,12 @@ inline int obst_class(int mbar) { return mbar <= 4 ? 4 : (mbar <= 8 ? 8 : 16); }
 // (4 cm) 23 us and full 182, but eps 1e-7 (0.4 m) 1460 and eps 1e-6 2140.
 inline bool cull_edges_bounded(const FpConst& F) { return kCullEdge * F.eps <= 0.01f; }
 
+// Footprints with a corner below 11 degrees and below 1.1 (FpConst::cull_open, the
+// tangent of half an exterior angle): the bounds of open chains and of polygons that
+// are not strictly convex are loose, and where a call is small the full evaluation
+// is over before the culled one has left them out.
+constexpr float kNeedle = 10.0f, kThinNeedle = 100.0f;
+
 // Whether eps leaves the screens' circles a bound of the evaluation.  Its frame of
 // an edge of length L is shrunk by eps / L, which moves a distance r by r eps / L;
 // the circles have a millimetre to spare: 0.1 m edges at 100 m.

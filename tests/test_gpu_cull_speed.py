@@ -58,14 +58,14 @@ def _time(torch, call, n=10):
     return best
 
 
-def _batch(kind, fp):
+def _batch(kind, fp, k=16, N=50, M=16384):
     import torch
     from paper_2607_04310_amd import api
     rng = np.random.default_rng(5)
     insts = []
-    for _ in range(16):
-        edges, off, mbar = _map(rng, 16384, kind)
-        insts.append(SimpleNamespace(footprint=fp, poses=inputs.path_poses(rng, 50, -HALF / 2, HALF / 2),
+    for _ in range(k):
+        edges, off, mbar = _map(rng, M, kind)
+        insts.append(SimpleNamespace(footprint=fp, poses=inputs.path_poses(rng, N, -HALF / 2, HALF / 2),
                                      edges=edges, obst_off=off))
     a = api.Batch(insts, mbar=mbar)
     b = api.Batch(insts, mbar=mbar, exhaustive=True)
@@ -99,3 +99,13 @@ def test_staging_does_not_slow_the_bound_form(kind, fp):
 def test_batch_is_not_slower_than_the_full_evaluation(kind, fp):
     full, out = _batch(kind, FOOTPRINTS[fp])
     assert max(out.values()) <= 1.1 * full, (full, out)
+
+
+@pytest.mark.parametrize("k,N,M", [(1, 300, 16384), (1, 2000, 16384), (1, 20000, 2048), (16, 100, 16384),
+                                   (16, 200, 4096), (4, 200, 16384)])
+@pytest.mark.parametrize("fp", ["20 degrees", "5 degrees", "0.1 degrees"])
+def test_long_horizons_are_not_slower(fp, k, N, M):
+    """(The bound form of a batch that is not culled is screened by circles, which
+    leave chains to its full evaluation.)"""
+    full, out = _batch("chains", FOOTPRINTS[fp], k, N, M)
+    assert out["culled"] <= 1.25 * full, (full, out)

@@ -186,3 +186,18 @@ emit(out)
 """, tmp_path_factory)
     assert got == 2 * [[True, False, False], [True, False, False],
                        [False, True, True], [False, True, True]]
+
+
+def test_sizes_and_footprints_that_are_culled(tmp_path_factory):
+    """Footprints with a sharp corner, against which what is no
+    convex polygon has a loose bound, ask for larger problems."""
+    got = script("""
+def needle(w):
+    return [[-0.5, 0.0], [0.5, -w], [0.5, w]]
+blunt, thin, thinner = needle(0.176), needle(0.0437), needle(8.7e-4)
+batches = [run(plan([(fp, N, M, 4 * M)] * k)[1])[0] == "cull_list" for fp, k, N, M in (
+    (blunt, 1, 300, 16384), (thin, 1, 300, 16384), (thin, 1, 2000, 16384), (thin, 16, 64, 16384),
+    (thinner, 16, 64, 16384), (thinner, 1, 2000, 16384), (thinner, 1, 20000, 2048))]
+emit(batches)
+""", tmp_path_factory)
+    assert got == [True, False, True, True, False, True, True]
