@@ -23,7 +23,7 @@
 // call the two separated, and the box as it is bounds the distance.  Such an
 // obstacle is stored with its box as it is and a mark; the list enlarges it, and
 // tries the stages' axes where that leaves too many (cull_list_kernel), the stage
-// kernel tries its axes, the plain kernel enlarges.  16 x 50 stages x 16384 chains of
+// kernel tries its axes, the plain kernel does the one or the other.  16 x 50 stages x 16384 chains of
 // three edges, enlarged boxes stored -> enlarged where used -> and axes tried, us:
 // hexagon 178 -> 27 -> 25 (full evaluation 240), equilateral triangle 181 -> 27 -> 26
 // (153), corner of 20 degrees 202 -> 56 -> 40 (150), of 5 degrees 331 -> 265 -> 60
@@ -986,6 +986,12 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
 // latency (12 to 14 us) up to about a million pairs; one pose against 1 M
 // rectangles reads 68 MB in 20 us (full form 24 us, its evaluations of every
 // obstacle), 50 x 65536 takes 17 us (54 us).
+// Loose obstacles (open chains, polygons that are not strictly convex) are
+// enlarged for blunt footprints and tried on the stage's axes for sharp ones (a
+// corner below 53 degrees: an enlargement by more than twice the size).  200 x 16384
+// chains, enlarged -> axes: hexagon 33 us either way, corner of 20 degrees 36 -> 34,
+// 5 degrees 62 -> 39 (full 48), 0.1 degrees 80 -> 59 (47: choose_shape keeps it full).
+constexpr float kCullSharp = 2.0f;
 struct SegSource {
   const float* ax;
   const float* ay;
@@ -1079,9 +1085,11 @@ void cull_main_kernel(
       px = p[0]; py = p[1];
       sincosf(p[2], &sn, &cs);
       if (lane < F.m) fs[lane] = cull_slot(F, lane, cs, sn);
+      wave_sync();
     }
     const bool within = fmaxf(fabsf(px), fabsf(py)) < kCullMax;
     const bool pose_ok = isfinite(px) && isfinite(py) && isfinite(cs) && isfinite(sn);
+    const bool sharp = F.cull_open > kCullSharp;
     CullBest best{kEmptyKey, 0, make_int4(0, 0, 0, 0)};
     float d2[kBoxRounds];   // NaN: no edge
     uint32_t kb = 0xffffffffu;
@@ -1089,7 +1097,8 @@ void cull_main_kernel(
     for (int r = 0; r < kBoxRounds; ++r) {
       const float4 b = lbox[64 * r + lane];
       const bool empty = b.x == kEmptyBox;
-      const float x = cull_dist2(F, b, px, py, within);
+      const float x = sharp ? cull_stage_dist2(F, fs, b, px, py, within)
+                            : cull_dist2(F, b, px, py, within);
       d2[r] = empty ? __builtin_nanf("") : x;
       kb = min(kb, empty ? 0xffffffffu : __float_as_uint(d2[r]));
     }

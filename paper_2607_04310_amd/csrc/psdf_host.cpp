@@ -24,11 +24,15 @@ namespace {
 // 21.1 / 19.0 us, 0.41 M 16.3 / 19.5, 1 x 1000003 31.2 / 27.2, 3.3 M 57 / 22;
 // m = 4: 0.82 M 18.2 / 18.8, 1.3 M 24.0 / 19.9; eight edges: 0.41 M
 // 32 / 28, 0.33 M 26 / 28, 3.3 M 98 / 38.
-// A footprint without a bound (a needle) would have every obstacle evaluated.
+// A footprint without a bound (a needle) would have every obstacle evaluated, and
+// one with a sharp corner has loose bounds of what is no convex polygon, which the
+// host cannot see: full / culled, open chains, corner of 5 degrees, N M m = 9.8 M
+// 47 / 39 to 40 / 44, 4.9 M 33 / 39; of 0.1 degrees 9.8 M 47 / 59, 39 M 144 / 128.
 bool cull_plain(const FpConst& F, int mbar, int N, int M) {
-  const double cost =
-      (double)N * M * (F.m <= 8 ? F.m : kMaxFp) * (obst_class(mbar) == 4 ? 1 : 2);
-  return cost >= 4.6e6 && std::isfinite(F.cull_tau) && cull_edges_bounded(F);
+  const int cls = obst_class(mbar), slots = F.m <= 8 ? F.m : kMaxFp;
+  const double cost = (double)N * M * slots * (cls == 4 ? 1 : 2);
+  const double least = F.cull_open <= kNeedle ? 4.6e6 : F.cull_open <= kThinNeedle ? 9e6 : 2.5e7;
+  return cost >= least && std::isfinite(F.cull_tau) && cull_edges_bounded(F);
 }
 
 thread_local std::string g_err;

@@ -109,3 +109,34 @@ def test_long_horizons_are_not_slower(fp, k, N, M):
     leave chains to its full evaluation.)"""
     full, out = _batch("chains", FOOTPRINTS[fp], k, N, M)
     assert out["culled"] <= 1.25 * full, (full, out)
+
+
+def _plain(fp, N, M, e, off, mbar):
+    import torch
+    from paper_2607_04310_amd import api
+    rng = np.random.default_rng(7)
+    es = api.EdgeSet(e, off, mbar)
+    poses = torch.tensor(inputs.path_poses(rng, N, -HALF / 2, HALF / 2), device="cuda")
+    blk, sb = (64 if M <= 1024 else 256), 1       # the full form's automatic shape
+    while sb < 64 and (M + 63) // 64 * ((N + 2 * sb - 1) // (2 * sb)) >= 4096:
+        sb *= 2
+    ws = api.workspace(N, M, "cuda")
+    res, ms = [], []
+    for shape in ((0, 0), (blk, sb)):
+        api.set_launch_shape(*shape)
+        try:
+            out = api.psdf_grad(fp, poses, es, ws=ws)
+            res.append([t.clone() for t in out])
+            ms.append(_time(torch, lambda: api.psdf_grad(fp, poses, es, out=out, ws=ws)))
+        finally:
+            api.set_launch_shape(0, 0)
+    assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(*res))
+    print(N, M, mbar, "chosen, full:", [round(1e3 * t, 1) for t in ms], flush=True)
+    assert ms[0] <= 1.3 * ms[1], ms
+
+
+@pytest.mark.parametrize("kind", ["chains", "side"])
+@pytest.mark.parametrize("fp", FOOTPRINTS)
+@pytest.mark.parametrize("N,M", [(100, 16384), (200, 16384), (200, 65536), (1000, 4096)])
+def test_plain_call_is_not_slower(kind, fp, N, M):
+    _plain(FOOTPRINTS[fp], N, M, *_map(np.random.default_rng(5), M, kind))

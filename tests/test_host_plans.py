@@ -198,6 +198,10 @@ blunt, thin, thinner = needle(0.176), needle(0.0437), needle(8.7e-4)
 batches = [run(plan([(fp, N, M, 4 * M)] * k)[1])[0] == "cull_list" for fp, k, N, M in (
     (blunt, 1, 300, 16384), (thin, 1, 300, 16384), (thin, 1, 2000, 16384), (thin, 16, 64, 16384),
     (thinner, 16, 64, 16384), (thinner, 1, 2000, 16384), (thinner, 1, 20000, 2048))]
-emit(batches)
+calls = [plain(fp, N, M, mbar=b)[0] == "cull_main" for fp, N, M, b in (
+    (blunt, 100, 16384, 4), (thin, 100, 16384, 4), (thin, 200, 16384, 4), (thinner, 200, 16384, 4),
+    (thinner, 600, 16384, 4))]
+emit([batches, calls])
 """, tmp_path_factory)
-    assert got == [True, False, True, True, False, True, True]
+    assert got == [[True, False, True, True, False, True, True],
+                   [True, False, True, False, True]]
