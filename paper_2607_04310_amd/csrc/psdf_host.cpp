@@ -28,11 +28,18 @@ namespace {
 // one with a sharp corner has loose bounds of what is no convex polygon, which the
 // host cannot see: full / culled, open chains, corner of 5 degrees, N M m = 9.8 M
 // 47 / 39 to 40 / 44, 4.9 M 33 / 39; of 0.1 degrees 9.8 M 47 / 59, 39 M 144 / 128.
+// A stage costs 3 ns or more however few its obstacles: it has to be more than
+// its 64-obstacle tiles are in full.  20000 stages, eight edges, full / culled: m = 3
+// 128 obstacles 69 / 80, 192 86 / 81; m = 4 64 55 / 70, 128 76 / 78; m = 6 64
+// 67 / 74, 96 99 / 75; m = 8 64 74 / 76; m = 16 16 145 / 91; sixteen edges: m = 3 48
+// 102 / 85.
 bool cull_plain(const FpConst& F, int mbar, int N, int M) {
   const int cls = obst_class(mbar), slots = F.m <= 8 ? F.m : kMaxFp;
   const double cost = (double)N * M * slots * (cls == 4 ? 1 : 2);
   const double least = F.cull_open <= kNeedle ? 4.6e6 : F.cull_open <= kThinNeedle ? 9e6 : 2.5e7;
-  return cost >= least && std::isfinite(F.cull_tau) && cull_edges_bounded(F);
+  const long tile = slots * (cls == 4 ? 1 : cls == 8 ? 2 : 6);
+  return cost >= least && ((long)M + 63) / 64 * tile >= 18 && std::isfinite(F.cull_tau) &&
+         cull_edges_bounded(F);
 }
 
 thread_local std::string g_err;

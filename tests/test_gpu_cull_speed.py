@@ -140,3 +140,15 @@ def _plain(fp, N, M, e, off, mbar):
 @pytest.mark.parametrize("N,M", [(100, 16384), (200, 16384), (200, 65536), (1000, 4096)])
 def test_plain_call_is_not_slower(kind, fp, N, M):
     _plain(FOOTPRINTS[fp], N, M, *_map(np.random.default_rng(5), M, kind))
+
+
+@pytest.mark.parametrize("m", [3, 4, 6, 16])
+@pytest.mark.parametrize("mbar,M", [(8, 16), (8, 64), (8, 100), (8, 200), (16, 16), (4, 257), (4, 400)])
+def test_many_stages_against_a_small_map(m, mbar, M):
+    rng = np.random.default_rng(9)
+    c = rng.uniform(-HALF / 8, HALF / 8, (M, 1, 2))
+    a = np.arange(mbar) * 2 * np.pi / mbar + rng.uniform(0, 1, (M, 1))
+    e = _closed(c + rng.uniform(0.1, 0.5, (M, 1, 1)) * np.stack([np.cos(a), np.sin(a)], 2))
+    t = np.arange(m) * 2 * np.pi / m
+    fp = (0.5 * np.stack([np.cos(t), np.sin(t)], 1)).astype(np.float32)
+    _plain(fp, 20000, M, e.reshape(-1, 4).astype(np.float32), inputs.csr_offsets([mbar] * M), mbar)

@@ -189,7 +189,7 @@ emit(out)
 
 
 def test_sizes_and_footprints_that_are_culled(tmp_path_factory):
-    """Footprints with a sharp corner, against which what is no
+    """Small maps, and footprints with a sharp corner, against which what is no
     convex polygon has a loose bound, ask for larger problems."""
     got = script("""
 def needle(w):
@@ -200,8 +200,9 @@ batches = [run(plan([(fp, N, M, 4 * M)] * k)[1])[0] == "cull_list" for fp, k, N,
     (thinner, 16, 64, 16384), (thinner, 1, 2000, 16384), (thinner, 1, 20000, 2048))]
 calls = [plain(fp, N, M, mbar=b)[0] == "cull_main" for fp, N, M, b in (
     (blunt, 100, 16384, 4), (thin, 100, 16384, 4), (thin, 200, 16384, 4), (thinner, 200, 16384, 4),
-    (thinner, 600, 16384, 4))]
+    (thinner, 600, 16384, 4), (HEX, 20000, 64, 8), (HEX, 20000, 65, 8), (HEX, 20000, 64, 16),
+    (HEX[:3], 20000, 320, 4), (HEX[:3], 20000, 321, 4), (HEX[:3], 20000, 128, 8), (HEX[:3], 20000, 129, 8))]
 emit([batches, calls])
 """, tmp_path_factory)
     assert got == [[True, False, True, True, False, True, True],
-                   [True, False, True, False, True]]
+                   [True, False, True, False, True, False, True, True, False, True, False, True]]
