@@ -95,9 +95,16 @@ __device__ __forceinline__ CullBox cull_box(const float4& b) {
 }
 
 // What a loose obstacle's box is enlarged by on every side (0 for the others).
-__device__ __forceinline__ float cull_enlarged(const FpConst& F, const CullBox& b) {
+__device__ __forceinline__ float cull_enlargement(const FpConst& F, const CullBox& b) {
   const float size = (b.hix - b.lox) + (b.hiy - b.loy);
   return b.loose ? fminf(F.cull_open * size, kCullPlane) : 0.f;
+}
+// The box with that, unmarked.  (Its rounding is within the enlargement by rel *
+// size that the box has: rel is above 1e-5.)
+__device__ __forceinline__ float4 cull_enlarged(const FpConst& F, const float4& s) {
+  const CullBox b = cull_box(s);
+  const float e = cull_enlargement(F, b);
+  return b.loose ? make_float4(b.lox - e, b.loy - e, b.hix + e, b.hiy + e) : s;
 }
 
 // The least of (W - p) . n over the points W of a box.
@@ -128,6 +135,7 @@ __device__ __forceinline__ bool cull_separates(const FpConst& F, const CullBox& 
 // in what the evaluation reads next: the box, the obstacle's index, first edge
 // (global) and edge count, flags, and the points of a closed polygon of at most
 // four edges (A_j) or of one edge (A_0, B_0).
+constexpr int kListLoose = 1 << 30;
 constexpr int kRecClosed = 1, kRecBad = 2, kRecPoints = 4;
 struct CullRec {
   float4 box;
@@ -164,7 +172,7 @@ struct CullArgs {
   const float4* sbox;   // staged: every obstacle's box (kEmptyBox in lo.x: no edge) and
   const CullRec* srec;  // record, at slot0 + obstacle (null: from the edges)
   CullRec* rec;   // list slots
-  int* cnt;       // per segment: list length
+  int* cnt;       // per segment: list length, kListLoose where a loose obstacle is in it
   float* d;
   int* edge;
   int* obst;
@@ -465,39 +473,56 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
 
   // the list, in obstacle order within each wave; open: loose obstacles that only
   // the stages' own axes can leave out
-  bool take[kCullPer], open[kCullPer];
+  bool take[kCullPer], open[kCullPer], marked = false;
 #pragma unroll
   for (int q = 0; q < kCullPer; ++q) {
     const CullBox b = cull_box(box[q]);
-    const float ox = fmaxf(b.lox - phx, plx - b.hix), oy = fmaxf(b.loy - phy, ply - b.hiy);
-    const float gx = fmaxf(ox, 0.f), gy = fmaxf(oy, 0.f);
+    const float gx = fmaxf(fmaxf(b.lox - phx, plx - b.hix), 0.f);
+    const float gy = fmaxf(fmaxf(b.loy - phy, ply - b.hiy), 0.f);
     const bool far = box[q].x == box[q].x && fmaf(gx, gx, gy * gy) > bar2 && !all;
-    const float e = cull_enlarged(F, b);
-    const float ex = fmaxf(ox - e, 0.f), ey = fmaxf(oy - e, 0.f);
-    open[q] = box[q].x == box[q].x && far && !none && b.loose && !(fmaf(ex, ex, ey * ey) > bar2);
-    take[q] = box[q].x != kEmptyBox && !none && (!far || open[q]);
+    take[q] = box[q].x != kEmptyBox && !none && !far;
+    open[q] = far && !none && b.loose;
+    marked = marked || b.loose;
+  }
+  const bool some = __ballot(marked) != 0;   // loose obstacles in this wave
+  if (some) {
+#pragma unroll
+    for (int q = 0; q < kCullPer; ++q) {
+      const CullBox b = cull_box(box[q]);
+      const float e = cull_enlargement(F, b);
+      const float ex = fmaxf(fmaxf(b.lox - phx, plx - b.hix) - e, 0.f);
+      const float ey = fmaxf(fmaxf(b.loy - phy, ply - b.hiy) - e, 0.f);
+      open[q] = open[q] && !(fmaf(ex, ex, ey * ey) > bar2);
+      take[q] = take[q] || open[q];
+    }
   }
   // takes the counts (listed, and open among them: at most kSegObst each)
   int at[kCullPer], base, total;
+  bool loose;
   auto count = [&]() {
-    int n = 0, no = 0;
+    int n = 0, no = 0, lo = 0;
 #pragma unroll
     for (int q = 0; q < kCullPer; ++q) {
       const uint64_t m = __ballot(take[q]);
       at[q] = n + lanes_below(m);
       n += (int)__popcll(m);
-      no += (int)__popcll(__ballot(open[q]));
+      if (some) {
+        no += (int)__popcll(__ballot(open[q]));
+        lo |= __ballot(take[q] && cull_box(box[q]).loose) ? kListLoose : 0;
+      }
     }
-    if (lane == 0) s_n[w] = n | no << 16;
+    if (lane == 0) s_n[w] = n | no << 16 | lo;
     __syncthreads();
     base = S.slot0;
     total = no = 0;
+    loose = false;
 #pragma unroll
     for (int i = 0; i < kCullThreads / 64; ++i) {
       const int c = s_n[i] & 0xffff;
       base += i < w ? c : 0;
       total += c;
-      no += s_n[i] >> 16;
+      no += s_n[i] >> 16 & 0xfff;
+      loose = loose || (s_n[i] & kListLoose);
     }
     return no;
   };
@@ -568,7 +593,7 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
       if (STAGED) *r = A.srec[S.slot0 + k];
       else ld[q].record(r, box[q], S.o0 + k, flags[q]);
     }
-  if (tid == 0) A.cnt[blockIdx.x] = total;
+  if (tid == 0) A.cnt[blockIdx.x] = total | (loose ? kListLoose : 0);
 }
 
 constexpr int kCullRounds = 4;    // list entries kept in registers: 64 x this
@@ -609,31 +634,21 @@ struct CullBest {
   }
 };
 
-// Squared distance from (px, py) to a stored box, a loose one enlarged (taken off
-// the differences, which are exact to their own rounding); -1 for an irregular
-// obstacle, or with ok false (last as unsigned bits, within every bar).
-__device__ __forceinline__ float cull_dist2(const FpConst& F, const float4& s, float px, float py,
-                                            bool ok) {
-  const CullBox b = cull_box(s);
-  float gx = fmaxf(b.lox - px, px - b.hix), gy = fmaxf(b.loy - py, py - b.hiy);
-  if (__ballot(b.loose)) {
-    const float e = cull_enlarged(F, b);
-    gx -= e;
-    gy -= e;
-  }
-  gx = fmaxf(gx, 0.f);
-  gy = fmaxf(gy, 0.f);
+// Squared distance from (px, py) to a stored box that is not marked; -1 for an
+// irregular obstacle, or with ok false (last as unsigned bits, within every bar).
+__device__ __forceinline__ float cull_dist2(const float4& s, float px, float py, bool ok) {
+  const float gx = fmaxf(fmaxf(s.x - px, px - s.z), 0.f);
+  const float gy = fmaxf(fmaxf(s.y - py, py - s.w), 0.f);
   return (s.x == s.x && ok) ? fmaf(gx, gx, gy * gy) : -1.f;
 }
 
-// The same at a stage whose rotated footprint fs is visible to the wave: a loose
-// obstacle's box as it is, where a robot axis is sure to separate it, else 0.
+// The same at a stage whose rotated footprint fs is visible to the wave, boxes
+// marked or not: a loose obstacle's box as it is, where a robot axis is sure to
+// separate it, else 0.
 __device__ __forceinline__ float cull_stage_dist2(const FpConst& F, const FpSlot* fs,
                                                   const float4& s, float px, float py, bool ok) {
   const CullBox b = cull_box(s);
-  const float gx = fmaxf(fmaxf(b.lox - px, px - b.hix), 0.f);
-  const float gy = fmaxf(fmaxf(b.loy - py, py - b.hiy), 0.f);
-  float d2 = fmaf(gx, gx, gy * gy);
+  float d2 = cull_dist2(make_float4(b.lox, b.loy, b.hix, b.hiy), px, py, true);
   if (__ballot(b.loose)) {
     float gap = -__builtin_huge_valf();
     for (int l = 0; l < F.m; ++l)
@@ -778,14 +793,17 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
   const float px = p[0], py = p[1], th = p[2];
   const CullRec* rec = A.rec + R.slot0;
   const int* cnt = A.cnt + R.seg0;
-  const int cv = lane < nseg ? cnt[lane] : 0;
+  const int cl = lane < nseg ? cnt[lane] : 0, cv = cl & ~kListLoose;
   const FpConst& F = fp_const(A.fps, R.inst);
   FpRow fr;
   if (lane < kMaxFp) fr = A.rows[R.inst * kMaxFp + lane];
   starts[lane] = starts[64 + lane] = 0u;
 
   const bool within = fmaxf(fabsf(px), fabsf(py)) < kCullMax;
-  auto dist2 = [&](const float4& b) { return cull_stage_dist2(F, fs, b, px, py, within); };
+  const bool loose = nseg > 64 || __ballot(cl & kListLoose) != 0;
+  auto dist2 = [&](const float4& b) {
+    return loose ? cull_stage_dist2(F, fs, b, px, py, within) : cull_dist2(b, px, py, within);
+  };
 
   // ---- the list as one
   static_assert(kCullFlat == 64 * 64, "two words of starts per lane");
@@ -874,7 +892,7 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
       return k.r * 64 < total;
     }
     while (go && k.seg < nseg) {
-      const int c = k.seg < 64 ? (int)lane_u32((uint32_t)cv, k.seg) : cnt[k.seg];
+      const int c = k.seg < 64 ? (int)lane_u32((uint32_t)cv, k.seg) : cnt[k.seg] & ~kListLoose;
       float4 b[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -1018,7 +1036,7 @@ __device__ __forceinline__ FpSlot cull_slot(const FpConst& F, int l, float c, fl
   return FpSlot{rotated_slot(F, l, c, s), F.cu[l], F.cn[l], F.len[l], F.oa[l], F.ob[l]};
 }
 
-template <int MI>
+template <int MI, bool SHARP>
 __global__ __launch_bounds__(kCullThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void cull_main_kernel(
     FpConst F, const float* __restrict__ poses, int N, int SB, const float* __restrict__ ax,
@@ -1070,7 +1088,7 @@ void cull_main_kernel(
       int flags;
       ld[q].finish(A, F, box, flags);
       if (ld[q].mi == 0) box.x = kEmptyBox;
-      lbox[k] = box;
+      lbox[k] = SHARP ? box : cull_enlarged(F, box);
       le0[k] = ld[q].e0;
       lmeta[k] = (uint16_t)((ld[q].mi & 31) << 4 | (flags & 15));
     }
@@ -1089,7 +1107,6 @@ void cull_main_kernel(
     }
     const bool within = fmaxf(fabsf(px), fabsf(py)) < kCullMax;
     const bool pose_ok = isfinite(px) && isfinite(py) && isfinite(cs) && isfinite(sn);
-    const bool sharp = F.cull_open > kCullSharp;
     CullBest best{kEmptyKey, 0, make_int4(0, 0, 0, 0)};
     float d2[kBoxRounds];   // NaN: no edge
     uint32_t kb = 0xffffffffu;
@@ -1097,8 +1114,8 @@ void cull_main_kernel(
     for (int r = 0; r < kBoxRounds; ++r) {
       const float4 b = lbox[64 * r + lane];
       const bool empty = b.x == kEmptyBox;
-      const float x = sharp ? cull_stage_dist2(F, fs, b, px, py, within)
-                            : cull_dist2(F, b, px, py, within);
+      const float x = SHARP ? cull_stage_dist2(F, fs, b, px, py, within)
+                            : cull_dist2(b, px, py, within);
       d2[r] = empty ? __builtin_nanf("") : x;
       kb = min(kb, empty ? 0xffffffffu : __float_as_uint(d2[r]));
     }

@@ -477,13 +477,14 @@ static hipError_t launch_stage_min(const FpConst& F, const float* poses, int N,
     return PSDF_BY_MF(launch_main_mf, cls, ls, F, poses, N, e, partial, st, ev0, ev1);
   const dim3 grid((e.M + kSegObst - 1) / kSegObst, (N + ls.sb - 1) / ls.sb);
   ulonglong2* pk = reinterpret_cast<ulonglong2*>(partial);
-#define PSDF_CULL(MI)                                                                            \
-  hipExtLaunchKernelGGL(cull_main_kernel<MI>, grid, dim3(kCullThreads), 0, st, ev0, ev1, 0, F,   \
-                        poses, N, ls.sb, e.ax, e.ay, e.bx, e.by, e.obst_off, e.E, e.M, pk)
-  if (cls == 4) PSDF_CULL(4);
-  else if (cls == 8) PSDF_CULL(8);
-  else PSDF_CULL(16);
-#undef PSDF_CULL
+  auto launch = [&](auto kernel) {
+    hipExtLaunchKernelGGL(kernel, grid, dim3(kCullThreads), 0, st, ev0, ev1, 0, F, poses, N, ls.sb,
+                          e.ax, e.ay, e.bx, e.by, e.obst_off, e.E, e.M, pk);
+  };
+  const bool sharp = F.cull_open > kCullSharp;
+  if (cls == 4) launch(sharp ? cull_main_kernel<4, true> : cull_main_kernel<4, false>);
+  else if (cls == 8) launch(sharp ? cull_main_kernel<8, true> : cull_main_kernel<8, false>);
+  else launch(sharp ? cull_main_kernel<16, true> : cull_main_kernel<16, false>);
   return hipGetLastError();
 }
 
