@@ -206,3 +206,19 @@ emit([batches, calls])
 """, tmp_path_factory)
     assert got == [[True, False, True, True, False, True, True],
                    [True, False, True, False, True, False, True, True, False, True, False, True]]
+
+
+def test_routes_of_the_needle_tests(tmp_path_factory):
+    """The sizes of test_gpu_cull_needles.py are culled."""
+    got = script("""
+def needle(w):
+    return [[-0.5, 0.0], [0.5, -w], [0.5, w]]
+out = []
+for w in (0.1, 0.0437, 8.7e-4, 2e-6):
+    rc, p = plan([(HEX, 300, 16384, 65536)] + [(needle(w), N, M, 4 * M) for N, M in ((30, 1000), (70, 908), (3, 18))])
+    out.append(run(p)[0])
+for w in (0.1, 0.0437, 8.7e-4):
+    out.append(plain(needle(w), 300, 30011)[0])
+emit(out)
+""", tmp_path_factory)
+    assert got == 4 * ["cull_list"] + 3 * ["cull_main"]
