@@ -23,12 +23,12 @@
 // call the two separated, and the box as it is bounds the distance.  Such an
 // obstacle is stored with its box as it is and a mark; the list enlarges it, and
 // tries the stages' axes where that leaves too many (cull_list_kernel), the stage
-// kernel tries its axes, the plain kernel does the one or the other.  16 x 50 stages x 16384 chains of
-// three edges, enlarged boxes stored -> enlarged where used -> and axes tried, us:
-// hexagon 178 -> 27 -> 25 (full evaluation 240), equilateral triangle 181 -> 27 -> 26
-// (153), corner of 20 degrees 202 -> 56 -> 40 (150), of 5 degrees 331 -> 265 -> 60
-// (152); from staged boxes 358 -> 18 -> 16, 334 -> 19 -> 17, 344 -> 49 -> 32 and
-// 376 -> 256 -> 51.
+// kernel tries its axes, the plain kernel does the one or the other.  16 x 50 stages x
+// 16384 chains of three edges, enlarged boxes stored -> enlarged where used -> and
+// axes tried, us: hexagon 178 -> 27 -> 25 (full evaluation 240), equilateral triangle
+// 181 -> 27 -> 27 (153), corner of 20 degrees 202 -> 56 -> 42 (150), of 5 degrees 331 ->
+// 265 -> 52 (152); from staged boxes 358 -> 18 -> 17, 334 -> 19 -> 18, 344 -> 49 -> 34
+// and 376 -> 256 -> 45.
 // Any other obstacle (invalid, a degenerate edge, coordinates beyond 1e15) is
 // irregular: it is always evaluated.
 //
@@ -50,9 +50,9 @@
 //    obstacle has sd >= LB > T >= phi.  The wave then ends the stage
 //    (write_stage).
 // What it measured (graph replay per call, one card; full evaluation before):
-// 64 instances x 50 stages x 16384 rectangles 539 -> 41 us (list 17.5 us for
-// 67 MB of edges, stage 19 us), 512 uneven instances (23 800 stages, 2.7 M
-// edges) 583 -> 72 us (list 19.5, stage 51 us).
+// 64 instances x 50 stages x 16384 rectangles 539 -> 40 us (list 19 us for
+// 67 MB of edges, stage 17.6 us), 512 uneven instances (23 800 stages, 2.7 M
+// edges) 583 -> 73 us (list 21, stage 51 us).
 // Lists have a fixed place per segment and are rewritten by every call:
 // no counter to reset, nothing kept between calls, no capacity to exceed.
 #pragma once
@@ -365,8 +365,8 @@ __global__ __launch_bounds__(256) void cull_stage_edges_kernel(CullArgs A, float
   ld.record(srec + S.slot0 + k, box, S.o0 + k, flags);
 }
 
-// Bound: the read of every edge once (67 MB in 17.5 us at 64 x 16384
-// rectangles), or of every staged box (17 MB in 7.5 us, the chain of loads
+// Bound: the read of every edge once (67 MB in 19 us at 64 x 16384
+// rectangles), or of every staged box (17 MB in 10 us, the chain of loads
 // and two barriers).  Each thread holds kCullPer obstacles whose loads are all
 // in flight together.
 constexpr int kAxisHorizon = 64;   // stages whose axes are tried on the list of any instance
@@ -531,7 +531,7 @@ __global__ __launch_bounds__(kCullThreads) void cull_list_kernel(CullArgs A) {
   // every stage, which run beside each other, a 64th of a round, one to three times.
   // Worth it where a few hundred are open, and the horizon is short or the lists
   // many.  Chains of three edges, without -> with: 16 x 50 stages x 16384, corner of
-  // 5 degrees 164 -> 60 us, of 0.1 degrees 269 -> 115, but 20 degrees, with fewer
+  // 5 degrees 164 -> 52 us, of 0.1 degrees 269 -> 115, but 20 degrees, with fewer
   // open, 38 -> 55; 5 degrees, 16 x 100 x 16384 189 -> 80, 16 x 250 x 16384 190 ->
   // 158, but 16 x 200 x 4096 91 -> 157, 1 x 2000 x 16384 217 -> 1260, 1 x 20000 x
   // 2048 235 -> 12300 (full evaluation 376).
@@ -1002,8 +1002,8 @@ __global__ __launch_bounds__(64) void cull_stage_kernel(CullArgs A) {
 // bar that the nearest sets.  The segment's minimum is exact, so the
 // epilogue reduces these partials as it does the full kernel's.  Bound by
 // latency (12 to 14 us) up to about a million pairs; one pose against 1 M
-// rectangles reads 68 MB in 20 us (full form 24 us, its evaluations of every
-// obstacle), 50 x 65536 takes 17 us (54 us).
+// rectangles reads 68 MB in 22 us (full form 24 us, its evaluations of every
+// obstacle), 50 x 65536 takes 19 us (54 us).
 // Loose obstacles (open chains, polygons that are not strictly convex) are
 // enlarged for blunt footprints and tried on the stage's axes for sharp ones (a
 // corner below 53 degrees: an enlargement by more than twice the size).  200 x 16384
