@@ -423,18 +423,37 @@ constexpr double kCullObstacles = 512;   // per stage, mean
 // unless the corner is below a degree: 16 x 50 x 16384 5 degrees 152 / 60.
 constexpr double kNeedlePairs = 1.6e6;   // per segment of the largest instance
 
+// An instance of more than 64 segments has its lists walked one after the other,
+// 0.7 us each, by every stage.  Full / culled: 3 x 16 x 130000 87 / 116 us, 2 x 32 x
+// 130000 116 / 88, 3 x 4 x 400000 76 / 322, 1 x 32 x 400000 156 / 257, 1 x 64 x 400000
+// 262 to 340 / 254 to 300; eight edges 2 x 32 x 130000 208 / 157, 1 x 32 x 400000
+// 293 / 288; sixteen 5 x 8 x 130000 328 / 324.
+double long_pairs(int mi_class) {        // per segment of such an instance
+  return mi_class == 4 ? 1e5 : mi_class == 8 ? 5e4 : 2e4;
+}
+
+// The list kernel reads obstacles of more than four edges edge by edge, which the
+// stages that share a list have to pay for.  Full / culled, pairs 4.2 million: eight
+// edges, 1 stage per instance of 16384 322 / 372 us, 2 192 / 190; sixteen edges, 2
+// stages 452 / 836, 4 329 / 400, 8 286 / 160.
+double cull_stages(int mi_class) { return mi_class == 4 ? 0.0 : mi_class == 8 ? 2.0 : 6.0; }
+
 bool cull_pays(const psdf_batch_plan& p) {
-  double pairs = 0.0, needle = 0.0;
+  double pairs = 0.0, obst = 0.0, least = kCullPairs;
   if (p.n_inst > 0 && !cull_edges_bounded(p.fp[0])) return false;   // one eps for all
   for (int k = 0; k < p.n_inst; ++k) {
     pairs += (double)p.desc[k].N * p.desc[k].M;
     const float open = p.fp[k].cull_open;
+    const int segs = (p.desc[k].M + kSegObst - 1) / kSegObst;
     if (open > kThinNeedle || (open > kNeedle && p.desc[k].N > kAxisHorizon))
-      needle = std::max(needle, kNeedlePairs * ((p.desc[k].M + kSegObst - 1) / kSegObst));
+      least = std::max(least, kNeedlePairs * segs);
+    if (segs > 64) least = std::max(least, long_pairs(p.mi_class) * segs);
+    obst += p.desc[k].N > 0 ? p.desc[k].M : 0;
     // a needle of a footprint has no bound: one wave would evaluate all
     if (p.desc[k].M > kSegObst && !std::isfinite(p.fp[k].cull_tau)) return false;
   }
-  return pairs >= kCullPairs && pairs >= kCullObstacles * p.total_stages && pairs >= needle;
+  return pairs >= least && pairs >= kCullObstacles * p.total_stages &&
+         pairs >= cull_stages(p.mi_class) * obst;
 }
 
 // Gives the culled evaluation's tables back: the plan takes the full one.

@@ -152,3 +152,32 @@ def test_many_stages_against_a_small_map(m, mbar, M):
     t = np.arange(m) * 2 * np.pi / m
     fp = (0.5 * np.stack([np.cos(t), np.sin(t)], 1)).astype(np.float32)
     _plain(fp, 20000, M, e.reshape(-1, 4).astype(np.float32), inputs.csr_offsets([mbar] * M), mbar)
+
+
+def _octagons(rng, M, mbar, half):
+    a = np.arange(mbar) * 2 * np.pi / mbar + rng.uniform(0, 1, (M, 1))
+    e = _closed(rng.uniform(-half, half, (M, 1, 2)) +
+                rng.uniform(0.1, 0.5, (M, 1, 1)) * np.stack([np.cos(a), np.sin(a)], 2))
+    return e.reshape(-1, 4).astype(np.float32), inputs.csr_offsets([mbar] * M)
+
+
+@pytest.mark.parametrize("mbar,k,N,M", [(4, 20, 1, 210000), (4, 3, 16, 130000), (4, 1, 32, 400000), (8, 257, 1, 16384),
+                                        (16, 65, 2, 16384), (16, 65, 4, 16384), (4, 257, 1, 16384),
+                                        (8, 2, 32, 130000), (16, 2, 32, 130000)])
+def test_few_stages_per_instance(mbar, k, N, M):
+    """Each obstacle is read for a stage or a few: batches of edge sets per stage, and
+    instances of more than 64 segments."""
+    import torch
+    from paper_2607_04310_amd import api
+    rng = np.random.default_rng(11)
+    half = HALF * np.sqrt(M / 16384)
+    maps = [_octagons(rng, M, mbar, half) for _ in range(2)]
+    insts = [SimpleNamespace(footprint=FOOTPRINTS["hexagon"], poses=inputs.path_poses(rng, N, -half / 2, half / 2),
+                             edges=maps[i % 2][0], obst_off=maps[i % 2][1]) for i in range(k)]
+    a, b = api.Batch(insts, mbar=mbar), api.Batch(insts, mbar=mbar, exhaustive=True)
+    assert all(torch.equal(x.view(torch.uint8), y.view(torch.uint8)) for x, y in zip(a.run(), b.run()))
+    ms = [_time(torch, x.run, 5) for x in (a, b)]
+    a.close()
+    b.close()
+    print(mbar, k, N, M, "default, full:", [round(1e3 * t, 1) for t in ms], flush=True)
+    assert ms[0] <= 1.25 * ms[1], ms

@@ -222,3 +222,24 @@ for w in (0.1, 0.0437, 8.7e-4):
 emit(out)
 """, tmp_path_factory)
     assert got == 4 * ["cull_list"] + 3 * ["cull_main"]
+
+
+def test_batches_that_read_an_obstacle_for_few_stages(tmp_path_factory):
+    """Instances of more than 64 segments, and wide obstacles, ask for more stages; the
+    sizes of test_gpu_cull_long.py are culled."""
+    got = script("""
+def route(k, N, M, mbar):
+    rc, p = plan([(HEX, N, M, M * mbar)] * k, mbar=mbar)
+    r = run(p)[0]
+    lib.psdf_batch_plan_destroy(p)
+    return r == "cull_list"
+few = [route(*c) for c in ((20, 1, 210000, 4), (3, 16, 130000, 4), (1, 120, 130000, 4), (70, 1, 60000, 4),
+                           (257, 1, 16384, 8), (257, 2, 16384, 8), (65, 5, 16384, 16), (65, 6, 16384, 16),
+                           (3, 12, 130000, 8), (2, 32, 130000, 8), (3, 16, 130000, 16))]
+long = [route(1, 150, 70000, mbar) for mbar in (4, 8, 16)]
+for M in (65536, 65537, 140000):
+    rc, p = plan([(HEX, 300, 16384, 65536)] + [(HEX[::2], N, M, 4 * M) for N in (70, 60, 1)])
+    long.append(run(p)[0] == "cull_list")
+emit([few, long])
+""", tmp_path_factory)
+    assert got == [[False, False, True, True, False, True, False, True, False, True, True], 6 * [True]]
