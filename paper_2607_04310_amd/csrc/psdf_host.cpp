@@ -199,9 +199,14 @@ int check_edges(const psdf_edges* in, psdf_edges* out) {
 LaunchShape choose_shape(const FpConst& F, int mbar, int N, int M) {
   if (cull_plain(F, mbar, N, M)) {
     // every stage block reads and bounds the segment's edges anew, so as few
-    // blocks as cover the chip: four waves (stages) at a time
+    // blocks as cover the chip: four waves (stages) at a time; fewer where the
+    // edges are read one by one.  Whole calls, 1024 -> 512 (from 128 segments:
+    // -> one block per 64 stages), full: eight edges 200 x 16384 75 -> 54 us (72), 5 x
+    // 1000000 145 -> 91 (104), 16 x 250000 87 -> 52 (84); sixteen 50 x 60000 223 ->
+    // 101 (193), 16 x 250000 311 -> 79 (246); but 20000 x 400 84 -> 99.
     const long segs = (M + kCullBlk - 1) / kCullBlk;
-    const long want = (1024 + segs - 1) / segs;      // stage blocks
+    const long cover = obst_class(mbar) == 4 || segs < 4 ? 1024 : segs < 128 ? 512 : segs;
+    const long want = (cover + segs - 1) / segs;     // stage blocks
     const long sb = ((N + want - 1) / want + 3) / 4 * 4;
     return LaunchShape{kCullBlk, (int)std::min<long>(sb, kMaxStageBlock)};
   }

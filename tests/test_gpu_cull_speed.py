@@ -181,3 +181,13 @@ def test_few_stages_per_instance(mbar, k, N, M):
     b.close()
     print(mbar, k, N, M, "default, full:", [round(1e3 * t, 1) for t in ms], flush=True)
     assert ms[0] <= 1.25 * ms[1], ms
+
+
+@pytest.mark.parametrize("m", [3, 6])
+@pytest.mark.parametrize("mbar,N,M", [(8, 1000, 1100), (8, 200, 16384), (8, 16, 250000), (8, 5, 1000000),
+                                      (16, 50, 60000), (16, 9, 250000), (4, 50, 60000)])
+def test_plain_call_on_wide_obstacles(m, mbar, N, M):
+    rng = np.random.default_rng(10)
+    t = np.arange(m) * 2 * np.pi / m
+    fp = (0.5 * np.stack([np.cos(t), np.sin(t)], 1)).astype(np.float32)
+    _plain(fp, N, M, *_octagons(rng, M, mbar, HALF * np.sqrt(M / 16384)), mbar)
