@@ -327,8 +327,14 @@ __global__ __launch_bounds__(64 * NW) void small_kernel(
 constexpr int kQuadWaves = 8;
 // Which of the two: a quad costs about twice the instructions per obstacle,
 // so it is for calls that do not fill the chip (always for one wave, where
-// small_kernel's would be mostly empty).
+// small_kernel's would be mostly empty).  Of free segments a quad evaluates the one
+// edge four times over, where small_kernel has an instance for them: for two waves
+// at most (50 stages, small_kernel / this: 33 segments 6.3 / 6.6 us, 64 6.3 / 6.9, 128
+// 6.6 / 7.1).
 constexpr long kQuadWork = 8192;   // stages times waves squared, at most
+inline bool quad_pays(int mbar, int nw, int N) {
+  return nw == 1 || (nw <= (mbar == 1 ? 2 : kQuadWaves) && (long)N * nw * nw <= kQuadWork);
+}
 
 template <int MF>
 __global__ __launch_bounds__(64 * kQuadWaves) void small_quad_kernel(
@@ -448,7 +454,7 @@ template <int MF>
 hipError_t launch_small_mf(const FpConst& F, const float* poses, int N, const psdf_edges& e,
                            const EpiOut& O, hipStream_t st) {
   const int nw = (e.M + 15) / 16;
-  if (nw <= kQuadWaves && (nw == 1 || (long)N * nw * nw <= kQuadWork))
+  if (quad_pays(e.mbar, nw, N))
     small_quad_kernel<MF><<<N, 64 * nw, 0, st>>>(F, poses, N, e.ax, e.ay, e.bx, e.by, e.obst_off,
                                                  e.E, e.M, O);
   else if (e.M <= 64)

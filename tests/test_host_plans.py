@@ -243,3 +243,14 @@ for M in (65536, 65537, 140000):
 emit([few, long])
 """, tmp_path_factory)
     assert got == [[False, False, True, True, False, True, False, True, False, True, True], 6 * [True]]
+
+
+def test_small_calls(tmp_path_factory):
+    """A quad of lanes per obstacle for few stages; not for more than 32 free segments,
+    whose one edge a quad evaluates four times."""
+    got = script("""
+emit([plain(HEX, N, M, mbar=b)[0] for N, M, b in (
+    (50, 16, 1), (50, 32, 1), (50, 33, 1), (1, 128, 1), (50, 33, 2), (50, 128, 4), (300, 128, 4), (50, 129, 4))])
+""", tmp_path_factory)
+    quad, lane = "small_quad", "small_kernel"
+    assert got == [quad, quad, lane, lane, quad, quad, lane, lane]
