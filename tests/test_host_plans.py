@@ -254,3 +254,16 @@ emit([plain(HEX, N, M, mbar=b)[0] for N, M, b in (
 """, tmp_path_factory)
     quad, lane = "small_quad", "small_kernel"
     assert got == [quad, quad, lane, lane, quad, quad, lane, lane]
+
+
+def test_soft_minimum_that_reaches_far(tmp_path_factory):
+    """A stage looks at all obstacles within log(axes) / eta."""
+    got = script("""
+out = []
+for par in (params(eta=1000.0), params(eta=1.0), params(eta=0.1), params(eta=float("inf")), params(eps_sat=1.0),
+            params(eps_sat=20.0)):
+    rc, p = plan([(HEX, 300, 16384, 65536)], par=par)
+    out.append(run(p)[0] == "cull_list")
+emit(out)
+""", tmp_path_factory)
+    assert got == [True, True, False, True, True, False]
