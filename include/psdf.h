@@ -349,8 +349,10 @@ int psdf_batch_plan_create(psdf_batch_plan** plan, const psdf_batch_desc* desc, 
 void psdf_batch_plan_destroy(psdf_batch_plan* plan);
 
 /* Evaluate every instance: d, edge, obst, grad and keys as described above.
- * A batch of enough (stage, obstacle) pairs, with enough obstacles per stage,
- * is evaluated culled: a bound on every pair (from the obstacle's bounding
+ * A batch of enough (stage, obstacle) pairs, with enough obstacles per stage
+ * (and stages per obstacle where that has many edges, or an instance many
+ * obstacles), is evaluated culled, unless a footprint's corner is too sharp or
+ * eps or 1 / eta too large for that to be the faster way: a bound on every pair (from the obstacle's bounding
  * box) leaves a few obstacles per stage, which alone are evaluated, in two
  * launches on `stream`; the outputs are those of the full
  * evaluation bit for bit, for every input.  With PSDF_BATCH_EXHAUSTIVE, or
