@@ -352,10 +352,10 @@ void psdf_batch_plan_destroy(psdf_batch_plan* plan);
  * A batch of enough (stage, obstacle) pairs, with enough obstacles per stage
  * (and stages per obstacle where that has many edges, or an instance many
  * obstacles), is evaluated culled, unless a footprint's corner is too sharp or
- * eps or 1 / eta too large for that to be the faster way: a bound on every pair (from the obstacle's bounding
- * box) leaves a few obstacles per stage, which alone are evaluated, in two
- * launches on `stream`; the outputs are those of the full
- * evaluation bit for bit, for every input.  With PSDF_BATCH_EXHAUSTIVE, or
+ * eps or 1 / eta too large for that to be the faster way: a bound on every
+ * pair (from the obstacle's bounding box) leaves a few obstacles per stage,
+ * which alone are evaluated, in two launches on `stream`; the outputs are
+ * those of the full evaluation bit for bit, for every input.  With PSDF_BATCH_EXHAUSTIVE, or
  * after psdf_batch_set_shape, every pair is evaluated.  In the full
  * evaluation the launches of the different footprint sizes run concurrently: they fork
  * from `stream` onto up to three plan-owned side streams with events and
