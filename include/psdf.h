@@ -446,11 +446,14 @@ int psdf_batch_screened(psdf_batch_plan* plan, const float* theta, int32_t pool,
  * than 512 obstacles have LB_i <= T, when the bound of the obstacles outside
  * its instance's horizon list is not above T, or when that list is unusable.
  * Same assumptions, limits and optional outputs as psdf_batch_screened
- * (stage_cand counts the seed).  Without the optional outputs, a plan that
- * psdf_batch evaluates culled is evaluated the same way here (boxes instead of
- * circles, lists that leave no stage to a full evaluation), from the staged
- * boxes where psdf_batch_stage took them, and with an eps above 1e-6, where no
- * circle bounds the evaluation, every pair is evaluated. */
+ * (stage_cand counts the seed).  Without the optional outputs, a plan of
+ * at least 4 million pairs and 512 obstacles per stage is evaluated as a culled
+ * psdf_batch is (boxes instead of circles, lists that leave no stage to a full
+ * evaluation, obstacles of any kind), from the staged boxes where
+ * psdf_batch_stage took them, unless it is PSDF_BATCH_EXHAUSTIVE, a shape was
+ * set, the tuner found the full evaluation faster, or eps is above 2.5e-9; and
+ * with an eps above 1e-6, where no circle bounds the evaluation, every pair is
+ * evaluated. */
 int psdf_batch_screened_bound(psdf_batch_plan* plan, const float* poses, const float* ax,
                               const float* ay, const float* bx, const float* by,
                               const int32_t* obst_off, float* d, int32_t* edge, int32_t* obst,
@@ -470,7 +473,7 @@ int psdf_batch_screened_bound(psdf_batch_plan* plan, const float* poses, const f
  * certificate exclude the true winner).  The first call allocates device
  * memory held by the plan: 16 bytes per obstacle for the circles and
  * 40 * edge class + 16 bytes for the rows, and, where they fit, 80 bytes for the
- * boxes and records of a batch that psdf_batch culls; each call enqueues one or
+ * boxes and records where psdf_batch_screened_bound reads them; each call enqueues one or
  * two kernels on `stream`.  Same limits as psdf_batch_screened. */
 int psdf_batch_stage(psdf_batch_plan* plan, const float* ax, const float* ay, const float* bx,
                      const float* by, const int32_t* obst_off, hipStream_t stream);

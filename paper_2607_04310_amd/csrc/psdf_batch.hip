@@ -81,6 +81,9 @@ struct psdf_batch_plan {
   // segments and stage records, and its lists (rewritten by every call)
   bool cull_ready = false;   // the tables below exist
   bool culled = false;
+  // whether psdf_batch_screened_bound takes it: where the tables exist, unless a
+  // shape was set or the tuner found the full evaluation faster
+  bool bound_culled = false;
   int n_segs = 0;
   FpRow* d_frows = nullptr;
   CullSeg* d_segs = nullptr;
@@ -443,9 +446,22 @@ double cull_stages(int mi_class) { return mi_class == 4 ? 0.0 : mi_class == 8 ? 
 // eta 1 (3 m) 145 / 29 us, 0.1 (30 m) 145 / 176.
 constexpr float kCullFloor = 10.0f;      // metres
 
-bool cull_pays(const psdf_batch_plan& p) {
-  double pairs = 0.0, obst = 0.0, least = kCullPairs;
+// Whether the plan gets the tables: the bound form takes them (its circles are no
+// better against needles and hold for convex obstacles only), and the tuner may.
+bool cull_possible(const psdf_batch_plan& p) {
+  double pairs = 0.0;
   if (p.n_inst > 0 && !cull_edges_bounded(p.fp[0])) return false;   // one eps for all
+  for (int k = 0; k < p.n_inst; ++k) {
+    pairs += (double)p.desc[k].N * p.desc[k].M;
+    // a needle of a footprint has no bound: one wave would evaluate all
+    if (p.desc[k].M > kSegObst && !std::isfinite(p.fp[k].cull_tau)) return false;
+  }
+  return pairs >= kCullPairs && pairs >= kCullObstacles * p.total_stages;
+}
+
+// Whether psdf_batch takes them.
+bool cull_pays(const psdf_batch_plan& p) {
+  double pairs = 0.0, obst = 0.0, least = 0.0;
   for (int k = 0; k < p.n_inst; ++k) {
     pairs += (double)p.desc[k].N * p.desc[k].M;
     const float open = p.fp[k].cull_open;
@@ -455,11 +471,8 @@ bool cull_pays(const psdf_batch_plan& p) {
     if (segs > 64) least = std::max(least, long_pairs(p.mi_class) * segs);
     obst += p.desc[k].N > 0 ? p.desc[k].M : 0;
     if (p.fp[k].sd_floor > kCullFloor && std::isfinite(p.fp[k].cull_tau)) return false;
-    // a needle of a footprint has no bound: one wave would evaluate all
-    if (p.desc[k].M > kSegObst && !std::isfinite(p.fp[k].cull_tau)) return false;
   }
-  return pairs >= least && pairs >= kCullObstacles * p.total_stages &&
-         pairs >= cull_stages(p.mi_class) * obst;
+  return pairs >= least && pairs >= cull_stages(p.mi_class) * obst;
 }
 
 // Gives the culled evaluation's tables back: the plan takes the full one.
@@ -474,7 +487,7 @@ void cull_free(psdf_batch_plan* p) {
   p->d_cstages = nullptr;
   p->d_crec = nullptr;
   p->d_ccnt = nullptr;
-  p->cull_ready = p->culled = false;
+  p->cull_ready = p->culled = p->bound_culled = false;
 }
 
 // Segments, stage records and lists of the culled evaluation.
@@ -729,11 +742,11 @@ static int screened_run(psdf_batch_plan* p, bool bound, const float* theta, int3
     circ = p->d_circ;
   }
   const bool outputs_alone = !stage_cand && !stage_cert && !cand_keys;
-  // nothing bounds the evaluation: all pairs, as psdf_batch takes them (a culled
-  // plan's eps is smaller)
+  // nothing bounds the evaluation: all pairs, as psdf_batch takes them (the eps of a
+  // plan with culled tables is smaller)
   if (bound && outputs_alone && p->n_inst > 0 && !circles_bounded(p->fp[0]))
     return run(p, poses, ax, ay, bx, by, off, d, edge, obst, grad, keys, stream, false);
-  if (bound && p->culled && outputs_alone) {
+  if (bound && p->bound_culled && outputs_alone) {
     // the same scheme with boxes for circles and lists that leave no stage
     // uncertified: nothing to fall back from, two launches.  (On 64 x 50 x
     // 16384 the circles' 512-entry lists leave some stages of most draws to
@@ -841,7 +854,7 @@ int psdf_batch_stage(psdf_batch_plan* p, const float* ax, const float* ay, const
       if (err != hipSuccess) p->d_rows = nullptr;
     }
     if (err != hipSuccess) return hip_status(err);
-    const bool boxes = p->culled && stage_boxes(p);
+    const bool boxes = p->bound_culled && stage_boxes(p);
     const dim3 grid((p->max_M + 255) / 256, p->n_inst);
 #define PSDF_STAGE_BATCH(MI)                                                               \
   stage_batch_kernel<MI><<<grid, 256, 0, stream>>>(p->d_fp, p->d_inst, ax, ay, bx, by, off, \
@@ -1093,7 +1106,7 @@ int psdf_batch_plan_create(psdf_batch_plan** out, const psdf_batch_desc* desc, i
   }
   int rc = build_items(p, sh);
   if (rc) { psdf_batch_plan_destroy(p); return rc; }
-  if (!(flags & PSDF_BATCH_EXHAUSTIVE) && p->sum_M + kCullPad < 0x7fffffffu && cull_pays(*p)) {
+  if (!(flags & PSDF_BATCH_EXHAUSTIVE) && p->sum_M + kCullPad < 0x7fffffffu && cull_possible(*p)) {
     const hipError_t ce = cull_create(p);
     if (ce == hipErrorOutOfMemory) {
       // the full evaluation needs none of these tables (64 bytes per obstacle)
@@ -1104,7 +1117,8 @@ int psdf_batch_plan_create(psdf_batch_plan** out, const psdf_batch_desc* desc, i
       psdf_batch_plan_destroy(p);
       return rc;
     } else {
-      p->culled = true;
+      p->culled = cull_pays(*p);
+      p->bound_culled = true;
     }
   }
   *out = p;
@@ -1190,6 +1204,7 @@ int psdf_batch_autotune(psdf_batch_plan* p, const float* poses, const float* ax,
   // the form is this plan's own: which is faster depends on the map and the
   // footprints, and the cache's signature knows sizes only
   p->culled = rc ? was_culled : t_cull < best;
+  if (!rc) p->bound_culled = p->culled;
   best = std::min(best, t_cull);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
@@ -1210,7 +1225,7 @@ int psdf_batch_set_shape(psdf_batch_plan* p, int32_t stages_per_item, int32_t ob
       (obstacles_per_tile != 64 && obstacles_per_tile != 256) || (direct != 0 && direct != 1))
     return set_error(PSDF_EINVAL, "shape sb=%d tile=%d direct=%d (sb 1..%d, tile 64 or 256, direct 0 or 1)",
                      stages_per_item, obstacles_per_tile, direct, kMaxStageBlock);
-  p->culled = false;   // the shape is the full evaluation's
+  p->culled = p->bound_culled = false;   // the shape is the full evaluation's
   return build_items(p, Shape{stages_per_item, obstacles_per_tile / 64, direct});
 }
 

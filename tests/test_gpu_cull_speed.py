@@ -105,8 +105,8 @@ def test_batch_is_not_slower_than_the_full_evaluation(kind, fp):
                                    (16, 200, 4096), (4, 200, 16384)])
 @pytest.mark.parametrize("fp", ["20 degrees", "5 degrees", "0.1 degrees"])
 def test_long_horizons_are_not_slower(fp, k, N, M):
-    """(The bound form of a batch that is not culled is screened by circles, which
-    leave chains to its full evaluation.)"""
+    """(The bound form stays culled, and exact on chains, where the batch itself takes
+    the full evaluation.)"""
     full, out = _batch("chains", FOOTPRINTS[fp], k, N, M)
     assert out["culled"] <= 1.25 * full, (full, out)
 

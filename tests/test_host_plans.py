@@ -267,3 +267,27 @@ for par in (params(eta=1000.0), params(eta=1.0), params(eta=0.1), params(eta=flo
 emit(out)
 """, tmp_path_factory)
     assert got == [True, True, False, True, True, False]
+
+
+def test_bound_form_of_plans_that_the_batch_does_not_cull(tmp_path_factory):
+    """Where a footprint, the stages per obstacle or eta speak against it, psdf_batch is
+    not culled; the bound form still is, and the tuner still times the culled form (here
+    the form of fewer launches is the faster)."""
+    got = script("""
+def needle(w):
+    return [[-0.5, 0.0], [0.5, -w], [0.5, w]]
+out = []
+for insts, mbar, par in (([(needle(8.7e-4), 300, 16384, 65536)], 4, None), ([(HEX, 2, 16384, 16384 * 16)] * 130, 16, None),
+                         ([(HEX, 300, 16384, 65536)], 4, params(eta=0.1))):
+    rc, p = plan(insts, mbar=mbar, par=par)
+    out.append([run(p)[0], bound(p), stage(p)[1], bound(p)])
+    lib.psdf_batch_set_shape(p, 8, 64, 1)
+    out[-1].append("screen_bound" in bound(p))
+    rc, p = plan(insts + [(HEX[:5], 1, 1, 1)], mbar=mbar, par=par, flags=_lib.PSDF_BATCH_AUTOTUNE)
+    autotune(p)
+    out[-1].append(run(p)[0])
+emit(out)
+""", tmp_path_factory)
+    both = ["cull_list", "cull_stage_kernel"]
+    want = ["batch_kernel", both, ["stage_batch", "cull_stage_edges"], both, True, "cull_list"]
+    assert got == 3 * [want]
